@@ -34,8 +34,7 @@ constexpr unsigned long long kNoErr = ~0ull;
 constexpr int kTooDeep = 0x7fffffff;  // error-word node of "depth * num_ops too large for the sort keys"
 constexpr long long kMaxKeys = 1LL << 30;
 constexpr int kBlock = 256;
-constexpr int kMaxOps = 256;  // the op table travels as a kernel argument (2 KB)
-constexpr int kDepthLdsInts = 8192;  // 32 KiB per workgroup; larger graphs use global scratch
+constexpr int kMaxOps = 256;  // the op table travels as a kernel argument
 constexpr int kScanItems = 8;        // items per thread in device-wide scans
 constexpr int kScanTile = kBlock * kScanItems;
 constexpr int kRadixItems = 8;
@@ -43,12 +42,14 @@ constexpr int kRadixTile = kBlock * kRadixItems;
 
 struct OpTable {
   int n;
-  int arity[kMaxOps];
-  int has_input[kMaxOps];
+  unsigned char bits[kMaxOps];  // arity, and 4 where the operation reads the leaf table
+  __host__ __device__ int arity(int op) const { return bits[op] & 3; }
+  __host__ __device__ int has_input(int op) const { return bits[op] >> 2; }
 };
 
 // error word: ((node + 1) << 8) | (-code); structural errors use node + 1 = 0.  atomicMin keeps the
-// lowest node with an error and, within it, the first check in the order op, arity, child, input.
+// lowest node with an error and, within it, the first check in the order op, arity, child, input.  Cycles have a word
+// of their own: a graph's counts only where no check of any graph failed.
 __device__ __forceinline__ void report(unsigned long long* err, int node_plus_1, int code) {
   unsigned long long w = ((unsigned long long)(unsigned)node_plus_1 << 8) | (unsigned long long)(-code);
   atomicMin(err, w);
@@ -120,118 +121,294 @@ __global__ void k_node_graph(const int* gp, int* node_graph, const unsigned long
   for (int v = gp[g] + threadIdx.x; v < gp[g + 1]; v += blockDim.x) node_graph[v] = g;
 }
 
-__global__ void k_check_nodes(const int* node_op, const int* cp, const int* ci, const int* node_input,
-                              const int* node_graph, int N, int num_inputs, OpTable ops,
-                              unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= N) return;
-  const int op = node_op[v];
-  if (op < 0 || op >= ops.n) { report(err, v + 1, FOLD_E_OP); return; }
-  const int a = cp[v], b = cp[v + 1];
-  if (b - a != ops.arity[op]) { report(err, v + 1, FOLD_E_ARITY); return; }
-  const int gv = node_graph[v];
-  for (int j = a; j < b; ++j) {
-    int c = ci[j];
-    if (c == -1) continue;
-    if (c < 0 || c >= N || node_graph[c] != gv) { report(err, v + 1, FOLD_E_CHILD); return; }
+// ---------------------------------------------------------------- depth (one workgroup per graph)
+
+// Depths of one graph, bottom-up over its reverse edges: the node that delivers a parent's last child finishes that
+// parent and goes on with it, so a chain runs in one lane from step to step with no barrier and no queue.  What
+// bounds it is the chain of dependent LDS accesses per step (the parent link, then one returning atomic); a
+// level-synchronous frontier paid two barriers, a queue and generic-address atomics per level instead (4,096 graphs,
+// 2.0 M nodes, 511-node chains among them: 700 us, now 182; 1,024 sentiment trees: 101 us, now 26; 512 LSTM chains of up to 100 steps
+// under reduce trees: 75 us, now 64).
+// Parents of a node are a linked list of its edges; a node with one parent keeps that parent's number itself.  A lane
+// that finishes several parents at once goes on with the lowest (the nearest one up a chain, where nodes are numbered
+// children first) and puts the others on a list, which the next round takes.
+//
+// Where the links live: Lds, or Glob for a graph that does not fit (the same steps on 32-bit indices in scratch
+// memory; what atomics write is read through atomics there, past the first-level cache).  ARITY2: at most two
+// children, and one atomic both counts a child in and hands over its depth (count in the top byte, the depths summed
+// below it: the second child reads the first one's); otherwise a maximum and a count.
+constexpr int kGraphThreads = 128;
+
+template <bool ARITY2>
+struct LdsLinks {
+  static constexpr unsigned kNone = 0xffffu, kSingle = 0x80000000u;  // kNone has no kSingle bit
+  static constexpr int kNodeBytes = ARITY2 ? 10 : 14, kEdgeBytes = 4;
+  uint32_t *state, *depth, *head, *edge;
+  uint16_t* list;
+  __device__ __forceinline__ LdsLinks(char* at, int n, int e) {
+    state = reinterpret_cast<uint32_t*>(at);
+    head = state + n;
+    depth = head + n;
+    edge = ARITY2 ? depth : depth + n;
+    list = reinterpret_cast<uint16_t*>(edge + e);
   }
-  const int inp = node_input[v];
-  if (ops.has_input[op]) {
-    if (inp < 0 || inp >= num_inputs) report(err, v + 1, FOLD_E_INPUT);
-  } else if (inp != -1) {
-    report(err, v + 1, FOLD_E_INPUT);
+  // edge j comes from parent p, the node's next one is nx
+  __device__ __forceinline__ void set_edge(int j, int p, unsigned nx) const { edge[j] = (unsigned)p | nx << 16; }
+  __device__ __forceinline__ int get_edge(unsigned j, unsigned& nx) const {
+    const uint32_t x = edge[j];
+    nx = x >> 16;
+    return (int)(x & 0xffffu);
+  }
+  __device__ __forceinline__ unsigned get_head(int v) const { return head[v]; }
+  __device__ __forceinline__ void set_head(int v, unsigned h) const { head[v] = h; }
+  __device__ __forceinline__ unsigned link(int c, int j) const { return atomicExch(&head[c], (unsigned)j); }
+  __device__ __forceinline__ void wait_for(int v, int children) const {
+    if constexpr (ARITY2) {
+      state[v] = (unsigned)(2 - children) << 24;
+    } else {
+      state[v] = (unsigned)children;
+      depth[v] = 0;
+    }
+  }
+  __device__ __forceinline__ void set_depth(int v, int d) const {
+    if constexpr (ARITY2) state[v] = (unsigned)d;
+    else depth[v] = (unsigned)d;
+  }
+  __device__ __forceinline__ int get_depth(int v) const { return (int)(ARITY2 ? state[v] : depth[v]); }
+  // a child one step below depth d reports to p; true when it was the last one, with p's depth
+  __device__ __forceinline__ bool arrive(int p, int d, int& dp) const {
+    if constexpr (ARITY2) {
+      const uint32_t old = atomicAdd(&state[p], (1u << 24) + (unsigned)d);
+      dp = max((int)(old & 0xffffffu), d);
+      return (old >> 24) == 1;
+    } else {
+      atomicMax(&depth[p], (unsigned)d);
+      if (atomicSub(&state[p], 1u) != 1u) return false;
+      dp = (int)__hip_atomic_load(&depth[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      return true;
+    }
+  }
+};
+
+template <bool ARITY2>
+struct GlobLinks {
+  static constexpr unsigned kNone = 0x7fffffffu, kSingle = 0x80000000u;
+  static constexpr int kNodeInts = 4, kEdgeInts = 2;  // of scratch
+  unsigned long long* state;  // ARITY2: count and sum of depths; else the count (low) and the depth (high word)
+  int *head, *list, *next, *from;
+  __device__ __forceinline__ GlobLinks(int* at, int n, int e) {
+    state = reinterpret_cast<unsigned long long*>(at);
+    head = at + 2 * (size_t)n;
+    list = head + n;
+    next = list + n;
+    from = next + e;
+  }
+  template <class U>
+  __device__ __forceinline__ static U now(const U* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ unsigned* word(int v, int k) const { return reinterpret_cast<unsigned*>(state + v) + k; }
+  __device__ __forceinline__ void set_edge(int j, int p, unsigned nx) const {
+    from[j] = p;
+    next[j] = (int)nx;
+  }
+  __device__ __forceinline__ int get_edge(unsigned j, unsigned& nx) const {
+    nx = (unsigned)next[j];
+    return from[j];
+  }
+  __device__ __forceinline__ unsigned get_head(int v) const { return (unsigned)now(head + v); }
+  __device__ __forceinline__ void set_head(int v, unsigned h) const { head[v] = (int)h; }
+  __device__ __forceinline__ unsigned link(int c, int j) const { return (unsigned)atomicExch(&head[c], j); }
+  __device__ __forceinline__ void wait_for(int v, int children) const {
+    state[v] = ARITY2 ? (unsigned long long)(2 - children) << 56 : (unsigned long long)children;
+  }
+  __device__ __forceinline__ void set_depth(int v, int d) const {
+    if constexpr (ARITY2) state[v] = (unsigned long long)d;
+    else *word(v, 1) = (unsigned)d;
+  }
+  __device__ __forceinline__ int get_depth(int v) const { return (int)(ARITY2 ? now(state + v) : now(word(v, 1))); }
+  __device__ __forceinline__ bool arrive(int p, int d, int& dp) const {
+    if constexpr (ARITY2) {
+      const unsigned long long old = atomicAdd(&state[p], (1ull << 56) + (unsigned)d);
+      dp = max((int)(old & 0xffffffffull), d);
+      return (old >> 56) == 1;
+    } else {
+      atomicMax(word(p, 1), (unsigned)d);
+      __threadfence();  // the maximum is in before the count
+      if (atomicSub(word(p, 0), 1u) != 1u) return false;
+      dp = (int)now(word(p, 1));
+      return true;
+    }
+  }
+};
+
+// what the workgroup of one graph shares beside the links
+struct GraphShared {
+  int tail, done, deepest, parents, bad;
+};
+
+struct GraphArgs {
+  const int *gp, *cp, *ci;
+  int *depth, *indeg, *scratch;
+  unsigned long long *err, *cycle;
+  int* meta;  // [0] max depth, [1] max parents
+  // node checks (fold batches): op, arity and children, input
+  const int *node_op, *node_input;
+  int num_inputs;
+};
+
+// Links the graph (nodes g0 .. g0 + n - 1, edges e0 .. e0 + e - 1) and, for a fold batch, checks every node first
+// (the lowest node with an error counts, and its first check).
+template <class L, bool CHECK>
+__device__ __forceinline__ void run_graph(const L& g, const GraphArgs& a, const OpTable& ops, GraphShared& sh, int g0,
+                                          int n, int e0, int e) {
+  const int t = threadIdx.x, T = blockDim.x;
+  for (int v = t; v < n; v += T) g.set_head(v, L::kNone);
+  if (t == 0) sh = {0, 0, 0, 0, 0};
+  __syncthreads();
+  for (int v = t; v < n; v += T) {
+    const int lo = a.cp[g0 + v], hi = a.cp[g0 + v + 1];
+    if constexpr (CHECK) {
+      int fault = 0;
+      const int op = a.node_op[g0 + v], inp = a.node_input[g0 + v];
+      if (op < 0 || op >= ops.n) {
+        fault = FOLD_E_OP;
+      } else if (hi - lo != ops.arity(op)) {
+        fault = FOLD_E_ARITY;
+      } else {
+        for (int j = lo; j < hi; ++j)
+          if (a.ci[j] != -1 && (a.ci[j] < g0 || a.ci[j] >= g0 + n)) fault = FOLD_E_CHILD;
+        if (!fault && (ops.has_input(op) ? inp < 0 || inp >= a.num_inputs : inp != -1)) fault = FOLD_E_INPUT;
+      }
+      if (fault) {
+        report(a.err, g0 + v + 1, fault);
+        sh.bad = 1;
+        continue;
+      }
+    }
+    int children = 0;
+    for (int j = lo; j < hi; ++j) {
+      const int c = a.ci[j] - g0;
+      if (a.ci[j] < 0) continue;
+      ++children;
+      g.set_edge(j - e0, v, g.link(c, j - e0));
+    }
+    if (children) {
+      g.wait_for(v, children);
+    } else {
+      g.set_depth(v, 1);
+      g.list[atomicAdd(&sh.tail, 1)] = v;
+    }
+  }
+  __syncthreads();
+  if (sh.bad) return;
+  int parents = 0;
+  for (int v = t; v < n; v += T) {
+    int k = 0;
+    const unsigned h = g.get_head(v);
+    unsigned nx;
+    int p = 0;
+    for (unsigned j = h; j != L::kNone; j = nx) p = g.get_edge(j, nx), ++k;
+    if (k == 1) g.set_head(v, L::kSingle | (unsigned)p);
+    a.indeg[g0 + v] = k;
+    parents = max(parents, k);
+  }
+  int done = 0, deepest = 0;
+  for (int lo = 0;;) {
+    __syncthreads();
+    const int hi = sh.tail;
+    __syncthreads();
+    if (lo == hi) break;
+    for (int i = lo + t; i < hi; i += T) {
+      int v = g.list[i], d = g.get_depth(v);
+      unsigned h = g.get_head(v);
+      while (true) {
+        a.depth[g0 + v] = d;
+        ++done;
+        int nv = -1, nd = 0;
+        unsigned nh = L::kNone;
+        if (h & L::kSingle) {  // the parent's own link is read along with the report: one LDS latency a step
+          const int p = (int)(h & ~L::kSingle);
+          nh = g.get_head(p);
+          if (g.arrive(p, d + 1, nd)) nv = p;
+        } else if (h != L::kNone) {
+          unsigned nx;
+          int p = g.get_edge(h, nx);
+          while (true) {  // the next edge is read along with the report
+            const bool more = nx != L::kNone;
+            unsigned nx2 = L::kNone;
+            const int p2 = more ? g.get_edge(nx, nx2) : 0;
+            int dp;
+            if (g.arrive(p, d + 1, dp)) {
+              int other = p, od = dp;
+              if (nv < 0 || p < nv) other = nv, od = nd, nv = p, nd = dp;
+              if (other >= 0) {
+                g.set_depth(other, od);
+                g.list[atomicAdd(&sh.tail, 1)] = other;
+              }
+            }
+            if (!more) break;
+            p = p2, nx = nx2;
+          }
+          if (nv >= 0) nh = g.get_head(nv);
+        }
+        if (nv < 0) break;
+        v = nv, d = nd, h = nh;
+      }
+      deepest = max(deepest, d);  // a chain's last node is its deepest
+    }
+    lo = hi;
+  }
+  for (int s = kWave / 2; s; s >>= 1) {
+    done += __shfl_xor(done, s);
+    deepest = max(deepest, __shfl_xor(deepest, s));
+    parents = max(parents, __shfl_xor(parents, s));
+  }
+  if ((t & (kWave - 1)) == 0) {
+    atomicAdd(&sh.done, done);
+    atomicMax(&sh.deepest, deepest);
+    atomicMax(&sh.parents, parents);
+  }
+  __syncthreads();
+  if (t == 0) {
+    if (sh.done < n) {
+      report(a.cycle, g0 + 1, FOLD_E_CYCLE);
+    } else {  // most graphs find the batch's maxima there already
+      if (sh.deepest > __hip_atomic_load(&a.meta[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(&a.meta[0], sh.deepest);
+      if (sh.parents > __hip_atomic_load(&a.meta[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(&a.meta[1], sh.parents);
+    }
   }
 }
 
-// ---------------------------------------------------------------- depth (one workgroup per graph)
-
-// meta[0] = max depth, meta[1] = max number of parents of a node
-__global__ __launch_bounds__(kBlock) void k_depth(const int* gp, const int* cp, const int* ci, int* depth,
-                                                  int* indeg, int* scratch, unsigned long long* err,
-                                                  int* meta) {
-  if (*err != kNoErr) return;
-  extern __shared__ int lds[];
-  __shared__ int qn[2];
-  const int g = blockIdx.x, t = threadIdx.x;
-  const int g0 = gp[g], n = gp[g + 1] - g0;
+// The pointer arrays have been checked.  CHECK (fold batches, at most two children): the nodes are checked here;
+// without it their children have been checked too.  lds_bytes: dynamic LDS for the links.
+template <bool CHECK>
+__global__ __launch_bounds__(kGraphThreads) void k_graph_depth(GraphArgs a, OpTable ops, int lds_bytes) {
+  if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 8 == 0) return;  // a pointer array
+  if (!CHECK && *a.err != kNoErr) return;
+  extern __shared__ __attribute__((aligned(16))) char links[];
+  __shared__ GraphShared sh;
+  const int g = blockIdx.x;
+  const int g0 = a.gp[g], n = a.gp[g + 1] - g0;
   if (n == 0) return;
-  const int e0 = cp[g0], e = cp[g0 + n] - e0;
-  const long long need = 6LL * n + 1 + e;
-  int* base = (need <= kDepthLdsInts) ? lds : scratch + (6LL * g0 + g + e0);
-  int* pend = base;         // [n] children not yet done
-  int* dep = pend + n;      // [n]
-  int* pptr = dep + n;      // [n+1] parent-list offsets (counts, then exclusive scan)
-  int* pfill = pptr + n + 1;  // [n]
-  int* q0 = pfill + n;      // [n]
-  int* q1 = q0 + n;         // [n]
-  int* plist = q1 + n;      // [e]
+  const int e0 = a.cp[g0], e = a.cp[g0 + n] - e0;
+  using LL = LdsLinks<CHECK>;
+  using GL = GlobLinks<CHECK>;
+  const bool fits = n < (int)LL::kNone && e < (int)LL::kNone && n * LL::kNodeBytes + e * LL::kEdgeBytes <= lds_bytes;
+  if (fits)
+    run_graph<LL, CHECK>(LL(links, n, e), a, ops, sh, g0, n, e0, e);
+  else
+    run_graph<GL, CHECK>(GL(a.scratch + GL::kNodeInts * (size_t)g0 + GL::kEdgeInts * (size_t)e0, n, e), a, ops, sh, g0,
+                         n, e0, e);
+}
 
-  for (int v = t; v < n; v += kBlock) { pptr[v] = 0; pfill[v] = 0; dep[v] = 0; }
-  if (t == 0) { qn[0] = 0; qn[1] = 0; }
-  __syncthreads();
-  for (int v = t; v < n; v += kBlock) {
-    int cnt = 0;
-    for (int j = cp[g0 + v]; j < cp[g0 + v + 1]; ++j) {
-      int c = ci[j];
-      if (c >= 0) { ++cnt; atomicAdd(&pptr[c - g0], 1); }
-    }
-    pend[v] = cnt;
-  }
-  __syncthreads();
-  block_exscan_array(pptr, n);
-  for (int v = t; v < n; v += kBlock) {
-    for (int j = cp[g0 + v]; j < cp[g0 + v + 1]; ++j) {
-      int c = ci[j];
-      if (c >= 0) {
-        int s = atomicAdd(&pfill[c - g0], 1);
-        plist[pptr[c - g0] + s] = v;
-      }
-    }
-  }
-  __syncthreads();
-  int local_maxpar = 0;
-  for (int v = t; v < n; v += kBlock) {
-    indeg[g0 + v] = pfill[v];
-    local_maxpar = max(local_maxpar, pfill[v]);
-    if (pend[v] == 0) {
-      dep[v] = 1;
-      q0[atomicAdd(&qn[0], 1)] = v;
-    }
-  }
-  __syncthreads();
-  int processed = 0, cur = 0;
-  while (true) {
-    const int cnt = qn[cur];
-    if (cnt == 0) break;
-    processed += cnt;
-    int* Q = cur ? q1 : q0;
-    int* NQ = cur ? q0 : q1;
-    for (int i = t; i < cnt; i += kBlock) {
-      const int v = Q[i];
-      const int dv = dep[v] + 1;
-      for (int k = pptr[v]; k < pptr[v + 1]; ++k) {
-        const int p = plist[k];
-        atomicMax(&dep[p], dv);
-        if (atomicSub(&pend[p], 1) == 1) NQ[atomicAdd(&qn[cur ^ 1], 1)] = p;
-      }
-    }
-    __syncthreads();
-    if (t == 0) qn[cur] = 0;
-    __syncthreads();
-    cur ^= 1;
-  }
-  if (processed < n) {
-    if (t == 0) report(err, g0 + 1, FOLD_E_CYCLE);
-    return;
-  }
-  int local_max = 0;
-  for (int v = t; v < n; v += kBlock) {
-    depth[g0 + v] = dep[v];
-    local_max = max(local_max, dep[v]);
-  }
-  atomicMax(&meta[0], local_max);
-  atomicMax(&meta[1], local_maxpar);
+// LDS for the links of a graph: twice what an average graph takes, at least what a tree of 1,000 nodes takes (eleven
+// such workgroups fit a compute unit) and at most 60 KB; larger graphs use scratch memory
+inline int graph_lds_bytes(long long N, long long E, int G, int node_bytes, int edge_bytes) {
+  const long long mean = (N * node_bytes + E * edge_bytes) / std::max(G, 1);
+  return (int)std::min<long long>(61440, std::max<long long>(1000 * (node_bytes + edge_bytes), 2 * mean + 255) / 256 * 256);
 }
 
 // ---------------------------------------------------------------- device-wide exclusive scan
@@ -304,8 +481,10 @@ __global__ void k_make_keys(const int* depth, const int* node_op, int N, int num
 
 // number of 8-bit radix passes the keys (depth - 1) * num_ops + op need, from the depth found on the
 // device: meta[0] = D, written to *passes (at least 1); a depth whose keys would pass kMaxKeys is an error
-__global__ void k_sort_plan(const int* meta, int num_ops, unsigned long long* err, int* passes) {
+__global__ void k_sort_plan(const int* meta, int num_ops, unsigned long long* err, const unsigned long long* cycle,
+                            int* passes) {
   if (threadIdx.x != 0) return;
+  if (*err == kNoErr && *cycle != kNoErr) *err = *cycle;
   const long long nk = (long long)meta[0] * num_ops;
   if (nk > kMaxKeys) {
     report(err, kTooDeep, FOLD_E_INVALID);
@@ -439,7 +618,7 @@ __global__ void k_group_rows(const int* ng_ptr, int N, const int* g_row_begin, c
   const int end = (g + 1 < ng) ? g_row_begin[g + 1] : N;
   const int rows = end - g_row_begin[g];
   g_rows[g] = rows;
-  g_edges[g] = rows * ops.arity[g_op[g]];
+  g_edges[g] = rows * ops.arity(g_op[g]);
 }
 
 __global__ void k_emit(const int* pos_node, const int* node_pos, const int* gid, const int* g_row_begin,
@@ -451,7 +630,7 @@ __global__ void k_emit(const int* pos_node, const int* node_pos, const int* gid,
   if (p >= N) return;
   const int v = pos_node[p];
   const int g = gid[p];
-  const int a = ops.arity[g_op[g]];
+  const int a = ops.arity(g_op[g]);
   const int off = g_idx_off[g] + (p - g_row_begin[g]) * a;
   const int c0 = cp[v];
   for (int k = 0; k < a; ++k) {
@@ -485,10 +664,10 @@ __global__ void k_fill_ints(int* p, long long n, int v) {
     p[i] = v;
 }
 
-// error word "none", meta zero
+// error words "none", meta zero
 __global__ void k_init_meta(void* em) {
-  if (threadIdx.x == 0) *static_cast<unsigned long long*>(em) = kNoErr;
-  int* meta = reinterpret_cast<int*>(static_cast<unsigned long long*>(em) + 1);
+  if (threadIdx.x < 2) static_cast<unsigned long long*>(em)[threadIdx.x] = kNoErr;
+  int* meta = reinterpret_cast<int*>(static_cast<unsigned long long*>(em) + 2);
   if (threadIdx.x < 8) meta[threadIdx.x] = 0;
 }
 
@@ -576,7 +755,7 @@ __global__ void k_op_rows(const int* op_rows, const int* gid, const int* g_row_b
   const int p = op_rows[q];
   const int g = gid[p];
   const int r = p - g_row_begin[g];
-  const int a = ops.arity[g_op[g]];
+  const int a = ops.arity(g_op[g]);
   op_cpos[2 * q] = a > 0 ? child_pos[g_idx_off[g] + r * a] : -1;
   op_cpos[2 * q + 1] = a > 1 ? child_pos[g_idx_off[g] + r * a + 1] : -1;
   op_inp[q] = input_idx[p];
@@ -591,7 +770,7 @@ __global__ void k_cbase_init(const int* ng_ptr, int N, const int* g_op, const in
   if (*err != kNoErr) return;
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= N || g >= *ng_ptr) return;
-  const int a = ops.arity[g_op[g]], off = g_idx_off[g];
+  const int a = ops.arity(g_op[g]), off = g_idx_off[g];
   int b[2] = {-1, -1};
   for (int k = 0; k < a && k < 2; ++k) b[k] = child_one[off + k] ? child_pos[off + k] : -1;
   cb0[g] = b[0];
@@ -605,7 +784,7 @@ __global__ void k_cbase_check(int N, const int* gid, const int* g_row_begin, con
   if (*err != kNoErr) return;
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= N) return;
-  const int g = gid[p], r = p - g_row_begin[g], a = ops.arity[g_op[g]];
+  const int g = gid[p], r = p - g_row_begin[g], a = ops.arity(g_op[g]);
   for (int k = 0; k < a && k < 2; ++k) {
     int* cb = k == 0 ? cb0 : cb1;
     const int base = cb[g];
@@ -721,8 +900,7 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   OpTable ops{};
   ops.n = K;
   for (int i = 0; i < K; ++i) {
-    ops.arity[i] = b->ops[i].arity;
-    ops.has_input[i] = b->ops[i].has_input;
+    ops.bits[i] = (unsigned char)(b->ops[i].arity | (b->ops[i].has_input ? 4 : 0));
   }
   int device = 0;
   FOLD_HIP_CHECK(hipGetDevice(&device));
@@ -776,14 +954,14 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   // err, then meta: [0] max depth, [1] max parents, [2] radix passes, [3] scratch total, [4] groups, [5] roots,
   // [6] scratch total
   struct ErrMeta {
-    unsigned long long err;
+    unsigned long long err, cycle;  // a cycle counts only where no node check failed
     int meta[8];
   };
   ErrMeta* em = nullptr;
-  int *node_graph = nullptr, *indeg = nullptr, *scratch = nullptr, *edges = nullptr, *stage = nullptr;
+  int *indeg = nullptr, *scratch = nullptr, *edges = nullptr, *stage = nullptr;
   unsigned *ka = nullptr, *kb = nullptr;
   int *va = nullptr, *vb = nullptr, *flag = nullptr, *exs = nullptr, *radix_counts = nullptr, *scan_tmp = nullptr;
-  const long long scratch_ints = 6LL * N + G + E + 1;
+  const long long scratch_ints = GlobLinks<true>::kNodeInts * (long long)N + GlobLinks<true>::kEdgeInts * (long long)E;
   const int B = (N + kRadixTile - 1) / kRadixTile;
   const long long rc = 256LL * std::max(B, 1);
   const long long scan_tmp_n = std::max<long long>(rc, N) / kScanTile + 2;
@@ -794,7 +972,6 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   tmp.reserve(&stage, stage_n);
   tmp.reserve(&op_runs, kMaxOps);
   if (N > 0) {
-    tmp.reserve(&node_graph, N);
     tmp.reserve(&indeg, N);
     tmp.reserve(&scratch, (size_t)scratch_ints);
     tmp.reserve(&edges, N);
@@ -818,17 +995,16 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   hipLaunchKernelGGL(k_check_struct, grid_for(std::max(G + 1, N + 1)), dim3(kBlock), 0, st, b->graph_ptr, G,
                      b->child_ptr, N, E, err);
   if (N > 0) {
-    if (G > 0)
-      hipLaunchKernelGGL(k_node_graph, dim3(G), dim3(kBlock), 0, st, b->graph_ptr, node_graph, err);
-    hipLaunchKernelGGL(k_check_nodes, grid_for(N), dim3(kBlock), 0, st, b->node_op, b->child_ptr,
-                       b->child_idx, b->node_input, node_graph, N, b->num_inputs, ops, err);
-    if (G > 0)
-      hipLaunchKernelGGL(k_depth, dim3(G), dim3(kBlock), kDepthLdsInts * sizeof(int), st, b->graph_ptr,
-                         b->child_ptr, b->child_idx, s.depth, indeg, scratch, err, meta);
+    if (G > 0) {
+      const int lds = graph_lds_bytes(N, E, G, LdsLinks<true>::kNodeBytes, LdsLinks<true>::kEdgeBytes);
+      const GraphArgs ga{b->graph_ptr, b->child_ptr, b->child_idx, s.depth, indeg, scratch, err, &em->cycle, meta,
+                         b->node_op, b->node_input, b->num_inputs};
+      hipLaunchKernelGGL(k_graph_depth<true>, dim3(G), dim3(kGraphThreads), lds, st, ga, ops, lds);
+    }
 
     // sort by (depth - 1) * num_ops + op: as many 8-bit passes as N * num_ops could need are launched; the
     // ones the actual depth does not need copy their tile
-    hipLaunchKernelGGL(k_sort_plan, dim3(1), dim3(64), 0, st, meta, K, err, meta + 2);
+    hipLaunchKernelGGL(k_sort_plan, dim3(1), dim3(64), 0, st, meta, K, err, &em->cycle, meta + 2);
     hipLaunchKernelGGL(k_make_keys, grid_for(N), dim3(kBlock), 0, st, s.depth, b->node_op, N, K, ka, va, err);
     const unsigned long long max_key = std::min<unsigned long long>((unsigned long long)N * K,
                                                                     (unsigned long long)kMaxKeys) - 1;
@@ -1310,11 +1486,11 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   const long long Vmax = 8LL * std::max(N, 1);
   Temp tmp1(st);
   struct ErrMeta {
-    unsigned long long err;
+    unsigned long long err, cycle;
     int meta[8 + kMaxTypes];  // [0] max depth + 1, [1] max parents, [2] values, [3] pass-throughs,
                               // [4] batches, [5] gather entries, [6, 7] scratch totals, [8 + t] constants of type t
   };
-  static_assert(offsetof(ErrMeta, meta) == sizeof(unsigned long long), "k_init_meta's layout");
+  static_assert(offsetof(ErrMeta, meta) == 2 * sizeof(unsigned long long), "k_init_meta's layout");
   ErrMeta* em = nullptr;
   int *node_graph = nullptr, *indeg = nullptr, *scratch = nullptr, *kdepth = nullptr, *depth = nullptr,
       *nout_v = nullptr, *val_ptr = nullptr, *last = nullptr, *npass = nullptr, *pass_ptr = nullptr,
@@ -1322,7 +1498,7 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   tmp1.reserve(&em, 1);
   tmp1.reserve(&node_graph, N);
   tmp1.reserve(&indeg, N);
-  tmp1.reserve(&scratch, (size_t)(6LL * N + G + E + 1));
+  tmp1.reserve(&scratch, GlobLinks<false>::kNodeInts * (size_t)N + GlobLinks<false>::kEdgeInts * (size_t)E);
   tmp1.reserve(&kdepth, N);
   tmp1.reserve(&depth, N);
   tmp1.reserve(&nout_v, N);
@@ -1348,9 +1524,12 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
     if (G > 0) hipLaunchKernelGGL(k_node_graph, dim3(G), dim3(kBlock), 0, st, b->graph_ptr, node_graph, err);
     hipLaunchKernelGGL(k_typed_check, grid_for(N), dim3(kBlock), 0, st, b->node_op, b->in_ptr, b->in_node,
                        b->in_slot, node_graph, N, ops, err);
-    if (G > 0)
-      hipLaunchKernelGGL(k_depth, dim3(G), dim3(kBlock), kDepthLdsInts * sizeof(int), st, b->graph_ptr, b->in_ptr,
-                         b->in_node, kdepth, indeg, scratch, err, meta);
+    if (G > 0) {
+      const int lds = graph_lds_bytes(N, E, G, LdsLinks<false>::kNodeBytes, LdsLinks<false>::kEdgeBytes);
+      const GraphArgs ga{b->graph_ptr, b->in_ptr, b->in_node, kdepth, indeg, scratch, err, err, meta, nullptr, nullptr,
+                         0};
+      hipLaunchKernelGGL(k_graph_depth<false>, dim3(G), dim3(kGraphThreads), lds, st, ga, OpTable{}, lds);
+    }
     hipLaunchKernelGGL(k_typed_nodes, grid_for(N), dim3(kBlock), 0, st, kdepth, b->node_op, N, ops, depth, nout_v,
                        meta, err);
     scan_exclusive(nout_v, val_ptr, N, meta + 2, scan_tmp1, st);
