@@ -691,7 +691,7 @@ int32_t backward_impl(const Sched& s, const Packed& p, const void* table, int64_
       if (count <= 0) continue;
       if (op.kind == FOLD_EMBED) {  // the leaf-table gradient: dh summed over each leaf-table row's rows
         if (d_table)
-          launch_tok_table(s.tok_rows, s.tok_seg, s.tok_start, s.tok_row, s.h_op_row_ptr[o], count, dh, p.ld, p.H,
+          launch_tok_table(s.tok_rows, s.tok_seg, s.tok_start, s.tok_row, s.h_tok_row_ptr[o], count, dh, p.ld, p.H,
                            d_table, tld, st);
         continue;
       }
@@ -716,8 +716,8 @@ int32_t backward_impl(const Sched& s, const Packed& p, const void* table, int64_
         const bool bf = p.dtype == FOLD_BF16;
         float* zsum = part;
         uint16_t* zbf = reinterpret_cast<uint16_t*>(part + (size_t)U * Nw);
-        launch_tok_sum(p.dtype, s.tok_rows, s.tok_seg, s.tok_start, off, count, u0, U, gates, L.gstride, Nw, zsum,
-                       zbf, st);
+        launch_tok_sum(p.dtype, s.tok_rows, s.tok_seg, s.tok_start, s.h_tok_row_ptr[o], count, u0, U, gates, L.gstride,
+                       Nw, zsum, zbf, st);
         DxArgs d{};
         d.rows = U;
         d.H = p.H;

@@ -6,12 +6,12 @@
 //              graph's reverse edges in LDS: a node whose children are all done
 //              gets depth 1 + max(child depths) (the zero state -1 and leaf-table
 //              rows are depth-0 constants).  Unprocessed nodes mean a cycle.
-//   sort       stable LSD radix sort (8-bit digits) of the node ids by the key
-//              (depth - 1) * num_ops + op: ties stay in node-id order
-//   emit       group table, level_ptr, child_pos (pool rows of every edge),
-//              input_idx and root rows; the rows of every op in (op, row) order
-//              for the deferred weight gradients (one more stable radix pass,
-//              keyed by op)
+//   sort       stable LSD radix sort (10-bit digits) of the node ids by the key (depth - 1) * num_ops + op: ties stay in
+//              node-id order.  A pass is a count and a scatter over tiles of 2,048 items (a column scan between them
+//              only where there are many tiles)
+//   emit       two passes over the sorted tiles: sums per tile, then every index: group table, level_ptr, child_pos (pool
+//              rows of every edge), input_idx, root rows, the rows of every op in (op, row) order for the deferred
+//              weight gradients, and the rows that read the leaf table, which one more sort lists by (op, leaf-table row)
 // All results are integers and bit-exact by construction.  Everything runs on
 // the stream without a host round trip until one read-back at the end: arrays
 // are sized by N (levels and groups never outnumber nodes), the radix passes
@@ -37,8 +37,11 @@ constexpr int kBlock = 256;
 constexpr int kMaxOps = 256;  // the op table travels as a kernel argument
 constexpr int kScanItems = 8;        // items per thread in device-wide scans
 constexpr int kScanTile = kBlock * kScanItems;
-constexpr int kRadixItems = 8;
-constexpr int kRadixTile = kBlock * kRadixItems;
+constexpr int kTileThreads = 512, kTileItems = 4, kTile = kTileThreads * kTileItems;  // items of a sort or emit tile
+constexpr int kDigitBits = 10, kDigits = 1 << kDigitBits;
+// Up to this many tiles every tile adds up its predecessors' digit counts itself (32 x 4 KB from the L2, about 3 us);
+// above, a column scan does it once in a launch of its own (1,000 tiles: 4 MB, which every tile would read)
+constexpr int kSelfTiles = 32;
 
 struct OpTable {
   int n;
@@ -57,9 +60,10 @@ __device__ __forceinline__ void report(unsigned long long* err, int node_plus_1,
 
 // ---------------------------------------------------------------- block scan helpers
 
-// exclusive scan of one int per thread over a 256-thread block; returns the prefix, *total = sum
-__device__ int block_exscan_256(int x, int* total) {
-  __shared__ int wsum[kBlock / kWave];
+// exclusive scan of one int per thread over a workgroup of NT threads; returns the prefix, *total = sum
+template <int NT>
+__device__ int block_exscan(int x, int* total) {
+  __shared__ int wsum[NT / kWave];
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
   int v = x;
   for (int d = 1; d < kWave; d <<= 1) {
@@ -69,7 +73,7 @@ __device__ int block_exscan_256(int x, int* total) {
   if (lane == kWave - 1) wsum[w] = v;
   __syncthreads();
   int pre = 0, tot = 0;
-  for (int i = 0; i < kBlock / kWave; ++i) {
+  for (int i = 0; i < NT / kWave; ++i) {
     int s = wsum[i];
     if (i < w) pre += s;
     tot += s;
@@ -79,23 +83,12 @@ __device__ int block_exscan_256(int x, int* total) {
   return pre + v - x;
 }
 
-// in-place exclusive scan of a[0..n) (generic pointer: LDS or global), a[n] = total
-__device__ void block_exscan_array(int* a, int n) {
-  const int t = threadIdx.x;
-  const int chunk = (n + kBlock - 1) / kBlock;
-  const int lo = min(n, t * chunk), hi = min(n, lo + chunk);
-  int s = 0;
-  for (int i = lo; i < hi; ++i) s += a[i];
-  int tot;
-  int pre = block_exscan_256(s, &tot);
-  __syncthreads();
-  for (int i = lo; i < hi; ++i) {
-    int v = a[i];
-    a[i] = pre;
-    pre += v;
-  }
-  if (t == 0) a[n] = tot;
-  __syncthreads();
+// sum of one int per thread over a workgroup of NT threads, in every thread
+template <int NT>
+__device__ int block_sum(int x) {
+  int total;
+  (void)block_exscan<NT>(x, &total);
+  return total;
 }
 
 // ---------------------------------------------------------------- validation
@@ -421,242 +414,576 @@ __global__ void k_scan_reduce(const int* in, int n, int* partial) {
     long long j = base + i;
     if (j < n) s += in[j];
   }
-  int tot;
-  block_exscan_256(s, &tot);
-  if (t == 0) partial[b] = tot;
+  s = block_sum<kBlock>(s);
+  if (t == 0) partial[b] = s;
 }
 
-// single block: exclusive scan of partial[0..nb) in place, *total = sum
-__global__ void k_scan_partials(int* partial, int nb, int* total) {
-  int carry = 0;
-  for (int base = 0; base < nb; base += kBlock) {
-    const int i = base + threadIdx.x;
-    const int x = i < nb ? partial[i] : 0;
-    int tot;
-    const int pre = block_exscan_256(x, &tot);
-    if (i < nb) partial[i] = carry + pre;
-    carry += tot;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *total = carry;
-}
-
-__global__ void k_scan_down(const int* in, int n, const int* partial, int* out) {
+// every workgroup adds up the sums of the tiles before its own (a launch less than a scan of them)
+__global__ void k_scan_down(const int* in, int n, const int* partial, int* out, int* total) {
   const int b = blockIdx.x, t = threadIdx.x;
   const long long base = (long long)b * kScanTile + (long long)t * kScanItems;
   int v[kScanItems];
-  int s = 0;
+  int s = 0, before = 0;
+  for (int i = t; i < b; i += kBlock) before += partial[i];
   for (int i = 0; i < kScanItems; ++i) {
     long long j = base + i;
     v[i] = j < n ? in[j] : 0;
     s += v[i];
   }
+  before = block_sum<kBlock>(before);
   int tot;
-  int pre = block_exscan_256(s, &tot) + partial[b];
+  int pre = block_exscan<kBlock>(s, &tot) + before;
   for (int i = 0; i < kScanItems; ++i) {
     long long j = base + i;
     if (j < n) out[j] = pre;
     pre += v[i];
   }
+  if (b == (int)gridDim.x - 1 && t == 0) *total = before + tot;
 }
 
 // exclusive scan in -> out (may alias), total -> *total (device); temp holds >= ceil(n / tile) ints
 void scan_exclusive(const int* in, int* out, int n, int* total, int* temp, hipStream_t st) {
   const int nb = std::max(1, (n + kScanTile - 1) / kScanTile);
   hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kBlock), 0, st, in, n, temp);
-  hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kBlock), 0, st, temp, nb, total);
-  hipLaunchKernelGGL(k_scan_down, dim3(nb), dim3(kBlock), 0, st, in, n, temp, out);
+  hipLaunchKernelGGL(k_scan_down, dim3(nb), dim3(kBlock), 0, st, in, n, temp, out, total);
 }
 
 // ---------------------------------------------------------------- stable LSD radix sort
 
-__global__ void k_make_keys(const int* depth, const int* node_op, int N, int num_ops, unsigned* keys,
-                            int* vals, const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= N) return;
-  keys[v] = (unsigned)((depth[v] - 1) * num_ops + node_op[v]);
-  vals[v] = v;
+// Work of a tile: kTileThreads threads, kTileItems items each; a wave owns consecutive items, 64 to a round.
+__device__ __forceinline__ int tile_item(int r) {
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  return (w * kTileItems + r) * kWave + lane;
 }
+__device__ __forceinline__ unsigned long long lanes_below() { return (1ull << (threadIdx.x & (kWave - 1))) - 1; }
 
-// number of 8-bit radix passes the keys (depth - 1) * num_ops + op need, from the depth found on the
-// device: meta[0] = D, written to *passes (at least 1); a depth whose keys would pass kMaxKeys is an error
-__global__ void k_sort_plan(const int* meta, int num_ops, unsigned long long* err, const unsigned long long* cycle,
-                            int* passes) {
-  if (threadIdx.x != 0) return;
-  if (*err == kNoErr && *cycle != kNoErr) *err = *cycle;
-  const long long nk = (long long)meta[0] * num_ops;
-  if (nk > kMaxKeys) {
-    report(err, kTooDeep, FOLD_E_INVALID);
-    *passes = 0;
-    return;
-  }
-  unsigned long long mx = nk > 0 ? (unsigned long long)(nk - 1) : 0ull;
-  int bits = 1;
-  while (bits < 32 && (mx >> bits)) ++bits;
-  *passes = (bits + 7) / 8;
-}
-
-// counts[d * B + b] = number of items of tile b whose digit is d.  Pass `pass` runs only below *passes
-// (passes == nullptr: always) and when no error is set.
-__global__ void k_radix_count(const unsigned* keys, int n, int shift, int* counts, int B, const unsigned long long* err,
-                              const int* passes, int pass) {
-  if (*err != kNoErr || (passes && pass >= *passes)) return;
-  __shared__ int hist[256];
-  const int b = blockIdx.x, t = threadIdx.x;
-  hist[t] = 0;
-  __syncthreads();
-  const long long base = (long long)b * kRadixTile;
-  for (int r = 0; r < kRadixItems; ++r) {
-    long long i = base + (long long)r * kBlock + t;
-    if (i < n) atomicAdd(&hist[(keys[i] >> shift) & 255u], 1);
-  }
-  __syncthreads();
-  counts[t * B + b] = hist[t];
-}
-
-// Scatter in tile order.  Items of a round are ranked among equal digits by a wave-level match
-// (one ballot per digit bit) plus the counts of earlier waves; rounds go in item order, so the
-// scatter is stable.  A pass at or above *passes copies its tile unchanged (the keys are already
-// sorted), so the host can launch the most passes N * num_ops could need and the result still ends in
-// the output buffer of the last pass.
-__global__ __launch_bounds__(kBlock) void k_radix_scatter(const unsigned* keys_in, const int* vals_in,
-                                                          unsigned* keys_out, int* vals_out,
-                                                          const int* offsets, int n, int shift, int B,
-                                                          const unsigned long long* err, const int* passes,
-                                                          int pass) {
-  if (*err != kNoErr) return;
-  __shared__ int base[256];
-  __shared__ int wcnt[kBlock / kWave][256];
-  const int b = blockIdx.x, t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
-  if (passes && pass >= *passes) {
-    for (int r = 0; r < kRadixItems; ++r) {
-      const long long i = (long long)b * kRadixTile + (long long)r * kBlock + t;
-      if (i < n) {
-        keys_out[i] = keys_in[i];
-        vals_out[i] = vals_in[i];
-      }
-    }
-    return;
-  }
-  base[t] = offsets[t * B + b];
-  for (int i = 0; i < kBlock / kWave; ++i) wcnt[i][t] = 0;
-  __syncthreads();
-  const long long start = (long long)b * kRadixTile;
-  const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int r = 0; r < kRadixItems; ++r) {
-    const long long i = start + (long long)r * kBlock + t;
-    const bool valid = i < n;
-    const unsigned k = valid ? keys_in[i] : 0u;
-    const int d = valid ? (int)((k >> shift) & 255u) : 256;  // 256 marks padding
-    unsigned long long m = ~0ull;
-    for (int bit = 0; bit < 9; ++bit) {
-      const int on = (d >> bit) & 1;
+// Stable ranks: rank[r] = earlier items of this wave with the same digit d[r] (-1: no item); `mine` (this wave's
+// counters, zero before) ends as the wave's count of every digit.  One ballot per digit bit finds a round's equal
+// digits; rounds go in item order, so no barrier is needed inside a wave.
+__device__ __forceinline__ void wave_ranks(volatile uint16_t* mine, const int (&d)[kTileItems], int bits,
+                                           int (&rank)[kTileItems]) {
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    unsigned long long m = __ballot(d[r] >= 0);
+    for (int b = 0; b < bits; ++b) {
+      const int on = (d[r] >> b) & 1;
       const unsigned long long bal = __ballot(on);
       m &= on ? bal : ~bal;
     }
-    const int lrank = __popcll(m & lt_mask);
-    if (valid && lrank == 0) wcnt[w][d] = __popcll(m);
-    __syncthreads();
-    if (valid) {
-      int pre = 0;
-      for (int j = 0; j < w; ++j) pre += wcnt[j][d];
-      const int pos = base[d] + pre + lrank;
-      keys_out[pos] = k;
-      vals_out[pos] = vals_in[i];
-    }
-    __syncthreads();
-    int tot = 0;
-    for (int j = 0; j < kBlock / kWave; ++j) { tot += wcnt[j][t]; wcnt[j][t] = 0; }
-    base[t] += tot;
-    __syncthreads();
+    const int below = __popcll(m & lanes_below());
+    const int before = d[r] >= 0 ? mine[d[r]] : 0;
+    __builtin_amdgcn_wave_barrier();
+    if (d[r] >= 0 && below == 0) mine[d[r]] = (uint16_t)(before + __popcll(m));
+    __builtin_amdgcn_wave_barrier();
+    rank[r] = before + below;
   }
+}
+
+// the waves' counts of digit d become the counts of the waves before; returns the tile's count
+__device__ __forceinline__ int scan_waves(uint16_t* counts, int stride, int d) {
+  int run = 0;
+  for (int w = 0; w < kTileThreads / kWave; ++w) {
+    const int c = counts[w * stride + d];
+    counts[w * stride + d] = (uint16_t)run;
+    run += c;
+  }
+  return run;
+}
+
+// Whether a pass of a sort runs: never once the error word is set; with meta (the sort by depth and op) only if the
+// depth found on the device, meta[0], gives keys with bits in the pass's digit.  The host launches as many passes as
+// N * num_ops keys could need; sorted_buffer() says which buffer the last one that ran wrote.
+struct SortGate {
+  const unsigned long long* err;
+  const int* meta;
+  int num_ops, pass;
+  __device__ __forceinline__ bool off() const {
+    if (*err != kNoErr) return true;
+    return meta && pass > 0 && (((long long)meta[0] * num_ops - 1) >> (kDigitBits * pass)) == 0;
+  }
+};
+__device__ __forceinline__ int sorted_buffer(const int* meta, int num_ops) {
+  const long long top = (long long)meta[0] * num_ops - 1;
+  return (top >> kDigitBits) != 0 && (top >> (2 * kDigitBits)) == 0 ? 1 : 0;
+}
+
+// what a pass sorts: the nodes by depth and op, or the (key, value) pairs that an earlier pass left
+struct NodeKeys {
+  typedef unsigned Key;
+  const int *depth, *op;
+  int num_ops;
+  __device__ __forceinline__ unsigned key(int i) const { return (unsigned)((depth[i] - 1) * num_ops + op[i]); }
+  __device__ __forceinline__ int val(int i) const { return i; }
+};
+template <class K>
+struct PairKeys {
+  typedef K Key;
+  const K* k;
+  const int* v;
+  __device__ __forceinline__ K key(int i) const { return k[i]; }
+  __device__ __forceinline__ int val(int i) const { return v[i]; }
+};
+
+// n items (n_ptr: their number on the device, at most n)
+struct SortSize {
+  int n;
+  const int* n_ptr;
+  __device__ __forceinline__ int get() const { return n_ptr ? *n_ptr : n; }
+};
+
+// A cycle counts where no check failed; keys past kMaxKeys are an error.  Every workgroup of the sort's first launch
+// finds that by itself, the later launches see the error word.
+__device__ __forceinline__ bool sort_starts(unsigned long long* err, const unsigned long long* cycle, const int* meta,
+                                            int num_ops) {
+  if (*err != kNoErr) return false;
+  if (*cycle != kNoErr) {
+    if (threadIdx.x == 0) atomicMin(err, *cycle);
+    return false;
+  }
+  if ((long long)meta[0] * num_ops > kMaxKeys) {
+    if (threadIdx.x == 0) report(err, kTooDeep, FOLD_E_INVALID);
+    return false;
+  }
+  return true;
+}
+
+// counts[b * kDigits + d] = items of tile b with digit d
+template <class SRC, bool FIRST>
+__global__ __launch_bounds__(kTileThreads) void k_sort_count(SRC src, SortSize size, int shift, int* counts, SortGate gate,
+                                                             unsigned long long* err, const unsigned long long* cycle) {
+  if (FIRST ? !sort_starts(err, cycle, gate.meta, gate.num_ops) : gate.off()) return;
+  __shared__ int hist[kDigits];
+  const int n = size.get(), b = blockIdx.x, t = threadIdx.x;
+  if ((long long)b * kTile >= n) return;
+  for (int d = t; d < kDigits; d += kTileThreads) hist[d] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int i = b * kTile + r * kTileThreads + t;
+    if (i < n) atomicAdd(&hist[(int)(src.key(i) >> shift) & (kDigits - 1)], 1);
+  }
+  __syncthreads();
+  for (int d = t; d < kDigits; d += kTileThreads) counts[(size_t)b * kDigits + d] = hist[d];
+}
+
+// counts down every digit's column become the counts of the tiles before; the totals go to row B.  A workgroup takes
+// 64 digits: 16 segments of tiles are summed, then rewritten.
+__global__ __launch_bounds__(1024) void k_sort_columns(SortSize size, int* counts, int B, SortGate gate) {
+  if (gate.off()) return;
+  __shared__ int part[16][64];
+  const int d = blockIdx.x * 64 + (threadIdx.x & 63), seg = threadIdx.x >> 6;
+  const int nb = (size.get() + kTile - 1) / kTile, per = (nb + 15) / 16;
+  const int lo = min(nb, seg * per), hi = min(nb, lo + per);
+  int s = 0;
+  for (int b = lo; b < hi; ++b) s += counts[(size_t)b * kDigits + d];
+  part[seg][threadIdx.x & 63] = s;
+  __syncthreads();
+  int run = 0;
+  for (int k = 0; k < seg; ++k) run += part[k][threadIdx.x & 63];
+  for (int b = lo; b < hi; ++b) {
+    const int c = counts[(size_t)b * kDigits + d];
+    counts[(size_t)b * kDigits + d] = run;
+    run += c;
+  }
+  if (seg == 15) counts[(size_t)B * kDigits + d] = run;
+}
+
+// Scatter of one pass.  B > kSelfTiles: the counts have been scanned down the columns.
+template <class SRC>
+__global__ __launch_bounds__(kTileThreads) void k_sort_scatter(SRC src, SortSize size, int shift, const int* counts, int B,
+                                                               typename SRC::Key* keys_out, int* vals_out,
+                                                               SortGate gate) {
+  if (gate.off()) return;
+  const int n = size.get(), b = blockIdx.x, t = threadIdx.x;
+  if ((long long)b * kTile >= n) return;
+  __shared__ uint16_t wcount[kTileThreads / kWave][kDigits];
+  __shared__ int base[kDigits];
+  typename SRC::Key key[kTileItems];
+  int val[kTileItems], d[kTileItems], rank[kTileItems];
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int i = b * kTile + tile_item(r);
+    const bool in = i < n;
+    key[r] = in ? src.key(i) : 0;
+    val[r] = in ? src.val(i) : 0;
+    d[r] = in ? (int)(key[r] >> shift) & (kDigits - 1) : -1;
+  }
+  for (int i = t; i < (int)sizeof(wcount) / 4; i += kTileThreads) reinterpret_cast<uint32_t*>(&wcount[0][0])[i] = 0;
+  static_assert(kDigits == 2 * kTileThreads, "two digits a thread");
+  const int2* col = reinterpret_cast<const int2*>(counts) + t;
+  int2 before = make_int2(0, 0), total = make_int2(0, 0);
+  if (B > kSelfTiles) {
+    before = col[(size_t)b * kTileThreads];
+    total = col[(size_t)B * kTileThreads];
+  } else {
+    const int nb = (n + kTile - 1) / kTile;
+#pragma unroll 8
+    for (int k = 0; k < nb; ++k) {
+      const int2 c = col[(size_t)k * kTileThreads];
+      if (k < b) before.x += c.x, before.y += c.y;
+      total.x += c.x, total.y += c.y;
+    }
+  }
+  int all;
+  const int first = block_exscan<kTileThreads>(total.x + total.y, &all);  // its barriers publish the zeroed counters
+  base[2 * t] = first + before.x;
+  base[2 * t + 1] = first + total.x + before.y;
+  wave_ranks(wcount[t / kWave], d, kDigitBits, rank);
+  __syncthreads();
+  for (int k = t; k < kDigits; k += kTileThreads) (void)scan_waves(&wcount[0][0], kDigits, k);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    if (d[r] < 0) continue;
+    const int at = base[d[r]] + wcount[t / kWave][d[r]] + rank[r];
+    keys_out[at] = key[r];
+    vals_out[at] = val[r];
+  }
+}
+
+// one pass: count, column scan where there are many tiles, scatter; counts holds (B + 1) * kDigits ints
+template <class SRC, bool FIRST = false>
+void sort_pass(SRC src, SortSize size, int shift, int* counts, typename SRC::Key* keys_out, int* vals_out, SortGate gate,
+               unsigned long long* err, const unsigned long long* cycle, hipStream_t st) {
+  const int B = (size.n + kTile - 1) / kTile;
+  hipLaunchKernelGGL((k_sort_count<SRC, FIRST>), dim3(B), dim3(kTileThreads), 0, st, src, size, shift, counts, gate, err,
+                     cycle);
+  if (B > kSelfTiles)
+    hipLaunchKernelGGL(k_sort_columns, dim3(kDigits / 64), dim3(1024), 0, st, size, counts, B, gate);
+  hipLaunchKernelGGL((k_sort_scatter<SRC>), dim3(B), dim3(kTileThreads), 0, st, src, size, shift, counts, B, keys_out,
+                     vals_out, gate);
+}
+inline int sort_passes(unsigned long long max_key) {
+  int passes = 1;
+  while (max_key >> (kDigitBits * passes)) ++passes;
+  return passes;
 }
 
 // ---------------------------------------------------------------- emission
 
-__global__ void k_post_sort(const unsigned* keys, const int* vals, int N, int num_ops, int* pos_node,
-                            int* node_pos, int* flag, int* level_ptr, const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  const int v = vals[p];
-  pos_node[p] = v;
-  node_pos[v] = p;
-  const unsigned k = keys[p];
-  const bool start = (p == 0) || (keys[p - 1] != k);
-  flag[p] = start ? 1 : 0;
-  const int lvl = (int)(k / (unsigned)num_ops) + 1;
-  if (p == 0 || (int)(keys[p - 1] / (unsigned)num_ops) + 1 != lvl) level_ptr[lvl - 1] = p;
-  if (p == N - 1) level_ptr[lvl] = N;
+// Everything after the sort, in two passes over the tiles of sorted nodes: the first writes what needs no prefix and
+// sums per tile (group starts, edges, roots of the same range of node ids, rows of every op); in the second a tile
+// adds up the sums of the tiles before it (a few KB from the L2) and writes every index.  Separate scans, gathers and
+// sorts for these took about twenty launches.
+struct EmitArgs {
+  // the sort's two buffers
+  const unsigned* keys[2];
+  const int* vals[2];
+  const int *cp, *ci, *node_input, *indeg;
+  int N, num_ops, tiles;
+  unsigned* link;                          // [N] by node: pool row, kOneParent where it has one parent edge
+  int *starts, *edges, *roots, *op_count;  // [tiles] each; op_count [tiles][num_ops]
+  int* moved;                              // [2][N] by group: the slot's children are not consecutive single rows
+  int *pos_node, *node_pos, *gid, *level_ptr, *g_level, *g_op, *g_row_begin, *g_idx_off, *g_cbase0, *g_cbase1;
+  int *child_pos, *child_one, *input_idx, *pos_npar, *root_pos, *op_rows, *op_cpos, *op_inp;
+  unsigned long long* tok_key;  // rows that read the leaf table, by (op, row): (input op's number << 32) | leaf-table row
+  int* tok_val;                 // ... and their pool rows
+  int* meta;                    // [4] groups, [5] roots, [6] entries of tok_key
+  const unsigned long long* err;
+};
+
+constexpr unsigned kOneParent = 0x80000000u;
+
+// the op table in LDS: a lane's op indexes it, and from the kernel's arguments that is a load from memory
+__device__ __forceinline__ void copy_ops(unsigned char* to, const OpTable& ops) {
+  for (int o = threadIdx.x; o < ops.n; o += kTileThreads) to[o] = ops.bits[o];
 }
 
-__global__ void k_group_starts(const unsigned* keys, const int* flag, const int* exs, int N, int num_ops,
-                               int* gid, int* g_level, int* g_op, int* g_row_begin, const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  const int g = exs[p] + flag[p] - 1;
-  gid[p] = g;
-  if (flag[p]) {
-    g_row_begin[g] = p;
-    g_level[g] = (int)(keys[p] / (unsigned)num_ops) + 1;
-    g_op[g] = (int)(keys[p] % (unsigned)num_ops);
+__global__ __launch_bounds__(kTileThreads) void k_emit_sums(EmitArgs a, OpTable ops) {
+  if (*a.err != kNoErr) return;
+  __shared__ int rows[kMaxOps];
+  __shared__ unsigned char bits[kMaxOps];
+  copy_ops(bits, ops);
+  const int b = blockIdx.x, t = threadIdx.x, buf = sorted_buffer(a.meta, a.num_ops);
+  const unsigned* keys = a.keys[buf];
+  for (int o = t; o < a.num_ops; o += kTileThreads) rows[o] = 0;
+  __syncthreads();
+  int starts = 0, edges = 0, roots = 0;
+  const int p0 = b * kTile, p1 = min(a.N, p0 + kTile);
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int p = p0 + r * kTileThreads + t;
+    if (p >= p1) continue;
+    const int v = a.vals[buf][p];
+    const unsigned key = keys[p], prev = p > 0 ? keys[p - 1] : ~0u, next = p + 1 < a.N ? keys[p + 1] : ~0u;
+    const int level = (int)(key / (unsigned)a.num_ops), op = (int)(key - (unsigned)level * a.num_ops);
+    const int parents = a.indeg[v];
+    a.pos_node[p] = v;
+    a.node_pos[v] = p;
+    a.link[v] = (unsigned)p | (parents == 1 ? kOneParent : 0u);
+    a.pos_npar[p] = parents;
+    a.moved[p] = 0;
+    a.moved[a.N + p] = 0;
+    if (p == 0 || (int)(prev / (unsigned)a.num_ops) != level) a.level_ptr[level] = p;
+    if (p == a.N - 1) a.level_ptr[level + 1] = a.N;
+    starts += prev != key;  // ~0u is no key
+    edges += bits[op] & 3;
+    roots += a.indeg[p] == 0;
+    // rows of an op: the ends of its runs in the tile minus their starts
+    if (p == p0 || prev != key) atomicAdd(&rows[op], p0 - p);
+    if (p == p1 - 1 || next != key) atomicAdd(&rows[op], p + 1 - p0);
+  }
+  starts = block_sum<kTileThreads>(starts);
+  edges = block_sum<kTileThreads>(edges);
+  roots = block_sum<kTileThreads>(roots);
+  if (t == 0) {
+    a.starts[b] = starts;
+    a.edges[b] = edges;
+    a.roots[b] = roots;
+  }
+  for (int o = t; o < a.num_ops; o += kTileThreads) a.op_count[(size_t)b * a.num_ops + o] = rows[o];
+}
+
+__global__ __launch_bounds__(kTileThreads) void k_emit(EmitArgs a, OpTable ops) {
+  if (*a.err != kNoErr) return;
+  constexpr int kWaves = kTileThreads / kWave;
+  __shared__ uint16_t wcount[kWaves][kMaxOps];
+  __shared__ int op_at[kMaxOps], op_total[kMaxOps], tok_at[kMaxOps], tok_op[kMaxOps];
+  __shared__ int wsum[3][kWaves];
+  __shared__ unsigned char bits[kMaxOps];
+  copy_ops(bits, ops);
+  const int b = blockIdx.x, t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+  const int buf = sorted_buffer(a.meta, a.num_ops);
+  const unsigned* keys = a.keys[buf];
+  const int* vals = a.vals[buf];
+  for (int i = t; i < (int)sizeof(wcount) / 4; i += kTileThreads) reinterpret_cast<uint32_t*>(&wcount[0][0])[i] = 0;
+  for (int o = t; o < kMaxOps; o += kTileThreads) op_at[o] = op_total[o] = 0;
+  __syncthreads();
+  // sums of the tiles before this one; rows of every op before it and in all
+  int starts = 0, edges = 0, roots = 0;
+  for (int k = t; k < b; k += kTileThreads) {
+    starts += a.starts[k];
+    edges += a.edges[k];
+    roots += a.roots[k];
+  }
+  {
+    int span = 1;
+    while (span < a.num_ops) span <<= 1;
+    const int o = t & (span - 1), parts = kTileThreads / span;
+    int before = 0, total = 0;
+    if (o < a.num_ops)
+      for (int k = t / span; k < a.tiles; k += parts) {
+        const int c = a.op_count[(size_t)k * a.num_ops + o];
+        if (k < b) before += c;
+        total += c;
+      }
+    for (int d = kWave / 2; d >= span; d >>= 1) {  // few ops: add up the wave's parts first
+      before += __shfl_xor(before, d);
+      total += __shfl_xor(total, d);
+    }
+    if (lane < span) {
+      if (before) atomicAdd(&op_at[o], before);
+      if (total) atomicAdd(&op_total[o], total);
+    }
+  }
+  starts = block_sum<kTileThreads>(starts);
+  edges = block_sum<kTileThreads>(edges);
+  roots = block_sum<kTileThreads>(roots);
+  {
+    const bool is_op = t < a.num_ops, reads = is_op && (bits[t] & 4);
+    const int before = is_op ? op_at[t] : 0, total = is_op ? op_total[t] : 0;
+    int all, entries, n;
+    const int first = block_exscan<kTileThreads>(total, &all);
+    const int tok_first = block_exscan<kTileThreads>(reads ? total : 0, &entries);
+    const int number = block_exscan<kTileThreads>(reads ? 1 : 0, &n);
+    if (is_op) {
+      op_at[t] = first + before;
+      tok_at[t] = tok_first - first;  // entry of tok_key minus entry of op_rows
+      tok_op[t] = reads ? number : -1;
+    }
+    if (b == 0 && t == 0) a.meta[6] = entries;
+  }
+  __syncthreads();
+  // this tile's items
+  int key_[kTileItems], node[kTileItems], op[kTileItems], rank[kTileItems];
+  int s_at[kTileItems], e_at[kTileItems], r_at[kTileItems];
+  bool start[kTileItems], root[kTileItems];
+  int ws = 0, we = 0, wr = 0;
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int p = b * kTile + tile_item(r);
+    const bool in = p < a.N;
+    const unsigned key = in ? keys[p] : 0u;
+    key_[r] = (int)key;
+    node[r] = in ? vals[p] : -1;
+    op[r] = in ? (int)(key % (unsigned)a.num_ops) : -1;
+    start[r] = in && (p == 0 || keys[p - 1] != key);
+    root[r] = in && a.indeg[p] == 0;
+    const int arity = in ? bits[op[r]] & 3 : 0;
+    const unsigned long long ms = __ballot(start[r]), m1 = __ballot(arity & 1), m2 = __ballot(arity & 2),
+                             mr = __ballot(root[r]), lt = lanes_below();
+    s_at[r] = ws + __popcll(ms & lt);
+    e_at[r] = we + __popcll(m1 & lt) + 2 * __popcll(m2 & lt);
+    r_at[r] = wr + __popcll(mr & lt);
+    ws += __popcll(ms);
+    we += __popcll(m1) + 2 * __popcll(m2);
+    wr += __popcll(mr);
+  }
+  if (lane == 0) wsum[0][w] = ws, wsum[1][w] = we, wsum[2][w] = wr;
+  int op_bits = 0;
+  while ((1 << op_bits) < a.num_ops) ++op_bits;
+  wave_ranks(wcount[w], op, op_bits, rank);
+  __syncthreads();
+  for (int o = t; o < a.num_ops; o += kTileThreads) (void)scan_waves(&wcount[0][0], kMaxOps, o);
+  for (int k = 0; k < kWaves; ++k) {
+    if (k < w) starts += wsum[0][k], edges += wsum[1][k], roots += wsum[2][k];
+  }
+  __syncthreads();
+  if (b == a.tiles - 1 && t == kTileThreads - 1) {  // the last wave: everything before it, and its own
+    a.meta[4] = starts + ws;
+    a.meta[5] = roots + wr;
+  }
+  // every item's loads go out before any of its stores: chains of three (the node's edges, their nodes, those nodes'
+  // rows), four items at once
+  int c0[kTileItems], input[kTileItems], root_at[kTileItems];
+  int c[kTileItems][2], cpos[kTileItems][2], one[kTileItems][2], prev0[2] = {-1, -1};
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int v = max(node[r], 0), p = b * kTile + tile_item(r);
+    c0[r] = a.cp[v];
+    input[r] = a.node_input[v];
+    root_at[r] = root[r] ? a.node_pos[p] : 0;
+  }
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int arity = node[r] >= 0 ? bits[op[r]] & 3 : 0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) c[r][k] = k < arity ? a.ci[c0[r] + k] : -1;
+  }
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const unsigned x = c[r][k] >= 0 ? a.link[c[r][k]] : 0u;  // row and parent flag in one gather
+      cpos[r][k] = c[r][k] >= 0 ? (int)(x & ~kOneParent) : -1;
+      one[r][k] = (x & kOneParent) != 0;
+    }
+  // Static-graph layout of a child slot: its children are consecutive pool rows with one parent edge each (a batch
+  // of identically shaped graphs with one operation per node position, i.e. manual batching, has it on every slot;
+  // the kernels then address them as base + row).  The group's first row proposes its child as the base, a row
+  // whose child does not follow the previous row's withdraws it.  (prev0: the child of the row before the wave's.)
+  if (lane == 0 && node[0] >= 0 && !start[0]) {
+    const int q0 = a.cp[vals[b * kTile + tile_item(0) - 1]];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int x = k < (bits[op[0]] & 3) ? a.ci[q0 + k] : -1;
+      prev0[k] = x >= 0 ? a.node_pos[x] : -1;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int p = b * kTile + tile_item(r);
+    const bool in = node[r] >= 0;
+    const int arity = in ? bits[op[r]] & 3 : 0;
+    const int g = starts + s_at[r] + (start[r] ? 1 : 0) - 1, off = edges + e_at[r];
+    int prev[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int up = __shfl_up(cpos[r][k], 1), last = __shfl(cpos[r > 0 ? r - 1 : 0][k], kWave - 1);
+      prev[k] = lane > 0 ? up : (r > 0 ? last : prev0[k]);
+    }
+    if (!in) continue;
+    a.gid[p] = g;
+    if (start[r]) {
+      a.g_level[g] = (int)((unsigned)key_[r] / (unsigned)a.num_ops) + 1;
+      a.g_op[g] = op[r];
+      a.g_row_begin[g] = p;
+      a.g_idx_off[g] = off;
+      a.g_cbase0[g] = one[r][0] ? cpos[r][0] : -1;
+      a.g_cbase1[g] = one[r][1] ? cpos[r][1] : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      if (k < arity) {
+        a.child_pos[off + k] = cpos[r][k];
+        a.child_one[off + k] = one[r][k];
+        if (!start[r] && (!one[r][k] || cpos[r][k] != prev[k] + 1)) a.moved[(size_t)k * a.N + g] = 1;
+      }
+    const int q = op_at[op[r]] + wcount[w][op[r]] + rank[r];
+    a.input_idx[p] = input[r];
+    a.op_rows[q] = p;
+    a.op_cpos[2 * (size_t)q] = cpos[r][0];
+    a.op_cpos[2 * (size_t)q + 1] = cpos[r][1];
+    a.op_inp[q] = input[r];
+    if (tok_op[op[r]] >= 0) {
+      a.tok_key[q + tok_at[op[r]]] = (unsigned long long)tok_op[op[r]] << 32 | (unsigned)input[r];
+      a.tok_val[q + tok_at[op[r]]] = p;
+    }
+    if (root[r]) a.root_pos[roots + r_at[r]] = root_at[r];
   }
 }
 
-// ng = number of groups (device); rows and rows * arity of each group (g_edges has N entries)
-__global__ void k_group_rows(const int* ng_ptr, int N, const int* g_row_begin, const int* g_op, OpTable ops,
-                             int* g_rows, int* g_edges, const unsigned long long* err) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (*err != kNoErr || g >= N) return;
-  const int ng = *ng_ptr;
-  if (g >= ng) {
-    g_edges[g] = 0;
-    return;
+// The leaf-table gradient adds dz . W_in^T of every row into its leaf-table row; it is linear in dz, so the
+// backward first sums dz over the rows of each (op, leaf-table row) and contracts once per distinct row.  The rows
+// that read the leaf table are sorted by (op, leaf-table row), and the runs of equal keys are listed: starts per tile,
+// then every entry's run.
+__global__ __launch_bounds__(kTileThreads) void k_tok_sums(const unsigned long long* key, const int* n_ptr, int* starts,
+                                                           const unsigned long long* err) {
+  if (*err != kNoErr) return;
+  const int n = *n_ptr, b = blockIdx.x;
+  int s = 0;
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int i = b * kTile + r * kTileThreads + threadIdx.x;
+    if (i < n) s += i == 0 || key[i - 1] != key[i];
   }
-  const int end = (g + 1 < ng) ? g_row_begin[g + 1] : N;
-  const int rows = end - g_row_begin[g];
-  g_rows[g] = rows;
-  g_edges[g] = rows * ops.arity(g_op[g]);
+  s = block_sum<kTileThreads>(s);
+  if (threadIdx.x == 0) starts[b] = s;
 }
 
-__global__ void k_emit(const int* pos_node, const int* node_pos, const int* gid, const int* g_row_begin,
-                       const int* g_op, const int* g_idx_off, const int* cp, const int* ci,
-                       const int* node_input, const int* indeg, int N, OpTable ops, int* child_pos,
-                       int* child_one, int* input_idx, int* pos_npar, const unsigned long long* err) {
+__global__ __launch_bounds__(kTileThreads) void k_tok_emit(const unsigned long long* key, const int* n_ptr,
+                                                           const int* starts, int* tok_start, int* tok_row, int* tok_seg,
+                                                           int* number_runs, const unsigned long long* err) {
   if (*err != kNoErr) return;
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  const int v = pos_node[p];
-  const int g = gid[p];
-  const int a = ops.arity(g_op[g]);
-  const int off = g_idx_off[g] + (p - g_row_begin[g]) * a;
-  const int c0 = cp[v];
-  for (int k = 0; k < a; ++k) {
-    const int c = ci[c0 + k];
-    child_pos[off + k] = c >= 0 ? node_pos[c] : -1;
-    child_one[off + k] = c >= 0 && indeg[c] == 1 ? 1 : 0;
+  const int n = *n_ptr, b = blockIdx.x, t = threadIdx.x;
+  if ((long long)b * kTile >= n) return;
+  __shared__ int wsum[kTileThreads / kWave], runs[kMaxOps];
+  for (int o = t; o < kMaxOps; o += kTileThreads) runs[o] = 0;
+  int before = 0;
+  for (int k = t; k < b; k += kTileThreads) before += starts[k];
+  before = block_sum<kTileThreads>(before);
+  unsigned long long k_[kTileItems];
+  int at[kTileItems], sum = 0;
+  bool start[kTileItems];
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int i = b * kTile + tile_item(r);
+    k_[r] = i < n ? key[i] : ~0ull;
+    start[r] = i < n && (i == 0 || key[i - 1] != k_[r]);
+    const unsigned long long m = __ballot(start[r]);
+    at[r] = sum + __popcll(m & lanes_below());
+    sum += __popcll(m);
   }
-  input_idx[p] = node_input[v];
-  pos_npar[p] = indeg[v];
-}
-
-__global__ void k_root_flags(const int* indeg, int N, int* flag, const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < N) flag[v] = indeg[v] == 0 ? 1 : 0;
-}
-
-__global__ void k_root_emit(const int* flag, const int* rank, const int* node_pos, int N, int* root_pos,
-                            const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < N && flag[v]) root_pos[rank[v]] = node_pos[v];
-}
-
-__global__ void k_zero_ints(int* p, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
+  if ((t & (kWave - 1)) == 0) wsum[t / kWave] = sum;
+  __syncthreads();
+  for (int k = 0; k < t / kWave; ++k) before += wsum[k];
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int i = b * kTile + tile_item(r);
+    const int op = (int)(k_[r] >> 32);
+    if (i < n) {
+      const int u = before + at[r] + (start[r] ? 1 : 0) - 1;
+      tok_seg[i] = u;
+      if (start[r]) {
+        tok_start[u] = i;
+        tok_row[u] = (int)(unsigned)k_[r];
+      }
+      if (i == n - 1) tok_start[u + 1] = n;
+    }
+    // runs per input op: one add per op and round (the list is sorted by op), summed in LDS, then one add per op and
+    // workgroup to the shared counter (an add per round from every wave: 54 us at 0.8 M entries, now 7)
+    unsigned long long m = __ballot(start[r]);
+    while (m) {
+      const int leader = __ffsll((long long)m) - 1;
+      const int lop = __shfl(op, leader);
+      const unsigned long long same = __ballot(start[r] && op == lop);
+      if ((t & (kWave - 1)) == leader) atomicAdd(&runs[lop], __popcll(same));
+      m &= ~same;
+    }
+  }
+  __syncthreads();
+  for (int o = t; o < kMaxOps; o += kTileThreads)
+    if (runs[o]) atomicAdd(&number_runs[o], runs[o]);
 }
 
 __global__ void k_fill_ints(int* p, long long n, int v) {
@@ -664,134 +991,12 @@ __global__ void k_fill_ints(int* p, long long n, int v) {
     p[i] = v;
 }
 
-// error words "none", meta zero
-__global__ void k_init_meta(void* em) {
+// error words "none", the meta words and `more` zero
+__global__ void k_init_meta(void* em, int words, int* more, int n_more) {
   if (threadIdx.x < 2) static_cast<unsigned long long*>(em)[threadIdx.x] = kNoErr;
   int* meta = reinterpret_cast<int*>(static_cast<unsigned long long*>(em) + 2);
-  if (threadIdx.x < 8) meta[threadIdx.x] = 0;
-}
-
-// keys of the second sort: the op of every pool row, with the row as its value; a stable sort by op
-// lists every op's rows in (op, row) order
-__global__ void k_op_keys(const int* gid, const int* g_op, int N, unsigned* keys, int* vals,
-                          const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  keys[p] = (unsigned)g_op[gid[p]];
-  vals[p] = p;
-}
-
-// The leaf-table gradient adds dz . W_in^T of every row into its leaf-table row; it is linear in dz, so the
-// backward first sums dz over the rows of each (op, leaf-table row) and contracts once per distinct row.  Third
-// sort: pool rows by (op, leaf-table row) -- stable passes over the leaf-table row (rows without one: 0), then
-// one by op -- and the runs of equal keys in the result.
-__global__ void k_tok_keys(const int* input_idx, int N, unsigned* keys, int* vals, const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  keys[p] = (unsigned)max(input_idx[p], 0);
-  vals[p] = p;
-}
-__global__ void k_tok_opkeys(const int* vals, const int* gid, const int* g_op, int N, unsigned* keys,
-                             const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
-  keys[i] = (unsigned)g_op[gid[vals[i]]];
-}
-__global__ void k_tok_flags(const int* tok_rows, const int* gid, const int* g_op, const int* input_idx, int N,
-                            int* flag, const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N) return;
-  const int p = tok_rows[i];
-  int f = 1;
-  if (i > 0) {
-    const int q = tok_rows[i - 1];
-    f = g_op[gid[p]] != g_op[gid[q]] || input_idx[p] != input_idx[q];
-  }
-  flag[i] = f;
-}
-__global__ void k_tok_emit(const int* flag, const int* exs, const int* tok_rows, const int* gid, const int* g_op,
-                           const int* input_idx, int N, int* tok_start, int* tok_row, int* tok_seg, int* op_runs,
-                           const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  bool f = false;
-  int op = -1;
-  if (i < N) {
-    const int p = tok_rows[i];
-    f = flag[i] != 0;
-    const int u = exs[i] + (f ? 1 : 0) - 1;
-    tok_seg[i] = u;
-    if (f) {
-      tok_start[u] = i;
-      tok_row[u] = input_idx[p];
-      op = g_op[gid[p]];
-    }
-    if (i == N - 1) tok_start[u + 1] = N;
-  }
-  // runs per operation, one atomic add per operation and wave: the list is sorted by operation, so a wave's
-  // run starts belong to one or a few of them (one add per run start would serialise on the same counter
-  // when every row is a run of its own)
-  unsigned long long m = __ballot(f);
-  while (m) {
-    const int leader = __ffsll((long long)m) - 1;
-    const int lop = __shfl(op, leader);
-    const unsigned long long same = __ballot(f && op == lop);
-    if ((int)(threadIdx.x & 63) == leader) atomicAdd(&op_runs[lop], __popcll(same));
-    m &= ~same;
-  }
-}
-
-// for entry q of the (op, row) list: the row's children and leaf-table row
-__global__ void k_op_rows(const int* op_rows, const int* gid, const int* g_row_begin, const int* g_op,
-                          const int* g_idx_off, const int* child_pos, const int* input_idx, OpTable ops, int N,
-                          int* op_cpos, int* op_inp, const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= N) return;
-  const int p = op_rows[q];
-  const int g = gid[p];
-  const int r = p - g_row_begin[g];
-  const int a = ops.arity(g_op[g]);
-  op_cpos[2 * q] = a > 0 ? child_pos[g_idx_off[g] + r * a] : -1;
-  op_cpos[2 * q + 1] = a > 1 ? child_pos[g_idx_off[g] + r * a + 1] : -1;
-  op_inp[q] = input_idx[p];
-}
-
-// Static-graph layout of a group's child slot k: its children are the consecutive pool rows base .. base +
-// rows - 1 and each has exactly one parent edge.  A batch of identically shaped graphs with one operation per
-// node position (manual batching) has it on every slot; the kernels then address those children by
-// base + row instead of loading child_pos.  First every group proposes its first child as the base ...
-__global__ void k_cbase_init(const int* ng_ptr, int N, const int* g_op, const int* g_idx_off, const int* child_pos,
-                             const int* child_one, OpTable ops, int* cb0, int* cb1, const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= N || g >= *ng_ptr) return;
-  const int a = ops.arity(g_op[g]), off = g_idx_off[g];
-  int b[2] = {-1, -1};
-  for (int k = 0; k < a && k < 2; ++k) b[k] = child_one[off + k] ? child_pos[off + k] : -1;
-  cb0[g] = b[0];
-  cb1[g] = b[1];
-}
-
-// ... then every row withdraws it (-1) where its child is not base + r or has another parent edge
-__global__ void k_cbase_check(int N, const int* gid, const int* g_row_begin, const int* g_op, const int* g_idx_off,
-                              const int* child_pos, const int* child_one, OpTable ops, int* cb0, int* cb1,
-                              const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  const int g = gid[p], r = p - g_row_begin[g], a = ops.arity(g_op[g]);
-  for (int k = 0; k < a && k < 2; ++k) {
-    int* cb = k == 0 ? cb0 : cb1;
-    const int base = cb[g];
-    if (base < 0) continue;
-    const int e = g_idx_off[g] + r * a + k;
-    if (child_pos[e] != base + r || !child_one[e]) cb[g] = -1;
-  }
+  for (int i = threadIdx.x; i < words; i += blockDim.x) meta[i] = 0;
+  for (int i = threadIdx.x; i < n_more; i += blockDim.x) more[i] = 0;
 }
 
 // The one read-back of a schedule: the error word and meta, then the first lcap + 1 entries of level_ptr
@@ -801,21 +1006,33 @@ constexpr int kGroupArrays = 7;
 struct GroupArrays {
   const int* a[kGroupArrays];  // level, op, row_begin, rows, idx_off, child base of slot 0, of slot 1
 };
-__global__ void k_compact(const unsigned long long* err, const int* meta, const int* level_ptr, GroupArrays garr,
-                          int lcap, int gcap, const int* op_runs, int num_ops, int* out) {
+// (several workgroups: the group rows and child bases are finished here)
+__global__ void k_finish(const unsigned long long* err, const int* meta, const int* level_ptr, GroupArrays garr, int N,
+                         const int* moved, int* g_rows, int* cb0, int* cb1, int lcap, int gcap, const int* op_runs,
+                         int num_ops, int* out) {
   const unsigned long long e = *err;
-  if (threadIdx.x == 0) {
+  const int i0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  if (i0 == 0) {
     out[0] = (int)(unsigned)(e & 0xffffffffull);
     out[1] = (int)(unsigned)(e >> 32);
     for (int i = 0; i < 8; ++i) out[2 + i] = meta[i];
   }
   if (e != kNoErr) return;
-  const int nl = min(meta[0] + 1, lcap + 1), ng = min(meta[4], gcap);
-  for (int i = threadIdx.x; i < nl; i += blockDim.x) out[kHdr + i] = level_ptr[i];
+  const int ng = N > 0 ? meta[4] : 0, nl = N > 0 ? min(meta[0] + 1, lcap + 1) : 0;
+  for (int i = i0; i < nl; i += step) out[kHdr + i] = level_ptr[i];
   int* go = out + kHdr + lcap + 1;
-  for (int k = 0; k < kGroupArrays; ++k)
-    for (int i = threadIdx.x; i < ng; i += blockDim.x) go[k * gcap + i] = garr.a[k][i];
-  for (int o = threadIdx.x; o < num_ops; o += blockDim.x) go[kGroupArrays * gcap + o] = op_runs[o];
+  for (int g = i0; g < ng; g += step) {
+    const int begin = garr.a[2][g], rows = (g + 1 < ng ? garr.a[2][g + 1] : N) - begin;
+    const int c0 = moved[g] ? -1 : cb0[g], c1 = moved[N + g] ? -1 : cb1[g];
+    g_rows[g] = rows;
+    cb0[g] = c0;
+    cb1[g] = c1;
+    if (g >= gcap) continue;
+    const int row[kGroupArrays] = {garr.a[0][g], garr.a[1][g], begin, rows, garr.a[4][g], c0, c1};
+#pragma unroll
+    for (int k = 0; k < kGroupArrays; ++k) go[k * gcap + g] = row[k];
+  }
+  for (int o = i0; o < num_ops; o += step) go[kGroupArrays * gcap + o] = op_runs[o];
 }
 
 inline dim3 grid_for(long long n) { return dim3((unsigned)std::max(1LL, (n + kBlock - 1) / kBlock)); }
@@ -951,38 +1168,45 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
 
   // temporaries of the whole schedule, one pooled allocation
   Temp tmp(st);
-  // err, then meta: [0] max depth, [1] max parents, [2] radix passes, [3] scratch total, [4] groups, [5] roots,
-  // [6] scratch total
+  // err, then meta: [0] max depth, [1] max parents, [4] groups, [5] roots, [6] rows that read the leaf table
   struct ErrMeta {
     unsigned long long err, cycle;  // a cycle counts only where no node check failed
     int meta[8];
   };
   ErrMeta* em = nullptr;
-  int *indeg = nullptr, *scratch = nullptr, *edges = nullptr, *stage = nullptr;
-  unsigned *ka = nullptr, *kb = nullptr;
-  int *va = nullptr, *vb = nullptr, *flag = nullptr, *exs = nullptr, *radix_counts = nullptr, *scan_tmp = nullptr;
+  int *indeg = nullptr, *scratch = nullptr, *moved = nullptr, *stage = nullptr;
+  unsigned* link = nullptr;
+  unsigned* keys[2] = {nullptr, nullptr};
+  unsigned long long* tok_keys[2] = {nullptr, nullptr};
+  int *vals[2] = {nullptr, nullptr}, *tok_vals[2] = {nullptr, nullptr};
+  int *sort_counts = nullptr, *tile_sums = nullptr, *op_count = nullptr;
   const long long scratch_ints = GlobLinks<true>::kNodeInts * (long long)N + GlobLinks<true>::kEdgeInts * (long long)E;
-  const int B = (N + kRadixTile - 1) / kRadixTile;
-  const long long rc = 256LL * std::max(B, 1);
-  const long long scan_tmp_n = std::max<long long>(rc, N) / kScanTile + 2;
+  const int B = (N + kTile - 1) / kTile;
+  int input_ops = 0;
+  for (int i = 0; i < K; ++i) input_ops += b->ops[i].has_input ? 1 : 0;
+  const bool any_input = input_ops > 0;
   constexpr int kLcap = 4096, kGcap = 4096;  // levels and groups read back with the error word
   const size_t stage_n = kHdr + (kLcap + 1) + kGroupArrays * (size_t)kGcap + kMaxOps;
-  int* op_runs = nullptr;  // [kMaxOps] runs of equal (op, leaf-table row) per op
+  int* op_runs = nullptr;  // [kMaxOps] runs of equal (op, leaf-table row) of the ops that read the leaf table
   tmp.reserve(&em, 1);
   tmp.reserve(&stage, stage_n);
   tmp.reserve(&op_runs, kMaxOps);
   if (N > 0) {
     tmp.reserve(&indeg, N);
     tmp.reserve(&scratch, (size_t)scratch_ints);
-    tmp.reserve(&edges, N);
-    tmp.reserve(&ka, N);
-    tmp.reserve(&kb, N);
-    tmp.reserve(&va, N);
-    tmp.reserve(&vb, N);
-    tmp.reserve(&flag, N);
-    tmp.reserve(&exs, N);
-    tmp.reserve(&radix_counts, rc);
-    tmp.reserve(&scan_tmp, scan_tmp_n);
+    tmp.reserve(&moved, 2 * (size_t)N);
+    tmp.reserve(&link, N);
+    for (int i = 0; i < 2; ++i) {
+      tmp.reserve(&keys[i], N);
+      tmp.reserve(&vals[i], N);
+      if (any_input) {
+        tmp.reserve(&tok_keys[i], N);
+        tmp.reserve(&tok_vals[i], N);
+      }
+    }
+    tmp.reserve(&sort_counts, (size_t)(B + 1) * kDigits);
+    tmp.reserve(&tile_sums, 4 * (size_t)B);
+    tmp.reserve(&op_count, (size_t)B * K);
   }
   if (tmp.commit() != hipSuccess) {
     set_error("fold_schedule: out of device memory (temporaries)");
@@ -990,8 +1214,7 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   }
   unsigned long long* err = &em->err;
   int* meta = em->meta;
-  hipLaunchKernelGGL(k_init_meta, dim3(1), dim3(64), 0, st, em);
-  hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(kBlock), 0, st, op_runs, kMaxOps);
+  hipLaunchKernelGGL(k_init_meta, dim3(1), dim3(kBlock), 0, st, em, 8, op_runs, kMaxOps);
   hipLaunchKernelGGL(k_check_struct, grid_for(std::max(G + 1, N + 1)), dim3(kBlock), 0, st, b->graph_ptr, G,
                      b->child_ptr, N, E, err);
   if (N > 0) {
@@ -1002,88 +1225,66 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
       hipLaunchKernelGGL(k_graph_depth<true>, dim3(G), dim3(kGraphThreads), lds, st, ga, ops, lds);
     }
 
-    // sort by (depth - 1) * num_ops + op: as many 8-bit passes as N * num_ops could need are launched; the
-    // ones the actual depth does not need copy their tile
-    hipLaunchKernelGGL(k_sort_plan, dim3(1), dim3(64), 0, st, meta, K, err, &em->cycle, meta + 2);
-    hipLaunchKernelGGL(k_make_keys, grid_for(N), dim3(kBlock), 0, st, s.depth, b->node_op, N, K, ka, va, err);
+    // sort by (depth - 1) * num_ops + op: as many passes as N * num_ops keys could need are launched; those the actual
+    // depth does not need return at once
     const unsigned long long max_key = std::min<unsigned long long>((unsigned long long)N * K,
                                                                     (unsigned long long)kMaxKeys) - 1;
-    int bits = 1;
-    while (bits < 32 && (max_key >> bits)) ++bits;
-    const int passes = (bits + 7) / 8;
+    const int passes = sort_passes(max_key);
+    const SortSize all{N, nullptr};
     for (int ps = 0; ps < passes; ++ps) {
-      const int shift = 8 * ps;
-      hipLaunchKernelGGL(k_radix_count, dim3(B), dim3(kBlock), 0, st, ka, N, shift, radix_counts, B, err,
-                         meta + 2, ps);
-      scan_exclusive(radix_counts, radix_counts, (int)rc, meta + 3, scan_tmp, st);
-      hipLaunchKernelGGL(k_radix_scatter, dim3(B), dim3(kBlock), 0, st, ka, va, kb, vb, radix_counts, N, shift, B,
-                         err, meta + 2, ps);
-      std::swap(ka, kb);
-      std::swap(va, vb);
+      const SortGate gate{err, meta, K, ps};
+      if (ps == 0)
+        sort_pass<NodeKeys, true>({s.depth, b->node_op, K}, all, 0, sort_counts, keys[0], vals[0], gate, err, &em->cycle,
+                                  st);
+      else
+        sort_pass<PairKeys<unsigned>>({keys[(ps - 1) & 1], vals[(ps - 1) & 1]}, all, kDigitBits * ps, sort_counts,
+                                      keys[ps & 1], vals[ps & 1], gate, err, &em->cycle, st);
     }
-    int* gid = s.pos_group;
-    hipLaunchKernelGGL(k_post_sort, grid_for(N), dim3(kBlock), 0, st, ka, va, N, K, s.pos_node, s.node_pos,
-                       flag, s.level_ptr, err);
-    scan_exclusive(flag, exs, N, meta + 4, scan_tmp, st);
-    hipLaunchKernelGGL(k_group_starts, grid_for(N), dim3(kBlock), 0, st, ka, flag, exs, N, K, gid, s.g_level,
-                       s.g_op, s.g_row_begin, err);
-    hipLaunchKernelGGL(k_group_rows, grid_for(N), dim3(kBlock), 0, st, meta + 4, N, s.g_row_begin, s.g_op, ops,
-                       s.g_rows, edges, err);
-    // idx_off = exclusive scan of rows * arity over the groups (entries past the group count are unused)
-    scan_exclusive(edges, s.g_idx_off, N, meta + 6, scan_tmp, st);
-    hipLaunchKernelGGL(k_emit, grid_for(N), dim3(kBlock), 0, st, s.pos_node, s.node_pos, gid, s.g_row_begin,
-                       s.g_op, s.g_idx_off, b->child_ptr, b->child_idx, b->node_input, indeg, N, ops, s.child_pos,
-                       s.child_one, s.input_idx, s.pos_npar, err);
-    hipLaunchKernelGGL(k_root_flags, grid_for(N), dim3(kBlock), 0, st, indeg, N, flag, err);
-    scan_exclusive(flag, exs, N, meta + 5, scan_tmp, st);
-    hipLaunchKernelGGL(k_root_emit, grid_for(N), dim3(kBlock), 0, st, flag, exs, s.node_pos, N, s.root_pos, err);
+    EmitArgs ea{};
+    for (int i = 0; i < 2; ++i) {
+      ea.keys[i] = keys[i];
+      ea.vals[i] = vals[i];
+    }
+    ea.cp = b->child_ptr; ea.ci = b->child_idx; ea.node_input = b->node_input; ea.indeg = indeg;
+    ea.N = N; ea.num_ops = K; ea.tiles = B;
+    ea.starts = tile_sums; ea.edges = tile_sums + B; ea.roots = tile_sums + 2 * (size_t)B;
+    ea.op_count = op_count; ea.moved = moved; ea.link = link;
+    ea.pos_node = s.pos_node; ea.node_pos = s.node_pos; ea.gid = s.pos_group; ea.level_ptr = s.level_ptr;
+    ea.g_level = s.g_level; ea.g_op = s.g_op; ea.g_row_begin = s.g_row_begin; ea.g_idx_off = s.g_idx_off;
+    ea.g_cbase0 = s.g_cbase0; ea.g_cbase1 = s.g_cbase1;
+    ea.child_pos = s.child_pos; ea.child_one = s.child_one; ea.input_idx = s.input_idx; ea.pos_npar = s.pos_npar;
+    ea.root_pos = s.root_pos; ea.op_rows = s.op_rows; ea.op_cpos = s.op_cpos; ea.op_inp = s.op_inp;
+    ea.tok_key = tok_keys[0]; ea.tok_val = tok_vals[0];
+    ea.meta = meta; ea.err = err;
+    hipLaunchKernelGGL(k_emit_sums, dim3(B), dim3(kTileThreads), 0, st, ea, ops);
+    hipLaunchKernelGGL(k_emit, dim3(B), dim3(kTileThreads), 0, st, ea, ops);
 
-    // rows of every op in (op, row) order: one stable pass keyed by op (at most 256 ops: one digit)
-    hipLaunchKernelGGL(k_op_keys, grid_for(N), dim3(kBlock), 0, st, gid, s.g_op, N, kb, vb, err);
-    hipLaunchKernelGGL(k_radix_count, dim3(B), dim3(kBlock), 0, st, kb, N, 0, radix_counts, B, err,
-                       (const int*)nullptr, 0);
-    scan_exclusive(radix_counts, radix_counts, (int)rc, meta + 3, scan_tmp, st);
-    hipLaunchKernelGGL(k_radix_scatter, dim3(B), dim3(kBlock), 0, st, kb, vb, ka, s.op_rows, radix_counts, N, 0, B,
-                       err, (const int*)nullptr, 0);
-    hipLaunchKernelGGL(k_op_rows, grid_for(N), dim3(kBlock), 0, st, s.op_rows, gid, s.g_row_begin, s.g_op,
-                       s.g_idx_off, s.child_pos, s.input_idx, ops, N, s.op_cpos, s.op_inp, err);
-    hipLaunchKernelGGL(k_cbase_init, grid_for(N), dim3(kBlock), 0, st, meta + 4, N, s.g_op, s.g_idx_off,
-                       s.child_pos, s.child_one, ops, s.g_cbase0, s.g_cbase1, err);
-    hipLaunchKernelGGL(k_cbase_check, grid_for(N), dim3(kBlock), 0, st, N, gid, s.g_row_begin, s.g_op,
-                       s.g_idx_off, s.child_pos, s.child_one, ops, s.g_cbase0, s.g_cbase1, err);
-
-    // rows in (op, leaf-table row) order and their runs (only if some op reads the leaf table)
-    bool any_input = false;
-    for (int i = 0; i < K; ++i) any_input = any_input || b->ops[i].has_input;
+    // the rows that read the leaf table in (op, leaf-table row) order, and their runs: they come in (op, row) order,
+    // so passes over the leaf-table row's bits and, where several ops read it, one over the op sort them
     if (any_input) {
-      int ibits = 1;
-      while (ibits < 31 && ((long long)std::max(b->num_inputs - 1, 0) >> ibits)) ++ibits;
-      hipLaunchKernelGGL(k_tok_keys, grid_for(N), dim3(kBlock), 0, st, s.input_idx, N, ka, va, err);
-      for (int ps = 0; ps < (ibits + 7) / 8; ++ps) {
-        hipLaunchKernelGGL(k_radix_count, dim3(B), dim3(kBlock), 0, st, ka, N, 8 * ps, radix_counts, B, err,
-                           (const int*)nullptr, 0);
-        scan_exclusive(radix_counts, radix_counts, (int)rc, meta + 3, scan_tmp, st);
-        hipLaunchKernelGGL(k_radix_scatter, dim3(B), dim3(kBlock), 0, st, ka, va, kb, vb, radix_counts, N, 8 * ps,
-                           B, err, (const int*)nullptr, 0);
-        std::swap(ka, kb);
-        std::swap(va, vb);
+      const int row_passes = sort_passes((unsigned long long)std::max(b->num_inputs - 1, 0));
+      const int tok_passes = row_passes + (input_ops > 1 ? 1 : 0);
+      const SortSize entries{N, meta + 6};
+      for (int ps = 0; ps < tok_passes; ++ps) {
+        const SortGate gate{err, nullptr, 0, 0};
+        sort_pass<PairKeys<unsigned long long>>({tok_keys[ps & 1], tok_vals[ps & 1]}, entries,
+                                                ps < row_passes ? kDigitBits * ps : 32, sort_counts,
+                                                tok_keys[(ps + 1) & 1],
+                                                ps + 1 < tok_passes ? tok_vals[(ps + 1) & 1] : s.tok_rows, gate, err,
+                                                &em->cycle, st);
       }
-      hipLaunchKernelGGL(k_tok_opkeys, grid_for(N), dim3(kBlock), 0, st, va, gid, s.g_op, N, ka, err);
-      hipLaunchKernelGGL(k_radix_count, dim3(B), dim3(kBlock), 0, st, ka, N, 0, radix_counts, B, err,
-                         (const int*)nullptr, 0);
-      scan_exclusive(radix_counts, radix_counts, (int)rc, meta + 3, scan_tmp, st);
-      hipLaunchKernelGGL(k_radix_scatter, dim3(B), dim3(kBlock), 0, st, ka, va, kb, s.tok_rows, radix_counts, N, 0,
-                         B, err, (const int*)nullptr, 0);
-      hipLaunchKernelGGL(k_tok_flags, grid_for(N), dim3(kBlock), 0, st, s.tok_rows, gid, s.g_op, s.input_idx, N,
-                         flag, err);
-      scan_exclusive(flag, exs, N, meta + 7, scan_tmp, st);
-      hipLaunchKernelGGL(k_tok_emit, grid_for(N), dim3(kBlock), 0, st, flag, exs, s.tok_rows, gid, s.g_op,
-                         s.input_idx, N, s.tok_start, s.tok_row, s.tok_seg, op_runs, err);
+      const unsigned long long* sorted = tok_keys[tok_passes & 1];
+      int* tok_starts = tile_sums + 3 * (size_t)B;
+      hipLaunchKernelGGL(k_tok_sums, dim3(B), dim3(kTileThreads), 0, st, sorted, meta + 6, tok_starts, err);
+      hipLaunchKernelGGL(k_tok_emit, dim3(B), dim3(kTileThreads), 0, st, sorted, meta + 6, tok_starts, s.tok_start,
+                         s.tok_row, s.tok_seg, op_runs, err);
     }
   }
   GroupArrays ga{{s.g_level, s.g_op, s.g_row_begin, s.g_rows, s.g_idx_off, s.g_cbase0, s.g_cbase1}};
-  hipLaunchKernelGGL(k_compact, dim3(1), dim3(kBlock), 0, st, err, meta, s.level_ptr, ga, kLcap, kGcap, op_runs, K,
-                     stage);
+  // a workgroup per 1,024 possible groups, at most 16 (a batch has few groups; a thousand-level chain of them still
+  // takes a few steps)
+  hipLaunchKernelGGL(k_finish, dim3(std::min(16, N / 1024 + 1)), dim3(kBlock), 0, st, err, meta, s.level_ptr, ga, N, moved,
+                     s.g_rows, s.g_cbase0, s.g_cbase1, kLcap, kGcap, op_runs, K, stage);
   if (hipGetLastError() != hipSuccess) {
     set_error("fold_schedule: kernel launch failed");
     return fail(FOLD_E_DEVICE);
@@ -1139,13 +1340,18 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
       return fail(FOLD_E_DEVICE);
     }
   }
-  // ranges of op_rows per op, and of the runs of equal (op, leaf-table row) per op
+  // ranges of op_rows per op, and of tok_rows and their runs per op that reads the leaf table
   s.h_op_row_ptr.assign(K + 1, 0);
   for (int g = 0; g < ng; ++g) s.h_op_row_ptr[s.h_op[g] + 1] += s.h_rows[g];
-  for (int o = 0; o < K; ++o) s.h_op_row_ptr[o + 1] += s.h_op_row_ptr[o];
+  s.h_tok_row_ptr.assign(K + 1, 0);
   s.h_tok_ptr.assign(K + 1, 0);
-  const int* hr = hb.data() + kHdr + (kLcap + 1) + kGroupArrays * kGcap;
-  for (int o = 0; o < K; ++o) s.h_tok_ptr[o + 1] = s.h_tok_ptr[o] + (N > 0 ? hr[o] : 0);
+  const int* runs = hb.data() + kHdr + (kLcap + 1) + kGroupArrays * kGcap;
+  for (int o = 0; o < K; ++o) {
+    const bool reads = N > 0 && b->ops[o].has_input;
+    s.h_tok_row_ptr[o + 1] = s.h_tok_row_ptr[o] + (reads ? s.h_op_row_ptr[o + 1] : 0);
+    s.h_tok_ptr[o + 1] = s.h_tok_ptr[o] + (reads ? *runs++ : 0);
+  }
+  for (int o = 0; o < K; ++o) s.h_op_row_ptr[o + 1] += s.h_op_row_ptr[o];
   *out = h;
   return FOLD_OK;
 }
@@ -1513,8 +1719,7 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   }
   unsigned long long* err = &em->err;
   int* meta = em->meta;
-  hipLaunchKernelGGL(k_init_meta, dim3(1), dim3(64), 0, st, em);
-  hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, st, meta + 8, kMaxTypes);
+  hipLaunchKernelGGL(k_init_meta, dim3(1), dim3(64), 0, st, em, 8 + kMaxTypes, nullptr, 0);
   // pass counts of values past the last one stay 0, so the scan over the largest possible value count
   // yields the exact total
   hipLaunchKernelGGL(k_fill_ints, grid_for(std::min<long long>(Vmax, 1 << 20)), dim3(kBlock), 0, st, npass, Vmax, 0);
@@ -1593,16 +1798,15 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
 
   // phase 2
   const int NI = N + P;  // sort entries: every node (constants sort last) and every pass-through
-  const int B = (NI + kRadixTile - 1) / kRadixTile;
-  const long long rc = 256LL * std::max(B, 1);
+  const int B = (NI + kTile - 1) / kTile;
   Temp tmp2(st);
   unsigned *ka = nullptr, *kb = nullptr;
-  int *va = nullptr, *vb = nullptr, *flag = nullptr, *exs = nullptr, *radix_counts = nullptr, *scan_tmp = nullptr;
+  int *va = nullptr, *vb = nullptr, *flag = nullptr, *exs = nullptr, *sort_counts = nullptr, *scan_tmp = nullptr;
   int *bidx = nullptr, *gcount = nullptr, *cnt = nullptr, *cscan = nullptr, *dspan = nullptr, *vidx = nullptr,
       *pidx = nullptr, *stage = nullptr;
   constexpr int kCap = 4096;  // batches and state sizes read back with the final error word
   const size_t stage_n = kHdr + 5 * (size_t)kCap;
-  const long long scan_n = std::max<long long>(std::max<long long>(rc, NI), (long long)T * Mc);
+  const long long scan_n = std::max<long long>(NI, (long long)T * Mc);
   tmp2.reserve(&stage, stage_n);
   tmp2.reserve(&ka, std::max(NI, 1));
   tmp2.reserve(&kb, std::max(NI, 1));
@@ -1610,7 +1814,7 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   tmp2.reserve(&vb, std::max(NI, 1));
   tmp2.reserve(&flag, std::max(NI, 1));
   tmp2.reserve(&exs, std::max(NI, 1));
-  tmp2.reserve(&radix_counts, rc);
+  tmp2.reserve(&sort_counts, (size_t)(B + 1) * kDigits);
   tmp2.reserve(&scan_tmp, (size_t)(scan_n / kScanTile + 2));
   tmp2.reserve(&bidx, Mc);
   tmp2.reserve(&gcount, Mc);
@@ -1633,15 +1837,10 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
     const unsigned sent = (unsigned)(D * KT);
     hipLaunchKernelGGL(k_typed_keys, grid_for(NI), dim3(kBlock), 0, st, depth, b->node_op, N, s.pass_node,
                        s.pass_slot, s.pass_depth, P, ops, sent, ka, va);
-    int bits = 1;
-    while (bits < 32 && ((unsigned long long)sent >> bits)) ++bits;
-    const int passes = (bits + 7) / 8;
+    const int passes = sort_passes(sent);
     for (int ps = 0; ps < passes; ++ps) {
-      hipLaunchKernelGGL(k_radix_count, dim3(B), dim3(kBlock), 0, st, ka, NI, 8 * ps, radix_counts, B, err,
-                         (const int*)nullptr, 0);
-      scan_exclusive(radix_counts, radix_counts, (int)rc, meta + 6, scan_tmp, st);
-      hipLaunchKernelGGL(k_radix_scatter, dim3(B), dim3(kBlock), 0, st, ka, va, kb, vb, radix_counts, NI, 8 * ps, B,
-                         err, (const int*)nullptr, 0);
+      sort_pass<PairKeys<unsigned>>({ka, va}, {NI, nullptr}, kDigitBits * ps, sort_counts, kb, vb, {err, nullptr, 0, 0},
+                                    err, &em->cycle, st);
       std::swap(ka, kb);
       std::swap(va, vb);
     }

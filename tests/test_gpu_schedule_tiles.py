@@ -1,0 +1,65 @@
+"""The scheduler at the edges of its tiles and digits, bit-exact against the oracle's reference scheduler: batches one
+node around a tile of 2,048 and around the 32 tiles up to which a tile adds up its predecessors itself, keys of one, two
+and three 10-bit digits, and the leaf-table runs of several operations over many tiles (through the gradient they sum)."""
+import numpy as np
+import pytest
+
+from paper_1702_02181_amd import gen
+from tests import gpu_common as C
+from tests.test_gpu_schedule import _gpu_sched
+
+pytestmark = pytest.mark.gpu
+
+
+def _chains(rng, total, longest, num_ops):
+    """`total` nodes in chains of up to `longest`: an embedding, then random unary operations."""
+    graphs, left = [], total
+    while left:
+        n = min(left, int(rng.integers(1, longest + 1)))
+        op = np.concatenate([[0], rng.integers(1, num_ops, n - 1)]).astype(np.int32)
+        cnt = np.concatenate([[0], np.ones(n - 1)]).astype(np.int32)
+        inp = np.concatenate([[int(rng.integers(0, 9))], -np.ones(n - 1)]).astype(np.int64)
+        graphs.append((op, cnt, np.arange(n - 1), inp))
+        left -= n
+    ops = [gen.OpSpec(gen.KIND_EMBED, 0, 1, 0)] + [gen.OpSpec(gen.KIND_PROJ, 1, 0, 1)] * (num_ops - 1)
+    csr = gen.assemble(graphs)
+    return gen.Workload("chains", "f32", 2, ops=ops, params=[], leaf_table=np.zeros((9, 2), np.float32),
+                        dh_roots=np.zeros((len(graphs), 2), np.float32), **csr)
+
+
+@pytest.mark.parametrize("total,longest,num_ops", [
+    (1, 1, 2), (63, 5, 2), (2047, 9, 3), (2048, 9, 2), (2049, 40, 5),
+    (65535, 30, 2), (65537, 30, 4),     # 32 tiles and one node more: the column scan
+    (3000, 700, 3),                     # two digits
+    (5000, 5000, 256),                  # one chain of 5,000: keys past 2^20, three digits, no room in LDS
+])
+def test_tile_and_digit_edges(total, longest, num_ops):
+    w = _chains(np.random.default_rng(total + num_ops), total, longest, num_ops)
+    C.assert_schedule_equal(_gpu_sched(w), C.oracle_schedule(w))
+
+
+@pytest.mark.parametrize("total,rows", [(1, 1), (2049, 1), (4097, 3000), (70001, 5), (70001, 100003)])
+def test_leaf_table_runs(total, rows):
+    """Nodes that are embeddings of two operations, both reading random rows: each leaf-table row's gradient is the sum
+    of its nodes' upstream gradients (fp32 sums of n terms: error below n 2^-24 times the sum of their magnitudes)."""
+    import torch
+    from paper_1702_02181_amd.runner import DeviceRun
+    rng = np.random.default_rng(total + rows)
+    op, inp = rng.integers(0, 2, total), rng.integers(0, rows, total)
+    csr = dict(graph_ptr=np.arange(total + 1, dtype=np.int32), node_op=op.astype(np.int32),
+               child_ptr=np.zeros(total + 1, np.int32), child_idx=np.zeros(0, np.int32), node_input=inp.astype(np.int32))
+    params = [gen.ParamSet(gen.KIND_EMBED, 2, 0, None, None, np.zeros(0, np.float32))] * 2
+    w = gen.Workload("rows", "f32", 2, ops=[gen.OpSpec(gen.KIND_EMBED, 0, 1, 0), gen.OpSpec(gen.KIND_EMBED, 0, 1, 1)],
+                     params=params, leaf_table=np.zeros((rows, 2), np.float32),
+                     dh_roots=rng.standard_normal((total, 2)).astype(np.float32), **csr)
+    dev = DeviceRun(w)
+    dev.forward()
+    dev.alloc_grads(True)
+    dev.set_upstream(w.dh_roots)
+    dev.backward()
+    torch.cuda.synchronize()
+    got = dev.d_table.cpu().numpy()[:, :2].astype(np.float64)
+    want, size, count = np.zeros((rows, 2)), np.zeros((rows, 2)), np.bincount(inp, minlength=rows)[:, None]
+    np.add.at(want, inp, w.dh_roots.astype(np.float64))
+    np.add.at(size, inp, np.abs(w.dh_roots.astype(np.float64)))
+    assert np.all(np.abs(got - want) <= (count + 1) * 2.0 ** -24 * size)
