@@ -122,7 +122,7 @@ struct Sched {
 
 // The paper's own form of a schedule (typed per-depth states, pass-through operations), fold_schedule_typed.
 struct TypedSched {
-  int N = 0, E = 0, K = 0, T = 0, D = 0, nb = 0, P = 0, M = 0, ngather = 0;
+  int N = 0, E = 0, K = 0, T = 0, D = 0, nb = 0, P = 0, M = 0, ngather = 0, device = 0;
   void* blob = nullptr;  // every device array below
   int32_t *depth = nullptr, *batch_depth = nullptr, *batch_op = nullptr, *batch_rows = nullptr,
           *batch_goff = nullptr, *batch_begin = nullptr, *item_node = nullptr, *gather = nullptr,

@@ -1,0 +1,169 @@
+// Blocks and read-back buffers of the schedules (see pool.h).
+
+#include "pool.h"
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <map>
+#include <mutex>
+#include <vector>
+
+namespace fold {
+
+namespace {
+
+struct Idle {
+  void* ptr;
+  size_t bytes;
+};
+
+struct DevicePool {
+  std::vector<Idle> idle;  // oldest first
+  size_t idle_bytes = 0;
+  int alive = 0;
+};
+
+struct Pools {
+  std::mutex mu;
+  std::map<int, DevicePool> device;
+  std::map<void*, size_t> handed_out;
+  std::vector<int*> stages;
+};
+
+// never destroyed: no HIP call is made after the runtime's own shutdown
+Pools& pools() {
+  static Pools* p = new Pools;
+  return *p;
+}
+
+size_t size_class(size_t bytes) {
+  size_t step = 1 << 14;  // classes of 64 KB and more: 4, 5, 6, 7 steps
+  while (7 * step < bytes) step *= 2;
+  return std::max<size_t>(4, (bytes + step - 1) / step) * step;
+}
+
+// takes the oldest idle blocks past `keep` bytes out of the pool
+std::vector<void*> trim(DevicePool& d, size_t keep) {
+  std::vector<void*> out;
+  while (d.idle_bytes > keep) {
+    out.push_back(d.idle.front().ptr);
+    d.idle_bytes -= d.idle.front().bytes;
+    d.idle.erase(d.idle.begin());
+  }
+  return out;
+}
+
+void release(const std::vector<void*>& blocks) {
+  for (void* p : blocks) (void)hipFree(p);
+}
+
+}  // namespace
+
+void* pool_alloc(int device, size_t bytes, bool lasting) {
+  Pools& P = pools();
+  const size_t size = size_class(bytes);
+  std::vector<void*> drop;
+  {
+    std::lock_guard<std::mutex> lk(P.mu);
+    DevicePool& d = P.device[device];
+    for (size_t i = d.idle.size(); i-- > 0;) {  // the last one given back first
+      if (d.idle[i].bytes != size) continue;
+      void* p = d.idle[i].ptr;
+      P.handed_out[p] = size;
+      d.idle_bytes -= size;
+      d.idle.erase(d.idle.begin() + i);
+      d.alive += lasting;
+      return p;
+    }
+  }
+  void* p = nullptr;
+  if (hipMalloc(&p, size) != hipSuccess) {
+    (void)hipGetLastError();
+    {
+      std::lock_guard<std::mutex> lk(P.mu);
+      drop = trim(P.device[device], 0);
+    }
+    release(drop);
+    if (hipMalloc(&p, size) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+  }
+  std::lock_guard<std::mutex> lk(P.mu);
+  P.handed_out[p] = size;
+  P.device[device].alive += lasting;
+  return p;
+}
+
+void pool_free(int device, void* ptr, bool lasting) {
+  if (!ptr) return;
+  Pools& P = pools();
+  std::vector<void*> drop;
+  {
+    std::lock_guard<std::mutex> lk(P.mu);
+    DevicePool& d = P.device[device];
+    auto it = P.handed_out.find(ptr);
+    if (it == P.handed_out.end()) return;
+    d.idle.push_back({ptr, it->second});
+    d.idle_bytes += it->second;
+    P.handed_out.erase(it);
+    d.alive -= lasting;
+    drop = trim(d, d.alive > 0 ? kIdleBytes : kIdleBytesUnused);
+  }
+  release(drop);
+}
+
+void pool_free_after_wait(int device, void* ptr) {
+  if (!ptr) return;
+  int current = device;
+  (void)hipGetDevice(&current);
+  if (current != device) (void)hipSetDevice(device);
+  const bool waited = hipDeviceSynchronize() == hipSuccess;
+  if (waited) {
+    pool_free(device, ptr, true);
+  } else {  // a stream capture in progress, or a device in error: as if there were no pool
+    (void)hipGetLastError();
+    {
+      Pools& P = pools();
+      std::lock_guard<std::mutex> lk(P.mu);
+      P.handed_out.erase(ptr);
+      P.device[device].alive -= 1;
+    }
+    (void)hipFree(ptr);
+  }
+  if (current != device) (void)hipSetDevice(current);
+}
+
+int* stage_alloc() {
+  Pools& P = pools();
+  {
+    std::lock_guard<std::mutex> lk(P.mu);
+    if (!P.stages.empty()) {
+      int* p = P.stages.back();
+      P.stages.pop_back();
+      return p;
+    }
+  }
+  void* p = nullptr;
+  if (hipHostMalloc(&p, kStageInts * sizeof(int), hipHostMallocPortable) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return static_cast<int*>(p);
+}
+
+void stage_free(int* p) {
+  if (!p) return;
+  Pools& P = pools();
+  {
+    std::lock_guard<std::mutex> lk(P.mu);
+    if ((int)P.stages.size() < kIdleStages) {
+      P.stages.push_back(p);
+      return;
+    }
+  }
+  (void)hipHostFree(p);
+}
+
+}  // namespace fold

@@ -25,6 +25,7 @@
 
 #include "common.h"
 #include "internal.h"
+#include "pool.h"
 
 namespace fold {
 
@@ -1037,32 +1038,37 @@ __global__ void k_finish(const unsigned long long* err, const int* meta, const i
 
 inline dim3 grid_for(long long n) { return dim3((unsigned)std::max(1LL, (n + kBlock - 1) / kBlock)); }
 
-// Stream-ordered temporaries of one phase: the sizes are declared first (reserve), then one allocation
-// from the device's pool backs them all (commit); freed at scope exit.  One allocation per phase keeps
-// the host cost of a schedule independent of how many temporaries it uses.
+// Temporaries of one phase on one stream: the sizes are declared first (reserve), then one pooled block backs them all
+// (commit).  The block and the read-back buffer go back to the pool at scope exit, once the stream has finished with
+// them: finished() says that the call has waited already.
 struct Temp {
   hipStream_t st;
-  std::vector<void*> ptrs;
+  int device;
+  void* block = nullptr;
+  int* stage = nullptr;  // pinned, kStageInts ints
+  bool waited = false;
   std::vector<std::pair<void**, size_t>> want;
   size_t bytes = 0;
-  explicit Temp(hipStream_t s) : st(s) {}
+  Temp(hipStream_t s, int dev) : st(s), device(dev) {}
+  Temp(const Temp&) = delete;
+  Temp& operator=(const Temp&) = delete;
   ~Temp() {
-    for (void* p : ptrs) (void)hipFreeAsync(p, st);
+    if (!block && !stage) return;
+    if (!waited && hipStreamSynchronize(st) != hipSuccess) return;  // a device in error: nothing is reused
+    pool_free(device, block, false);
+    stage_free(stage);
   }
   template <class T>
   void reserve(T** p, size_t count) {
     want.push_back({reinterpret_cast<void**>(p), bytes});
     bytes += (std::max<size_t>(count, 1) * sizeof(T) + 255) / 256 * 256;
   }
-  hipError_t commit() {
-    void* q = nullptr;
-    hipError_t e = hipMallocAsync(&q, std::max<size_t>(bytes, 256), st);
-    if (e != hipSuccess) return e;
-    ptrs.push_back(q);
-    for (auto& w : want) *w.first = static_cast<char*>(q) + w.second;
-    want.clear();
-    bytes = 0;
-    return hipSuccess;
+  bool commit(bool with_stage) {
+    block = pool_alloc(device, std::max<size_t>(bytes, 256), false);
+    if (with_stage) stage = stage_alloc();
+    if (!block || (with_stage && !stage)) return false;
+    for (auto& w : want) *w.first = static_cast<char*>(block) + w.second;
+    return true;
   }
 };
 
@@ -1085,17 +1091,6 @@ int decode_error(unsigned long long w, std::string* msg) {
   }
   *msg = std::string("fold_schedule: ") + what + (node >= 0 ? " (node " + std::to_string(node) + ")" : "");
   return code;
-}
-
-void init_pool_once(int device) {
-  static bool done[64] = {false};
-  if (device < 0 || device >= 64 || done[device]) return;
-  hipMemPool_t pool;
-  if (hipDeviceGetDefaultMemPool(&pool, device) == hipSuccess) {
-    uint64_t thr = ~0ull;
-    (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &thr);
-  }
-  done[device] = true;
 }
 
 }  // namespace
@@ -1121,7 +1116,6 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   }
   int device = 0;
   FOLD_HIP_CHECK(hipGetDevice(&device));
-  init_pool_once(device);
 
   auto* h = new fold_sched();
   Sched& s = h->s;
@@ -1135,7 +1129,8 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   // persistent arrays sized by N and E; the level and group tables take N + 1 and 5 x N entries (there are
   // at most N levels and N groups), so nothing waits for the depth to be known on the host
   const size_t n1 = (size_t)N * 23 + 2 * (size_t)E + 17;
-  if (hipMalloc(&s.blob, n1 * sizeof(int)) != hipSuccess) {
+  s.blob = pool_alloc(device, n1 * sizeof(int), true);
+  if (!s.blob) {
     set_error("fold_schedule: out of device memory");
     return fail(FOLD_E_NOMEM);
   }
@@ -1167,14 +1162,14 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   s.g_cbase1 = q; q += cap;
 
   // temporaries of the whole schedule, one pooled allocation
-  Temp tmp(st);
+  Temp tmp(st, device);
   // err, then meta: [0] max depth, [1] max parents, [4] groups, [5] roots, [6] rows that read the leaf table
   struct ErrMeta {
     unsigned long long err, cycle;  // a cycle counts only where no node check failed
     int meta[8];
   };
   ErrMeta* em = nullptr;
-  int *indeg = nullptr, *scratch = nullptr, *moved = nullptr, *stage = nullptr;
+  int *indeg = nullptr, *scratch = nullptr, *moved = nullptr;
   unsigned* link = nullptr;
   unsigned* keys[2] = {nullptr, nullptr};
   unsigned long long* tok_keys[2] = {nullptr, nullptr};
@@ -1186,10 +1181,9 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   for (int i = 0; i < K; ++i) input_ops += b->ops[i].has_input ? 1 : 0;
   const bool any_input = input_ops > 0;
   constexpr int kLcap = 4096, kGcap = 4096;  // levels and groups read back with the error word
-  const size_t stage_n = kHdr + (kLcap + 1) + kGroupArrays * (size_t)kGcap + kMaxOps;
+  static_assert(kHdr + (kLcap + 1) + kGroupArrays * (size_t)kGcap + kMaxOps <= kStageInts, "the read-back buffer");
   int* op_runs = nullptr;  // [kMaxOps] runs of equal (op, leaf-table row) of the ops that read the leaf table
   tmp.reserve(&em, 1);
-  tmp.reserve(&stage, stage_n);
   tmp.reserve(&op_runs, kMaxOps);
   if (N > 0) {
     tmp.reserve(&indeg, N);
@@ -1208,7 +1202,7 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
     tmp.reserve(&tile_sums, 4 * (size_t)B);
     tmp.reserve(&op_count, (size_t)B * K);
   }
-  if (tmp.commit() != hipSuccess) {
+  if (!tmp.commit(true)) {
     set_error("fold_schedule: out of device memory (temporaries)");
     return fail(FOLD_E_NOMEM);
   }
@@ -1284,18 +1278,18 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   // a workgroup per 1,024 possible groups, at most 16 (a batch has few groups; a thousand-level chain of them still
   // takes a few steps)
   hipLaunchKernelGGL(k_finish, dim3(std::min(16, N / 1024 + 1)), dim3(kBlock), 0, st, err, meta, s.level_ptr, ga, N, moved,
-                     s.g_rows, s.g_cbase0, s.g_cbase1, kLcap, kGcap, op_runs, K, stage);
+                     s.g_rows, s.g_cbase0, s.g_cbase1, kLcap, kGcap, op_runs, K, tmp.stage);
   if (hipGetLastError() != hipSuccess) {
     set_error("fold_schedule: kernel launch failed");
     return fail(FOLD_E_DEVICE);
   }
   // the one synchronisation: error word, meta, and the level / group tables up to kLcap / kGcap entries
-  std::vector<int> hb(stage_n, 0);
-  if (hipMemcpyAsync(hb.data(), stage, stage_n * sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
-      hipStreamSynchronize(st) != hipSuccess) {
+  if (hipStreamSynchronize(st) != hipSuccess) {
     set_error("fold_schedule: device error while scheduling");
     return fail(FOLD_E_DEVICE);
   }
+  tmp.waited = true;
+  const int* hb = tmp.stage;
   const unsigned long long ew = (unsigned long long)(unsigned)hb[0] | ((unsigned long long)(unsigned)hb[1] << 32);
   if (ew != kNoErr) {
     std::string msg;
@@ -1303,7 +1297,7 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
     set_error(msg);
     return fail(code);
   }
-  const int* hm = hb.data() + 2;
+  const int* hm = hb + 2;
   const int D = N > 0 ? hm[0] : 0;
   const int ng = N > 0 ? hm[4] : 0;
   s.D = D;
@@ -1313,7 +1307,7 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   if (N == 0) {
     s.h_level_ptr.assign(1, 0);
   } else if (D + 1 <= kLcap + 1 && ng <= kGcap) {
-    const int* hl = hb.data() + kHdr;
+    const int* hl = hb + kHdr;
     s.h_level_ptr.assign(hl, hl + D + 1);
     const int* hg = hl + kLcap + 1;
     s.h_level.assign(hg, hg + ng);
@@ -1345,7 +1339,7 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   for (int g = 0; g < ng; ++g) s.h_op_row_ptr[s.h_op[g] + 1] += s.h_rows[g];
   s.h_tok_row_ptr.assign(K + 1, 0);
   s.h_tok_ptr.assign(K + 1, 0);
-  const int* runs = hb.data() + kHdr + (kLcap + 1) + kGroupArrays * kGcap;
+  const int* runs = hb + kHdr + (kLcap + 1) + kGroupArrays * kGcap;
   for (int o = 0; o < K; ++o) {
     const bool reads = N > 0 && b->ops[o].has_input;
     s.h_tok_row_ptr[o + 1] = s.h_tok_row_ptr[o] + (reads ? s.h_op_row_ptr[o + 1] : 0);
@@ -1358,7 +1352,7 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
 
 void sched_destroy_impl(fold_sched* h) {
   if (!h) return;
-  if (h->s.blob) (void)hipFree(h->s.blob);
+  if (h->s.blob) pool_free_after_wait(h->s.device, h->s.blob);
   delete h;
 }
 
@@ -1634,7 +1628,7 @@ __global__ void k_typed_compact(const unsigned long long* err, const int* meta, 
 
 void typed_sched_destroy_impl(fold_typed_sched* h) {
   if (!h) return;
-  if (h->t.blob) (void)hipFree(h->t.blob);
+  if (h->t.blob) pool_free_after_wait(h->t.device, h->t.blob);
   delete h;
 }
 
@@ -1675,10 +1669,9 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   }
   int device = 0;
   FOLD_HIP_CHECK(hipGetDevice(&device));
-  init_pool_once(device);
   auto* h = new fold_typed_sched();
   TypedSched& s = h->t;
-  s.N = N; s.E = E; s.K = K; s.T = T;
+  s.N = N; s.E = E; s.K = K; s.T = T; s.device = device;
   auto fail = [&](int code) {
     typed_sched_destroy_impl(h);
     return code;
@@ -1690,7 +1683,7 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
 
   // phase 1 temporaries (kept to the end): N-sized, and values (at most 8 per node)
   const long long Vmax = 8LL * std::max(N, 1);
-  Temp tmp1(st);
+  Temp tmp1(st, device);
   struct ErrMeta {
     unsigned long long err, cycle;
     int meta[8 + kMaxTypes];  // [0] max depth + 1, [1] max parents, [2] values, [3] pass-throughs,
@@ -1713,7 +1706,7 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   tmp1.reserve(&npass, Vmax);
   tmp1.reserve(&pass_ptr, Vmax);
   tmp1.reserve(&scan_tmp1, (size_t)(Vmax / kScanTile + 2));
-  if (tmp1.commit() != hipSuccess) {
+  if (!tmp1.commit(false)) {
     set_error("fold_schedule_typed: out of device memory (temporaries)");
     return fail(FOLD_E_NOMEM);
   }
@@ -1775,7 +1768,8 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   const size_t Mc = std::max(M, 1);
   const size_t n_int = (size_t)N + 6 * Mc + (size_t)std::max(ngather, 1) + 3 * (size_t)std::max(P, 1) + nsize +
                        (size_t)std::max(E, 1) + 16;
-  if (hipMalloc(&s.blob, n_int * sizeof(int)) != hipSuccess) {
+  s.blob = pool_alloc(device, n_int * sizeof(int), true);
+  if (!s.blob) {
     set_error("fold_schedule_typed: out of device memory");
     return fail(FOLD_E_NOMEM);
   }
@@ -1799,15 +1793,14 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   // phase 2
   const int NI = N + P;  // sort entries: every node (constants sort last) and every pass-through
   const int B = (NI + kTile - 1) / kTile;
-  Temp tmp2(st);
+  Temp tmp2(st, device);
   unsigned *ka = nullptr, *kb = nullptr;
   int *va = nullptr, *vb = nullptr, *flag = nullptr, *exs = nullptr, *sort_counts = nullptr, *scan_tmp = nullptr;
   int *bidx = nullptr, *gcount = nullptr, *cnt = nullptr, *cscan = nullptr, *dspan = nullptr, *vidx = nullptr,
-      *pidx = nullptr, *stage = nullptr;
+      *pidx = nullptr;
   constexpr int kCap = 4096;  // batches and state sizes read back with the final error word
-  const size_t stage_n = kHdr + 5 * (size_t)kCap;
+  static_assert(kHdr + 5 * (size_t)kCap <= kStageInts, "the read-back buffer");
   const long long scan_n = std::max<long long>(NI, (long long)T * Mc);
-  tmp2.reserve(&stage, stage_n);
   tmp2.reserve(&ka, std::max(NI, 1));
   tmp2.reserve(&kb, std::max(NI, 1));
   tmp2.reserve(&va, std::max(NI, 1));
@@ -1823,7 +1816,7 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   tmp2.reserve(&dspan, 2 * (size_t)(D + 1));
   tmp2.reserve(&vidx, std::max(V, 1));
   tmp2.reserve(&pidx, std::max(P, 1));
-  if (tmp2.commit() != hipSuccess) {
+  if (!tmp2.commit(true)) {
     set_error("fold_schedule_typed: out of device memory (temporaries)");
     return fail(FOLD_E_NOMEM);
   }
@@ -1874,16 +1867,15 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   }
   // batches <= items; read back the batch table and the state sizes up to kCap entries each
   hipLaunchKernelGGL(k_typed_compact, dim3(1), dim3(kBlock), 0, st, err, meta, s.batch_depth, s.batch_op,
-                     s.batch_rows, s.batch_goff, s.state_size, M, (int)nsize, kCap, stage);
+                     s.batch_rows, s.batch_goff, s.state_size, M, (int)nsize, kCap, tmp2.stage);
   if (hipGetLastError() != hipSuccess) return device_error("kernel launch failed");
-  std::vector<int> hb(stage_n, 0);
-  if (hipMemcpyAsync(hb.data(), stage, stage_n * sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
-      hipStreamSynchronize(st) != hipSuccess)
-    return device_error("device error while scheduling");
+  if (hipStreamSynchronize(st) != hipSuccess) return device_error("device error while scheduling");
+  tmp1.waited = tmp2.waited = true;
+  const int* hb = tmp2.stage;
   const int nb = M > 0 ? hb[2 + 4] : 0;
   s.nb = nb;
   if (nb <= kCap && (int)nsize <= kCap) {
-    const int* hs = hb.data() + kHdr;
+    const int* hs = hb + kHdr;
     s.h_depth_b.assign(hs, hs + nb);
     s.h_op_b.assign(hs + kCap, hs + kCap + nb);
     s.h_rows_b.assign(hs + 2 * kCap, hs + 2 * kCap + nb);

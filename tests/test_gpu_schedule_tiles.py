@@ -63,3 +63,27 @@ def test_leaf_table_runs(total, rows):
     np.add.at(want, inp, w.dh_roots.astype(np.float64))
     np.add.at(size, inp, np.abs(w.dh_roots.astype(np.float64)))
     assert np.all(np.abs(got - want) <= (count + 1) * 2.0 ** -24 * size)
+
+
+def test_schedules_from_several_threads():
+    """Schedules made and freed by four threads on streams of their own: the blocks they hand one another are whole."""
+    import threading
+    import torch
+    works = [_chains(np.random.default_rng(k), 500 + 700 * k, 12, 3) for k in range(4)]
+    refs = [C.oracle_schedule(w) for w in works]
+    failed = []
+
+    def go(k):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for i in range(6):
+                    C.assert_schedule_equal(_gpu_sched(works[(k + i) % 4]), refs[(k + i) % 4])
+        except BaseException as e:  # noqa: BLE001 -- reported by the main thread
+            failed.append(repr(e))
+
+    threads = [threading.Thread(target=go, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed
