@@ -407,8 +407,10 @@ inline int graph_lds_bytes(long long N, long long E, int G, int node_bytes, int 
 
 // ---------------------------------------------------------------- device-wide exclusive scan
 
+// blockIdx.y: one of several arrays of n, side by side (their partial sums and totals too)
 __global__ void k_scan_reduce(const int* in, int n, int* partial) {
   const int b = blockIdx.x, t = threadIdx.x;
+  in += (size_t)blockIdx.y * n;
   const long long base = (long long)b * kScanTile + (long long)t * kScanItems;
   int s = 0;
   for (int i = 0; i < kScanItems; ++i) {
@@ -416,12 +418,15 @@ __global__ void k_scan_reduce(const int* in, int n, int* partial) {
     if (j < n) s += in[j];
   }
   s = block_sum<kBlock>(s);
-  if (t == 0) partial[b] = s;
+  if (t == 0) partial[blockIdx.y * gridDim.x + b] = s;
 }
 
 // every workgroup adds up the sums of the tiles before its own (a launch less than a scan of them)
 __global__ void k_scan_down(const int* in, int n, const int* partial, int* out, int* total) {
   const int b = blockIdx.x, t = threadIdx.x;
+  in += (size_t)blockIdx.y * n;
+  out += (size_t)blockIdx.y * n;
+  partial += blockIdx.y * gridDim.x;
   const long long base = (long long)b * kScanTile + (long long)t * kScanItems;
   int v[kScanItems];
   int s = 0, before = 0;
@@ -439,14 +444,15 @@ __global__ void k_scan_down(const int* in, int n, const int* partial, int* out, 
     if (j < n) out[j] = pre;
     pre += v[i];
   }
-  if (b == (int)gridDim.x - 1 && t == 0) *total = before + tot;
+  if (b == (int)gridDim.x - 1 && t == 0) total[blockIdx.y] = before + tot;
 }
 
-// exclusive scan in -> out (may alias), total -> *total (device); temp holds >= ceil(n / tile) ints
-void scan_exclusive(const int* in, int* out, int n, int* total, int* temp, hipStream_t st) {
+// exclusive scans of `rows` arrays of n, in -> out (may alias), their totals -> total[0 .. rows) (device); temp holds
+// rows * ceil(n / tile) ints
+void scan_exclusive(const int* in, int* out, int n, int rows, int* total, int* temp, hipStream_t st) {
   const int nb = std::max(1, (n + kScanTile - 1) / kScanTile);
-  hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kBlock), 0, st, in, n, temp);
-  hipLaunchKernelGGL(k_scan_down, dim3(nb), dim3(kBlock), 0, st, in, n, temp, out, total);
+  hipLaunchKernelGGL(k_scan_reduce, dim3(nb, rows), dim3(kBlock), 0, st, in, n, temp);
+  hipLaunchKernelGGL(k_scan_down, dim3(nb, rows), dim3(kBlock), 0, st, in, n, temp, out, total);
 }
 
 // ---------------------------------------------------------------- stable LSD radix sort
@@ -987,11 +993,6 @@ __global__ __launch_bounds__(kTileThreads) void k_tok_emit(const unsigned long l
     if (runs[o]) atomicAdd(&number_runs[o], runs[o]);
 }
 
-__global__ void k_fill_ints(int* p, long long n, int v) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
 // error words "none", the meta words and `more` zero
 __global__ void k_init_meta(void* em, int words, int* more, int n_more) {
   if (threadIdx.x < 2) static_cast<unsigned long long*>(em)[threadIdx.x] = kNoErr;
@@ -1405,63 +1406,70 @@ __global__ void k_typed_check(const int* node_op, const int* in_ptr, const int* 
   }
 }
 
-// paper depth (constants 0), the number of values of each node, the number of constants of each type
+// paper depth (constants 0), the number of values of each node and of constants of each type; last[8 v + k] = the
+// deepest depth that reads value k of node v (its own depth if nobody does)
 __global__ void k_typed_nodes(const int* kdepth, const int* node_op, int N, TypedOpTable ops, int* depth,
-                              int* nout_v, int* meta, const unsigned long long* err) {
+                              int* nout_v, int* last, int* meta, const unsigned long long* err) {
   if (*err != kNoErr) return;
+  // constants are counted in LDS first: an add per constant to one counter takes 370 us for 32,000 of them
+  __shared__ int consts[kMaxTypes];
+  if (threadIdx.x < kMaxTypes) consts[threadIdx.x] = 0;
+  __syncthreads();
   const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= N) return;
-  const int op = node_op[v];
-  depth[v] = kdepth[v] - 1;
-  nout_v[v] = t_nout(ops, op);
-  if (op < 0) atomicAdd(&meta[8 + (-1 - op)], 1);
-}
-
-// last[value] = the deepest depth that reads it (its own depth if nobody does)
-__global__ void k_typed_last_init(const int* depth, const int* nout_v, const int* val_ptr, int N, int* last,
-                                  const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= N) return;
-  for (int k = 0; k < nout_v[v]; ++k) last[val_ptr[v] + k] = depth[v];
-}
-
-__global__ void k_typed_last(const int* depth, const int* in_ptr, const int* in_node, const int* in_slot,
-                             const int* val_ptr, int N, int* last, const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= N) return;
-  for (int e = in_ptr[v]; e < in_ptr[v + 1]; ++e) atomicMax(&last[val_ptr[in_node[e]] + in_slot[e]], depth[v]);
-}
-
-// pass-through instances of every value: one per depth strictly between its own and its deepest reader's
-__global__ void k_typed_npass(const int* depth, const int* nout_v, const int* val_ptr, const int* last, int N,
-                              int* npass, const unsigned long long* err) {
-  if (*err != kNoErr) return;
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= N) return;
-  for (int k = 0; k < nout_v[v]; ++k) {
-    const int q = val_ptr[v] + k;
-    npass[q] = max(0, last[q] - depth[v] - 1);
+  if (v < N) {
+    const int op = node_op[v], d = kdepth[v] - 1, n = t_nout(ops, op);
+    depth[v] = d;
+    nout_v[v] = n;
+    for (int k = 0; k < n; ++k) last[(size_t)kMaxSlots * v + k] = d;
+    if (op < 0) atomicAdd(&consts[-1 - op], 1);
   }
+  __syncthreads();
+  if (threadIdx.x < kMaxTypes && consts[threadIdx.x]) atomicAdd(&meta[8 + threadIdx.x], consts[threadIdx.x]);
 }
 
-__global__ void k_typed_pass_emit(const int* depth, const int* nout_v, const int* val_ptr, const int* npass,
-                                  const int* pass_ptr, int N, int* pass_node, int* pass_slot, int* pass_depth) {
+__global__ void k_typed_last(const int* depth, const int* in_ptr, const int* in_node, const int* in_slot, int N,
+                             int* last, const unsigned long long* err) {
+  if (*err != kNoErr) return;
   const int v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= N) return;
+  for (int e = in_ptr[v]; e < in_ptr[v + 1]; ++e)
+    atomicMax(&last[(size_t)kMaxSlots * in_node[e] + in_slot[e]], depth[v]);
+}
+
+// pass-through instances of every node's values: one per depth strictly between a value's own and its deepest reader's
+__device__ __forceinline__ int t_passes(const int* last, int v, int k, int d) {
+  return max(0, last[(size_t)kMaxSlots * v + k] - d - 1);
+}
+__global__ void k_typed_npass(const int* depth, const int* nout_v, const int* last, int N, int* npass,
+                              const unsigned long long* err) {
+  if (*err != kNoErr) return;
+  const int v = blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= N) return;
+  int n = 0;
+  for (int k = 0; k < nout_v[v]; ++k) n += t_passes(last, v, k, depth[v]);
+  npass[v] = n;
+}
+
+// the instances, and the first one of every value
+__global__ void k_typed_pass_emit(const int* depth, const int* nout_v, const int* val_ptr, const int* last,
+                                  const int* node_pass, int N, int* pass_ptr, int* pass_node, int* pass_slot,
+                                  int* pass_depth) {
+  const int v = blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= N) return;
+  int p = node_pass[v];
   for (int k = 0; k < nout_v[v]; ++k) {
-    const int q = val_ptr[v] + k, p0 = pass_ptr[q];
-    for (int j = 0; j < npass[q]; ++j) {
-      pass_node[p0 + j] = v;
-      pass_slot[p0 + j] = k;
-      pass_depth[p0 + j] = depth[v] + 1 + j;
+    pass_ptr[val_ptr[v] + k] = p;
+    const int n = t_passes(last, v, k, depth[v]);
+    for (int j = 0; j < n; ++j, ++p) {
+      pass_node[p] = v;
+      pass_slot[p] = k;
+      pass_depth[p] = depth[v] + 1 + j;
     }
   }
 }
 
-// sort keys (depth - 1) * (K + T) + op of operation nodes and pass-throughs (op K + t); constants get `sent`,
-// past every real key, and sort to the end
+// sort keys (depth - 1) * (K + T) + op of operation nodes and pass-throughs (op K + t); constants of type t get
+// `sent` + t, past every real key, and sort to the end by type
 __global__ void k_typed_keys(const int* depth, const int* node_op, int N, const int* pass_node, const int* pass_slot,
                              const int* pass_depth, int P, TypedOpTable ops, unsigned sent, unsigned* keys,
                              int* vals) {
@@ -1469,7 +1477,7 @@ __global__ void k_typed_keys(const int* depth, const int* node_op, int N, const 
   const int KT = ops.K + ops.T;
   if (i < N) {
     const int op = node_op[i];
-    keys[i] = op < 0 ? sent : (unsigned)((depth[i] - 1) * KT + op);
+    keys[i] = op < 0 ? sent + (unsigned)(-1 - op) : (unsigned)((depth[i] - 1) * KT + op);
     vals[i] = i;
   } else if (i < N + P) {
     const int p = i - N, u = pass_node[p], uop = node_op[u];
@@ -1479,10 +1487,18 @@ __global__ void k_typed_keys(const int* depth, const int* node_op, int N, const 
   }
 }
 
-__global__ void k_typed_items(const unsigned* keys, const int* vals, int M, int N, int* item_node, int* flag) {
+// the items in order, then the constants: a constant's index in its concatenation is its rank in its type
+__global__ void k_typed_items(const unsigned* keys, const int* vals, int M, int n, int N, unsigned sent,
+                              const int* meta, const int* val_ptr, int* item_node, int* flag, int* vidx) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= M) return;
+  if (i >= n) return;
   const int x = vals[i];
+  if (i >= M) {
+    int rank = i - M;
+    for (int t = 0; t < (int)(keys[i] - sent); ++t) rank -= meta[8 + t];
+    vidx[val_ptr[x]] = rank;
+    return;
+  }
   item_node[i] = x < N ? x : -1 - (x - N);
   flag[i] = (i == 0 || keys[i] != keys[i - 1]) ? 1 : 0;
 }
@@ -1500,32 +1516,33 @@ __global__ void k_typed_batches(const unsigned* keys, const int* flag, const int
   }
 }
 
-// per batch (entries past the batch count get zeros): rows, gather entries, and per type t its outputs of
-// type t (rows * the op's outputs of type t) at cnt[t * M + b]
+// per batch (entries past the batch count get zeros): rows, per type t its outputs of type t (rows * the op's outputs
+// of type t) at cnt[t * M + b], and its gather entries at cnt[T * M + b]
 __global__ void k_typed_batch_sizes(const int* nb_ptr, int M, const int* b_begin, const int* b_op, TypedOpTable ops,
-                                    int* b_rows, int* gcount, int* cnt) {
+                                    int* b_rows, int* cnt) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= M) return;
   const int nb = *nb_ptr;
   if (b >= nb) {
-    gcount[b] = 0;
-    for (int t = 0; t < ops.T; ++t) cnt[(size_t)t * M + b] = 0;
+    for (int t = 0; t <= ops.T; ++t) cnt[(size_t)t * M + b] = 0;
     return;
   }
   const int rows = (b + 1 < nb ? b_begin[b + 1] : M) - b_begin[b];
   const int op = b_op[b];
   b_rows[b] = rows;
-  gcount[b] = rows * (op < ops.K ? ops.nin[op] : 1);
+  cnt[(size_t)ops.T * M + b] = rows * (op < ops.K ? ops.nin[op] : 1);
   for (int t = 0; t < ops.T; ++t)
     cnt[(size_t)t * M + b] = rows * (op < ops.K ? ops.nout_t[op][t] : (op - ops.K == t ? 1 : 0));
 }
 
-// first and last batch of every depth
-__global__ void k_typed_depth_span(const int* nb_ptr, const int* b_depth, int* dfirst, int* dlast) {
+// first and last batch of every depth; the batches' gather offsets
+__global__ void k_typed_depth_span(const int* nb_ptr, const int* b_depth, const int* goff, int* dfirst, int* dlast,
+                                   int* b_goff) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   const int nb = *nb_ptr;
   if (b >= nb) return;
   const int d = b_depth[b];
+  b_goff[b] = goff[b];
   if (b == 0 || b_depth[b - 1] != d) dfirst[d] = b;
   if (b == nb - 1 || b_depth[b + 1] != d) dlast[d] = b;
 }
@@ -1542,16 +1559,6 @@ __global__ void k_typed_state_size(int D, int M, int T, const int* dfirst, const
   }
   const size_t o = (size_t)t * M;
   size[i] = cscan[o + dlast[d]] + cnt[o + dlast[d]] - cscan[o + dfirst[d]];
-}
-
-// concatenation index of every constant: its rank among the constants of its type (flag scan of type t)
-__global__ void k_typed_const_flag(const int* node_op, int N, int t, int* flag) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < N) flag[v] = node_op[v] == -1 - t ? 1 : 0;
-}
-__global__ void k_typed_const_idx(const int* flag, const int* exs, const int* val_ptr, int N, int* vidx) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < N && flag[v]) vidx[val_ptr[v]] = exs[v];
 }
 
 // concatenation index of every item's outputs at the item's depth: vidx[value] for operation nodes,
@@ -1604,24 +1611,25 @@ __global__ void k_typed_gather(const int* item_node, const int* bidx, const int*
   }
 }
 
-__global__ void k_typed_compact(const unsigned long long* err, const int* meta, const int* b_depth, const int* b_op,
-                                const int* b_rows, const int* b_goff, const int* size, int nb, int nsize, int cap,
-                                int* out) {
+__global__ void k_typed_finish(const unsigned long long* err, const int* meta, const int* b_depth, const int* b_op,
+                               const int* b_rows, const int* b_goff, const int* size, int M, int nsize, int cap,
+                               int* out) {
   const unsigned long long e = *err;
-  if (threadIdx.x == 0) {
+  const int i0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  if (i0 == 0) {
     out[0] = (int)(unsigned)(e & 0xffffffffull);
     out[1] = (int)(unsigned)(e >> 32);
     for (int i = 0; i < 14; ++i) out[2 + i] = meta[i];
   }
   if (e != kNoErr) return;
-  const int n = min(nb, cap), ns = min(nsize, cap);
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+  const int n = M > 0 ? min(meta[4], cap) : 0, ns = min(nsize, cap);
+  for (int i = i0; i < n; i += step) {
     out[kHdr + i] = b_depth[i];
     out[kHdr + cap + i] = b_op[i];
     out[kHdr + 2 * cap + i] = b_rows[i];
     out[kHdr + 3 * cap + i] = b_goff[i];
   }
-  for (int i = threadIdx.x; i < ns; i += blockDim.x) out[kHdr + 4 * cap + i] = size[i];
+  for (int i = i0; i < ns; i += step) out[kHdr + 4 * cap + i] = size[i];
 }
 
 }  // namespace
@@ -1681,31 +1689,27 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
     return fail(FOLD_E_DEVICE);
   };
 
-  // phase 1 temporaries (kept to the end): N-sized, and values (at most 8 per node)
-  const long long Vmax = 8LL * std::max(N, 1);
+  // phase 1 temporaries (kept to the end)
   Temp tmp1(st, device);
   struct ErrMeta {
     unsigned long long err, cycle;
     int meta[8 + kMaxTypes];  // [0] max depth + 1, [1] max parents, [2] values, [3] pass-throughs,
-                              // [4] batches, [5] gather entries, [6, 7] scratch totals, [8 + t] constants of type t
+                              // [4] batches, [8 + t] constants of type t
   };
   static_assert(offsetof(ErrMeta, meta) == 2 * sizeof(unsigned long long), "k_init_meta's layout");
   ErrMeta* em = nullptr;
   int *node_graph = nullptr, *indeg = nullptr, *scratch = nullptr, *kdepth = nullptr, *depth = nullptr,
-      *nout_v = nullptr, *val_ptr = nullptr, *last = nullptr, *npass = nullptr, *pass_ptr = nullptr,
-      *scan_tmp1 = nullptr;
+      *counts = nullptr, *offsets = nullptr, *last = nullptr, *scan_tmp1 = nullptr;  // values and pass-throughs by node
   tmp1.reserve(&em, 1);
   tmp1.reserve(&node_graph, N);
   tmp1.reserve(&indeg, N);
   tmp1.reserve(&scratch, GlobLinks<false>::kNodeInts * (size_t)N + GlobLinks<false>::kEdgeInts * (size_t)E);
   tmp1.reserve(&kdepth, N);
   tmp1.reserve(&depth, N);
-  tmp1.reserve(&nout_v, N);
-  tmp1.reserve(&val_ptr, N);
-  tmp1.reserve(&last, Vmax);
-  tmp1.reserve(&npass, Vmax);
-  tmp1.reserve(&pass_ptr, Vmax);
-  tmp1.reserve(&scan_tmp1, (size_t)(Vmax / kScanTile + 2));
+  tmp1.reserve(&counts, 2 * (size_t)N);
+  tmp1.reserve(&offsets, 2 * (size_t)N);
+  tmp1.reserve(&last, kMaxSlots * (size_t)N);
+  tmp1.reserve(&scan_tmp1, 2 * ((size_t)N / kScanTile + 2));
   if (!tmp1.commit(false)) {
     set_error("fold_schedule_typed: out of device memory (temporaries)");
     return fail(FOLD_E_NOMEM);
@@ -1713,9 +1717,7 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   unsigned long long* err = &em->err;
   int* meta = em->meta;
   hipLaunchKernelGGL(k_init_meta, dim3(1), dim3(64), 0, st, em, 8 + kMaxTypes, nullptr, 0);
-  // pass counts of values past the last one stay 0, so the scan over the largest possible value count
-  // yields the exact total
-  hipLaunchKernelGGL(k_fill_ints, grid_for(std::min<long long>(Vmax, 1 << 20)), dim3(kBlock), 0, st, npass, Vmax, 0);
+  int *nout_v = counts, *npass = counts + N, *val_ptr = offsets, *node_pass = offsets + N;
   hipLaunchKernelGGL(k_check_struct, grid_for(std::max(G + 1, N + 1)), dim3(kBlock), 0, st, b->graph_ptr, G,
                      b->in_ptr, N, E, err);
   if (N > 0) {
@@ -1729,13 +1731,11 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
       hipLaunchKernelGGL(k_graph_depth<false>, dim3(G), dim3(kGraphThreads), lds, st, ga, OpTable{}, lds);
     }
     hipLaunchKernelGGL(k_typed_nodes, grid_for(N), dim3(kBlock), 0, st, kdepth, b->node_op, N, ops, depth, nout_v,
-                       meta, err);
-    scan_exclusive(nout_v, val_ptr, N, meta + 2, scan_tmp1, st);
-    hipLaunchKernelGGL(k_typed_last_init, grid_for(N), dim3(kBlock), 0, st, depth, nout_v, val_ptr, N, last, err);
-    hipLaunchKernelGGL(k_typed_last, grid_for(N), dim3(kBlock), 0, st, depth, b->in_ptr, b->in_node, b->in_slot,
-                       val_ptr, N, last, err);
-    hipLaunchKernelGGL(k_typed_npass, grid_for(N), dim3(kBlock), 0, st, depth, nout_v, val_ptr, last, N, npass, err);
-    scan_exclusive(npass, pass_ptr, (int)Vmax, meta + 3, scan_tmp1, st);
+                       last, meta, err);
+    hipLaunchKernelGGL(k_typed_last, grid_for(N), dim3(kBlock), 0, st, depth, b->in_ptr, b->in_node, b->in_slot, N,
+                       last, err);
+    hipLaunchKernelGGL(k_typed_npass, grid_for(N), dim3(kBlock), 0, st, depth, nout_v, last, N, npass, err);
+    scan_exclusive(counts, offsets, N, 2, meta + 2, scan_tmp1, st);
   }
   if (hipGetLastError() != hipSuccess) return device_error("kernel launch failed");
   // first synchronisation: the error word, the depth, and the sizes of phase 2
@@ -1796,11 +1796,10 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   Temp tmp2(st, device);
   unsigned *ka = nullptr, *kb = nullptr;
   int *va = nullptr, *vb = nullptr, *flag = nullptr, *exs = nullptr, *sort_counts = nullptr, *scan_tmp = nullptr;
-  int *bidx = nullptr, *gcount = nullptr, *cnt = nullptr, *cscan = nullptr, *dspan = nullptr, *vidx = nullptr,
+  int *bidx = nullptr, *pass_ptr = nullptr, *cnt = nullptr, *cscan = nullptr, *dspan = nullptr, *vidx = nullptr,
       *pidx = nullptr;
   constexpr int kCap = 4096;  // batches and state sizes read back with the final error word
   static_assert(kHdr + 5 * (size_t)kCap <= kStageInts, "the read-back buffer");
-  const long long scan_n = std::max<long long>(NI, (long long)T * Mc);
   tmp2.reserve(&ka, std::max(NI, 1));
   tmp2.reserve(&kb, std::max(NI, 1));
   tmp2.reserve(&va, std::max(NI, 1));
@@ -1808,14 +1807,16 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   tmp2.reserve(&flag, std::max(NI, 1));
   tmp2.reserve(&exs, std::max(NI, 1));
   tmp2.reserve(&sort_counts, (size_t)(B + 1) * kDigits);
-  tmp2.reserve(&scan_tmp, (size_t)(scan_n / kScanTile + 2));
+  tmp2.reserve(&scan_tmp, (size_t)(T + 1) * (Mc / kScanTile + 2));
   tmp2.reserve(&bidx, Mc);
-  tmp2.reserve(&gcount, Mc);
-  tmp2.reserve(&cnt, (size_t)T * Mc);
-  tmp2.reserve(&cscan, (size_t)T * Mc);
+  tmp2.reserve(&pass_ptr, std::max(V, 1));
+  tmp2.reserve(&cnt, (size_t)(T + 1) * Mc);
+  tmp2.reserve(&cscan, (size_t)(T + 1) * Mc);
   tmp2.reserve(&dspan, 2 * (size_t)(D + 1));
   tmp2.reserve(&vidx, std::max(V, 1));
   tmp2.reserve(&pidx, std::max(P, 1));
+  int* totals = nullptr;  // of the scans, unused
+  tmp2.reserve(&totals, T + 1);
   if (!tmp2.commit(true)) {
     set_error("fold_schedule_typed: out of device memory (temporaries)");
     return fail(FOLD_E_NOMEM);
@@ -1825,37 +1826,32 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   const int KT = K + T;
   if (N > 0) {
     if (P > 0)
-      hipLaunchKernelGGL(k_typed_pass_emit, grid_for(N), dim3(kBlock), 0, st, depth, nout_v, val_ptr, npass, pass_ptr,
-                         N, s.pass_node, s.pass_slot, s.pass_depth);
+      hipLaunchKernelGGL(k_typed_pass_emit, grid_for(N), dim3(kBlock), 0, st, depth, nout_v, val_ptr, last, node_pass, N,
+                         pass_ptr, s.pass_node, s.pass_slot, s.pass_depth);
     const unsigned sent = (unsigned)(D * KT);
     hipLaunchKernelGGL(k_typed_keys, grid_for(NI), dim3(kBlock), 0, st, depth, b->node_op, N, s.pass_node,
                        s.pass_slot, s.pass_depth, P, ops, sent, ka, va);
-    const int passes = sort_passes(sent);
+    const int passes = sort_passes(sent + T - 1);
     for (int ps = 0; ps < passes; ++ps) {
       sort_pass<PairKeys<unsigned>>({ka, va}, {NI, nullptr}, kDigitBits * ps, sort_counts, kb, vb, {err, nullptr, 0, 0},
                                     err, &em->cycle, st);
       std::swap(ka, kb);
       std::swap(va, vb);
     }
+    hipLaunchKernelGGL(k_typed_items, grid_for(NI), dim3(kBlock), 0, st, ka, va, M, NI, N, sent, meta, val_ptr,
+                       s.item_node, flag, vidx);
     if (M > 0) {
-      hipLaunchKernelGGL(k_typed_items, grid_for(M), dim3(kBlock), 0, st, ka, va, M, N, s.item_node, flag);
-      scan_exclusive(flag, exs, M, meta + 4, scan_tmp, st);
+      scan_exclusive(flag, exs, M, 1, meta + 4, scan_tmp, st);
       hipLaunchKernelGGL(k_typed_batches, grid_for(M), dim3(kBlock), 0, st, ka, flag, exs, M, KT, bidx,
                          s.batch_begin, s.batch_depth, s.batch_op);
       hipLaunchKernelGGL(k_typed_batch_sizes, grid_for(M), dim3(kBlock), 0, st, meta + 4, M, s.batch_begin,
-                         s.batch_op, ops, s.batch_rows, gcount, cnt);
-      scan_exclusive(gcount, s.batch_goff, M, meta + 5, scan_tmp, st);
-      for (int t = 0; t < T; ++t)
-        scan_exclusive(cnt + (size_t)t * M, cscan + (size_t)t * M, M, meta + 7, scan_tmp, st);
-      hipLaunchKernelGGL(k_typed_depth_span, grid_for(M), dim3(kBlock), 0, st, meta + 4, s.batch_depth, dfirst, dlast);
+                         s.batch_op, ops, s.batch_rows, cnt);
+      scan_exclusive(cnt, cscan, M, T + 1, totals, scan_tmp, st);
+      hipLaunchKernelGGL(k_typed_depth_span, grid_for(M), dim3(kBlock), 0, st, meta + 4, s.batch_depth,
+                         cscan + (size_t)T * M, dfirst, dlast, s.batch_goff);
     }
     hipLaunchKernelGGL(k_typed_state_size, grid_for((long long)nsize), dim3(kBlock), 0, st, D, std::max(M, 1), T,
                        dfirst, dlast, cnt, cscan, meta, s.state_size);
-    for (int t = 0; t < T; ++t) {
-      hipLaunchKernelGGL(k_typed_const_flag, grid_for(N), dim3(kBlock), 0, st, b->node_op, N, t, flag);
-      scan_exclusive(flag, exs, N, meta + 7, scan_tmp, st);
-      hipLaunchKernelGGL(k_typed_const_idx, grid_for(N), dim3(kBlock), 0, st, flag, exs, val_ptr, N, vidx);
-    }
     if (M > 0) {
       hipLaunchKernelGGL(k_typed_out_idx, grid_for(M), dim3(kBlock), 0, st, s.item_node, bidx, s.batch_begin,
                          s.batch_depth, s.batch_op, s.batch_rows, dfirst, cscan, M, val_ptr, ops, vidx, pidx);
@@ -1866,7 +1862,7 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
     }
   }
   // batches <= items; read back the batch table and the state sizes up to kCap entries each
-  hipLaunchKernelGGL(k_typed_compact, dim3(1), dim3(kBlock), 0, st, err, meta, s.batch_depth, s.batch_op,
+  hipLaunchKernelGGL(k_typed_finish, dim3(16), dim3(kBlock), 0, st, err, meta, s.batch_depth, s.batch_op,
                      s.batch_rows, s.batch_goff, s.state_size, M, (int)nsize, kCap, tmp2.stage);
   if (hipGetLastError() != hipSuccess) return device_error("kernel launch failed");
   if (hipStreamSynchronize(st) != hipSuccess) return device_error("device error while scheduling");
