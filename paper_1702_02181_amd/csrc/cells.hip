@@ -27,6 +27,7 @@
 #include "internal.h"
 #include "dma.h"
 #include "mfma.h"
+#include "narrow.h"
 #include "wide.h"
 
 namespace fold {
@@ -502,6 +503,106 @@ __global__ void k_cell_epi(FwdArgs a, int nsplit) {
   cell_epi_body<T, KIND>(a, blockIdx.x, nsplit);
 }
 
+// ---------------------------------------------------------------- forward, narrow levels
+// 16 RT rows x U hidden units (all gates) per workgroup of 8 waves, K split over the waves (see narrow.h).  A column
+// tile holds 16 / U gates of U units.
+
+template <typename T, int KIND, int RT, int U>
+struct NarrowFwd {
+  static constexpr int G = Gates<KIND>::G, GT = 16 / U, CT = (G + GT - 1) / GT;  // gates a tile, column tiles
+  // steps in flight: what fits 256 registers beside the sums
+  static constexpr int PD = (CT >= 4 ? 4 : 5) - RT;
+  static constexpr int kLds = narrow::kWaves * RT * CT * 64;  // 16-byte units
+  static constexpr int NS = KIND == kTreeLstmLeaf || KIND == FOLD_PROJ ? 1 : (KIND == FOLD_LSTM ? 2 : 3);
+};
+
+template <typename T, int KIND, int RT, int U>
+__device__ __forceinline__ void cell_fwd_narrow(const FwdArgs a, unsigned L, f32x4* red) {
+  using P = NarrowFwd<T, KIND, RT, U>;
+  constexpr int G = P::G, GT = P::GT, CT = P::CT, NS = P::NS;
+  constexpr int es = sizeof(T);
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), l16 = lane & 15;
+  const int R = (a.rows + 16 * RT - 1) / (16 * RT), UB = a.HP / U;
+  int rt0, ub;
+  if (!xcd_tile_at(L, R, UB, rt0, ub)) return;
+  const int m0 = rt0 * 16 * RT;
+  const char* zero = static_cast<const char*>(a.zero) + (lane >> 4) * 16;
+  // this lane's row of every row tile in each segment of K: the input, child 0, child 1 (the absent ones are empty)
+  const char* row_at[NS][RT];
+  constexpr int kIn = KIND == kTreeLstmLeaf ? 0 : (KIND == FOLD_PROJ ? -1 : 0);  // slot of the input segment
+  constexpr int kKid = kIn + 1;                                                  // ... of child 0
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    const int row = m0 + rt * 16 + l16;
+#pragma unroll
+    for (int g = 0; g < NS; ++g) {
+      int sr = -1;
+      if (row < a.rows) {
+        if (g == kIn) sr = a.has_input ? a.input_idx[a.row_begin + row] : -1;
+        else sr = g - kKid < a.arity ? fwd_child(a, row, g - kKid) : -1;
+      }
+      const char* base = static_cast<const char*>(g == kIn ? a.table : a.h_pool);
+      row_at[g][rt] = sr >= 0 ? base + (size_t)sr * (g == kIn ? a.tld : a.ld) * es + (lane >> 4) * 16 : nullptr;
+    }
+  }
+  // weights: rows of K bytes by (32 units, gate, unit)
+  const size_t krow = (size_t)a.Kf * es;
+  const char* wbase = static_cast<const char*>(a.Wf) + (size_t)((ub * U) >> 5) * (G * 32) * krow +
+                      (size_t)((ub * U) & 31) * krow + (a.has_input ? 0 : (size_t)a.INP * es);
+  const size_t wtile = GT * 32 * krow;
+  const unsigned piece = (lane >> 4) * 16, wunit = (unsigned)((l16 % U) * krow) + piece;
+  const unsigned wlane = wunit + (unsigned)((l16 / U) * 32 * krow);
+  const unsigned wlast = wunit + (unsigned)(min(l16 / U, G - 1 - (CT - 1) * GT) * 32 * krow);  // no gate past the last
+  // the cell states of the children of the outputs this thread finishes are loaded while the contraction's first
+  // operands are on their way
+  constexpr int NK = CKids<KIND>::N;
+  const int u = tid % U, j = ub * U + u, orow = tid / U;
+  const int row = m0 + orow;
+  const bool mine = tid < RT * 16 * U && row < a.rows;
+  float cc[NK > 0 ? NK : 1], bz[G];
+  auto ahead = [&]() {
+#pragma unroll
+    for (int k = 0; k < (NK > 0 ? NK : 1); ++k) {
+      const int q = NK > 0 && mine && k < a.arity ? fwd_child(a, row, k) : -1;
+      cc[k] = q >= 0 ? a.c_pool[(size_t)q * a.ld + j] : 0.f;
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) bz[g] = a.bias[g * a.HP + j];
+  };
+  const int e0 = kIn < 0 ? 0 : (a.has_input ? a.INP * es / 128 : 0), pc = a.HP * es / 128;
+  const int e1 = e0 + (a.arity > 0 ? pc : 0), np = e0 + a.arity * pc;
+  auto arow = [&](int q, int rt) -> const char* {
+    // values, not a choice between array elements: that would keep the array in memory
+    const char *p0 = row_at[0][rt], *p1 = row_at[NS > 1 ? 1 : 0][rt], *p2 = row_at[NS - 1][rt];
+    const char* p = NS == 1 || q < e0 ? p0 : (NS == 2 || q < e1 ? p1 : p2);
+    const int at = NS == 1 || q < e0 ? q : (NS == 2 || q < e1 ? q - e0 : q - e1);
+    return p ? p + at * 128 : zero;
+  };
+  // one lane offset serves every column tile: the tiles' distances are the same for all lanes
+  auto bcol = [&](int q, int ct) -> const char* {
+    return wbase + (size_t)ct * wtile + q * 128 + (ct == CT - 1 ? wlast : wlane);
+  };
+  f32x4 acc[RT][CT];
+  narrow::contract<T, RT, CT, P::PD>(np, wave, zero, arow, bcol, ahead, acc);
+  narrow::reduce<RT, CT>(acc, red, wave, lane);
+  if (!mine) return;
+  if (j >= a.H) {
+    if (j < a.ld) pad_out<T>(a, row, j);
+    return;
+  }
+  const float* sums = reinterpret_cast<const float*>(red) + (orow >> 4) * CT * 256;
+  float z[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) z[g] = sums[g / GT * 256 + narrow::float_of(orow & 15, (g % GT) * U + u)] + bz[g];
+  cell_out<T, KIND>(a, row, j, z, cc[0], NK > 1 ? cc[NK > 1 ? 1 : 0] : 0.f);
+}
+
+template <typename T, int KIND, int RT, int U>
+__global__ __launch_bounds__(narrow::kThreads) void k_cell_fwd_n(FwdArgs a) {
+  __shared__ f32x4 red[NarrowFwd<T, KIND, RT, U>::kLds];
+  cell_fwd_narrow<T, KIND, RT, U>(a, blockIdx.x, red);
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void k_embed_fwd(int rows, int row_begin, int H, int ld, int tld, const T* table,
                                                    const int* input_idx, T* h_pool, float* c_pool) {
@@ -964,6 +1065,23 @@ __global__ __launch_bounds__(kThreads) void k_level_fwd(Merged<FwdArgs> m) {
   }
 }
 
+// the same on narrow tiles (variant = kind): the groups' cells finish in the launch
+template <typename T, int RT, int U>
+__global__ __launch_bounds__(narrow::kThreads) void k_level_fwd_n(Merged<FwdArgs> m) {
+  __shared__ f32x4 red[NarrowFwd<T, FOLD_TREELSTM, RT, U>::kLds];
+  const int i = merged_part(m.begin, m.n, blockIdx.x);
+  const unsigned bid = blockIdx.x - (unsigned)m.begin[i];
+  const FwdArgs a = m.a[i];
+  switch (m.variant[i]) {
+    case FOLD_TREERNN: cell_fwd_narrow<T, FOLD_TREERNN, RT, U>(a, bid, red); break;
+    case FOLD_TREELSTM: cell_fwd_narrow<T, FOLD_TREELSTM, RT, U>(a, bid, red); break;
+    case FOLD_LSTM: cell_fwd_narrow<T, FOLD_LSTM, RT, U>(a, bid, red); break;
+    case FOLD_PROJ: cell_fwd_narrow<T, FOLD_PROJ, RT, U>(a, bid, red); break;
+    case kTreeLstmLeaf: cell_fwd_narrow<T, kTreeLstmLeaf, RT, U>(a, bid, red); break;
+    default: break;
+  }
+}
+
 // K-split epilogues of a level: one workgroup per row, parts in rows; variant = kind
 template <typename T>
 __global__ void k_level_epi(Merged<FwdArgs> m) {
@@ -1030,6 +1148,9 @@ __global__ __launch_bounds__(kThreads) void k_level_dx(Merged<DxArgs> m) {
   }
 }
 
+inline int fwd_k(const FwdArgs& a) { return (a.has_input ? a.INP : 0) + a.arity * a.HP; }
+inline int narrow_grid(int rows, int HP, const NarrowPlan& n) { return xcd_grid(cdiv(rows, 16 * n.rt), HP / n.units); }
+
 template <typename T, int KIND>
 void cell_fwd_kind(const FwdArgs& a0, hipStream_t st) {
   const FwdPlan pl = fwd_plan(a0.rows, a0.HP, a0.has_input ? a0.INP : 0, a0.arity, sizeof(T), a0.zpart != nullptr,
@@ -1041,6 +1162,17 @@ void cell_fwd_kind(const FwdArgs& a0, hipStream_t st) {
     a.map = NU % 8 == 0 ? kMapOwnCols : kMapRows;
     dim3 grid(a.map == kMapOwnCols ? xcd_cols_grid(NU, R) : xcd_grid(NU, R));
     hipLaunchKernelGGL((k_cell_fwd_w<T, KIND>), grid, dim3(wide::kThreads), 0, st, a);
+    return;
+  }
+  if (const NarrowPlan n = narrow_fwd_plan(a.rows, a.HP, fwd_k(a), sizeof(T)); n.rt) {
+    const dim3 grid(narrow_grid(a.rows, a.HP, n)), block(narrow::kThreads);
+#define FOLD_N(RT_, U_) hipLaunchKernelGGL((k_cell_fwd_n<T, KIND, RT_, U_>), grid, block, 0, st, a)
+    if (n.rt == 1) {
+      if (n.units == 4) FOLD_N(1, 4); else if (n.units == 8) FOLD_N(1, 8); else FOLD_N(1, 16);
+    } else {
+      if (n.units == 4) FOLD_N(2, 4); else if (n.units == 8) FOLD_N(2, 8); else FOLD_N(2, 16);
+    }
+#undef FOLD_N
     return;
   }
   a.ksplit = pl.ksplit;
@@ -1328,7 +1460,63 @@ void launch_bwd_dx(int dtype, const DxArgs& a0, hipStream_t st, const char* name
 
 constexpr long long kLevelFwdWorkgroups = 256;  // the K-split forward of a level launch aims at this grid
 
+// Whether a level runs on narrow tiles: every group would alone, and together they give at most kLevelNarrow workgroups
+// of 32 rows x 16 units (bf16 H = 512, two or three groups a level, us with 5 us event overhead, 128-row tiles and
+// epilogues / narrow: 45 rows 16.5 / 12.4, 183 rows 19.4 / 14.3, 380 rows (416 workgroups) 22.7 / 22.0, 788 rows 28.2 /
+// 36.3).  A level of at most 128 rows always does, so that a group's arithmetic is the same with and without the others.
+constexpr int kLevelNarrow = 400;
+static bool level_is_narrow(const FwdArgs* args, int n, int esize) {
+  int tiles = 0, rows = 0, HP = 0;
+  for (int k = 0; k < n; ++k) {
+    const FwdArgs& a = args[k];
+    if (a.rows <= 0) continue;
+    if (!narrow_fwd_plan(a.rows, a.HP, fwd_k(a), esize).rt) return false;
+    tiles += (int)cdiv(a.rows, 32);
+    rows += a.rows;
+    HP = a.HP;
+  }
+  return rows > 0 && (tiles * (HP / 16) <= kLevelNarrow || rows <= 128);
+}
+
+// ... as one launch, with one tile for all its groups
+static void launch_level_fwd_n(int dtype, const int* kinds, const FwdArgs* args, int n, hipStream_t st) {
+  Merged<FwdArgs> m{};
+  NarrowPlan plan;
+  int most = 0, total = 0, tiles = 0, HP = 0;
+  for (int k = 0; k < n; ++k) most = std::max(most, args[k].rows);
+  plan.rt = most <= 48 ? 1 : 2;
+  for (int k = 0; k < n; ++k) {
+    tiles += (int)cdiv(std::max(args[k].rows, 0), 16 * plan.rt);
+    HP = args[k].HP;
+  }
+  plan.units = tiles * (HP / 4) <= kNarrowRound ? 4 : (tiles * (HP / 8) <= kNarrowRound ? 8 : 16);
+  for (int k = 0; k < n; ++k) {
+    if (args[k].rows <= 0) continue;
+    m.begin[m.n] = total;
+    m.variant[m.n] = kinds[k];
+    m.a[m.n++] = args[k];
+    total += narrow_grid(args[k].rows, HP, plan);
+  }
+  m.begin[m.n] = total;
+  const dim3 grid(total), block(narrow::kThreads);
+#define FOLD_LN(T_, RT_, U_) hipLaunchKernelGGL((k_level_fwd_n<T_, RT_, U_>), grid, block, 0, st, m)
+#define FOLD_LNU(T_, RT_) \
+  if (plan.units == 4) FOLD_LN(T_, RT_, 4); else if (plan.units == 8) FOLD_LN(T_, RT_, 8); else FOLD_LN(T_, RT_, 16);
+  if (dtype == FOLD_BF16) {
+    if (plan.rt == 1) { FOLD_LNU(uint16_t, 1) } else { FOLD_LNU(uint16_t, 2) }
+  } else {
+    if (plan.rt == 1) { FOLD_LNU(float, 1) } else { FOLD_LNU(float, 2) }
+  }
+#undef FOLD_LNU
+#undef FOLD_LN
+}
+
 void launch_level_fwd(int dtype, const int* kinds, const FwdArgs* args, int n, hipStream_t st) {
+  ProfScope prof(dtype == FOLD_BF16 ? "cell_fwd.level.bf16" : "cell_fwd.level.f32", st);
+  if (level_is_narrow(args, n, dtype == FOLD_BF16 ? 2 : 4)) {
+    launch_level_fwd_n(dtype, kinds, args, n, st);
+    return;
+  }
   Merged<FwdArgs> m{};
   Merged<FwdArgs> e{};  // the K-split parts' epilogues
   m.n = 0;
@@ -1377,7 +1565,6 @@ void launch_level_fwd(int dtype, const int* kinds, const FwdArgs* args, int n, h
   if (m.n == 0) return;
   m.begin[m.n] = total;
   e.begin[e.n] = erows;
-  ProfScope prof(dtype == FOLD_BF16 ? "cell_fwd.level.bf16" : "cell_fwd.level.f32", st);
   if (dtype == FOLD_BF16) {
     hipLaunchKernelGGL(k_level_fwd<uint16_t>, dim3(total), dim3(kThreads), 0, st, m);
     if (e.n) hipLaunchKernelGGL(k_level_epi<uint16_t>, dim3(erows), dim3(std::min(hp, 1024)), 0, st, e);

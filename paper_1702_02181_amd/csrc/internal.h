@@ -106,6 +106,33 @@ struct FwdPlan {
   int ksplit = 1;
   bool wide = false;  // 256 rows x 2 unit blocks per workgroup of 8 waves
 };
+// A narrow group's forward on 16-row tiles (narrow.h): rt row tiles of 16 and `units` hidden units per workgroup, which
+// contracts all of K; rt = 0: not narrow.
+struct NarrowPlan {
+  int rt = 0, units = 0;
+};
+// The line: all workgroups run in one round, one to a compute unit, at most 512 rows.  Within it the latency of one launch
+// replaces that of two; past it the operands are read again for every 16 or 32 rows and the 128-row tiles win (us per
+// Tree-LSTM level, 128-row tiles / narrow, event overhead of 5 us in both: bf16 H = 300 1 row 11.9 / 8.3, 64 rows 13.8 /
+// 9.9; H = 512 256 rows 22.0 / 14.4, 512 rows 22.3 / 24.7; H = 768 128 rows 19.7 / 17.7, 192 rows 20.6 / 30.5; fp32 H = 256
+// 64 rows 16.6 / 11.7, 512 rows 23.4 / 21.0; H = 1,024 1 row 34.0 / 16.1, 64 rows 36.2 / 34.5).  fp32 multiplies a quarter of
+// the bf16 K a cycle, so past 64 rows only a short K stays bound by latency (H = 512: 128 rows 25.1 / 26.9).  bf16 takes
+// single row tiles up to 48 rows (H = 300, 48 rows: 9.1 against 9.7 us; 64 rows: 13.5 against 9.9), fp32 wherever they
+// still fit the round (H = 256, 64 rows: 11.7 against 13.7).  Fewer units a workgroup while all still fit it: more
+// compute units share the weights (fp32 H = 1,024, 1 row: 8 units 20.9, 4 units 16.1).
+constexpr int kNarrowRows = 512, kNarrowRound = 256;
+inline NarrowPlan narrow_fwd_plan(int rows, int HP, int K, int esize) {
+  NarrowPlan p;
+  if (rows <= 0 || rows > kNarrowRows || (esize == 4 && K > 512 && rows > 64)) return p;
+  const int t1 = (rows + 15) / 16, t2 = (rows + 31) / 32;
+  const bool single = esize == 4 ? t1 * (HP / 16) <= kNarrowRound : rows <= 48;
+  const int tiles = single ? t1 : t2;
+  if (tiles * (HP / 16) > kNarrowRound) return p;
+  p.rt = single ? 1 : 2;
+  p.units = tiles * (HP / 4) <= kNarrowRound ? 4 : (tiles * (HP / 8) <= kNarrowRound ? 8 : 16);
+  return p;
+}
+
 // alone: the group launches by itself (not in a level launch, whose groups' splits are cut together)
 inline FwdPlan fwd_plan(int rows, int HP, int inp_used, int arity, int esize, bool can_split, bool alone = false) {
   const int BK = esize == 4 ? 32 : 64;
