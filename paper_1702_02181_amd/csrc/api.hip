@@ -569,6 +569,19 @@ int32_t backward_impl(const Sched& s, const Packed& p, const void* table, int64_
     std::vector<int> dgroup;
     std::vector<AttnArgs> attn;
     std::vector<int> attn_kind, attn_group;
+    // The level's dz . W^T on narrow tiles, if all its groups together fit them (known before the cell backwards: K
+    // slices of the other tiles need the children's dh zeroed there)
+    NarrowDxPlan narrow;
+    const int merge = g_level_launches.load(std::memory_order_relaxed) ? kMaxMerge : 1;
+    {
+      std::vector<DxGroup> dx;
+      for (int g = g_lo; g < g_hi; ++g) {
+        const fold_op& op = s.ops[s.h_op[g]];
+        if (op.arity > 0 && !is_attn(op.kind))
+          dx.push_back({s.h_rows[g], op.arity * p.HP, p.sets[op.param_set].G * p.HP});
+      }
+      if ((int)dx.size() <= kMaxMerge) narrow = narrow_dx_plan(dx.data(), (int)dx.size(), esize);
+    }
     for (int g = g_lo; g < g_hi; ++g) {
       const fold_op& op = s.ops[s.h_op[g]];
       const PackedSet& ps = p.sets[op.param_set];
@@ -609,10 +622,11 @@ int32_t backward_impl(const Sched& s, const Packed& p, const void* table, int64_
       const bool leaf = is_tree_lstm_leaf(op);
       const int Kb = (leaf ? gates_of(kTreeLstmLeaf) : ps.G) * p.HP;
       // a dz . W^T whose K slices add into the children atomically needs their dh rows zeroed first
-      b.zero_child_dh = dh_fresh && op.arity > 0 && dx_plan(b.rows, op.arity * p.HP, Kb, esize, true).ksplit > 1;
+      b.zero_child_dh = dh_fresh && op.arity > 0 && !narrow.rt && dx_plan(b.rows, op.arity * p.HP, Kb, esize, true).ksplit > 1;
       ckind.push_back(leaf ? kTreeLstmLeaf : op.kind);
       cargs.push_back(b);
       DxArgs d;
+      d.narrow = narrow;
       d.rows = b.rows;
       d.row_begin = b.row_begin;
       d.idx_off = b.idx_off;
@@ -646,7 +660,6 @@ int32_t backward_impl(const Sched& s, const Packed& p, const void* table, int64_
       launch_attn_bwd(p.dtype, attn_kind[k], attn[k], st);
     }
     // cell backwards: the level's groups in chunks of at most kMaxMerge
-    const int merge = g_level_launches.load(std::memory_order_relaxed) ? kMaxMerge : 1;
     for (int k0 = 0; k0 < (int)cargs.size(); k0 += merge) {
       const int n = std::min<int>(merge, (int)cargs.size() - k0);
       if (n == 1) {
@@ -661,7 +674,7 @@ int32_t backward_impl(const Sched& s, const Packed& p, const void* table, int64_
     std::vector<DxArgs> nargs;
     std::vector<int> ngroup;
     for (size_t k = 0; k < dargs.size(); ++k) {
-      if (bwd_dx_is_narrow(p.dtype, dargs[k])) {
+      if (narrow.rt || bwd_dx_is_narrow(p.dtype, dargs[k])) {
         nargs.push_back(dargs[k]);
         ngroup.push_back(dgroup[k]);
       } else {

@@ -914,6 +914,71 @@ __global__ __launch_bounds__(kThreads) void k_bwd_dx2(DxArgs a) {
   bwd_dx2_body<T, MT, SPLIT>(a, blockIdx.x, A0, A1, B0, B1, tgt, sgl);
 }
 
+// dz . W^T on narrow levels: 16 RT rows x 16 CT columns per workgroup of 8 waves, all of K split over the waves (see
+// narrow.h): the sums are stored or added once, without K slices adding into rows zeroed before.
+template <int RT, int CT>
+struct NarrowDx {
+  static constexpr int PD = 7 - RT - CT;                      // steps in flight
+  static constexpr int kLds = narrow::kWaves * RT * CT * 64;  // 16-byte units
+};
+
+template <typename T, int RT, int CT>
+__device__ __forceinline__ void bwd_dx_narrow(const DxArgs a, unsigned L, f32x4* red) {
+  constexpr int es = sizeof(T), BM = 16 * RT, BN = 16 * CT;
+  constexpr int NI = (BM * BN + narrow::kThreads - 1) / narrow::kThreads;  // outputs a thread
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), l16 = lane & 15;
+  const int R = (a.rows + BM - 1) / BM, NT = a.Nb / BN;
+  int rt0, nt;
+  if (!xcd_tile_at(L, R, NT, rt0, nt)) return;
+  const int m0 = rt0 * BM, n0 = nt * BN;
+  const char* zero = static_cast<const char*>(a.zero) + (lane >> 4) * 16;
+  auto arow = [&](int q, int rt) -> const char* {
+    const int row = m0 + rt * 16 + l16;
+    return row < a.rows ? reinterpret_cast<const char*>(a.dz + (size_t)(a.row_begin + row) * a.gstride) +
+                              (lane >> 4) * 16 + q * 128
+                        : zero;
+  };
+  const size_t krow = (size_t)a.Kb * es;
+  const char* wbase = static_cast<const char*>(a.Wb) + (size_t)n0 * krow;
+  const unsigned wlane = (unsigned)(l16 * krow) + (lane >> 4) * 16;
+  auto bcol = [&](int q, int ct) -> const char* { return wbase + (size_t)ct * 16 * krow + q * 128 + wlane; };
+  // the targets of this thread's outputs, read while the contraction's first operands are on their way
+  const int k = n0 / a.HP;  // child slot: HP is a multiple of the columns of a workgroup
+  int tr[NI];
+  bool one[NI];
+  auto ahead = [&]() {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int row = m0 + (tid + i * narrow::kThreads) / BN;
+      const bool in = (tid + i * narrow::kThreads) < BM * BN && row < a.rows;
+      tr[i] = in ? a.child_pos[a.idx_off + row * a.arity + k] : -1;
+      one[i] = in && a.child_one[a.idx_off + row * a.arity + k] != 0;
+    }
+  };
+  f32x4 acc[RT][CT];
+  narrow::contract<T, RT, CT, NarrowDx<RT, CT>::PD>((int)(krow / 128), wave, zero, arow, bcol, ahead, acc);
+  narrow::reduce<RT, CT>(acc, red, wave, lane);
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    if (tr[i] < 0) continue;
+    const int at = tid + i * narrow::kThreads, r = at / BN, c = at % BN, jin = n0 + c - k * a.HP;
+    // pad columns (their products are 0) are stored only into rows that start undefined
+    const bool pad = jin >= a.H;
+    if (pad && !(a.dh_fresh && one[i])) continue;
+    const float v = reinterpret_cast<const float*>(red)[((r >> 4) * CT + (c >> 4)) * 256 +
+                                                         narrow::float_of(r & 15, c & 15)];
+    float* dst = &a.dh[(size_t)tr[i] * a.ld + jin];
+    if (one[i]) *dst = a.dh_fresh ? v : *dst + v;
+    else unsafeAtomicAdd(dst, v);
+  }
+}
+
+template <typename T, int RT, int CT>
+__global__ __launch_bounds__(narrow::kThreads) void k_bwd_dx_n(DxArgs a) {
+  __shared__ f32x4 red[NarrowDx<RT, CT>::kLds];
+  bwd_dx_narrow<T, RT, CT>(a, blockIdx.x, red);
+}
+
 // dz . W^T on wide levels: 256 rows x 256 columns per workgroup of 8 waves (each 64 x 128), 64-byte K
 // stages, three in flight (see wide.h).  Waves 0-3 issue the loads: 4 instructions of dz rows and 4 of
 // W^T rows each.  With gridDim.y = ksplit > 1 workgroup (x, y) takes the y-th slice of the K stages and
@@ -1112,6 +1177,15 @@ __global__ void k_level_cbwd(Merged<BwdCellArgs> m) {
     case kTreeLstmLeaf: cell_bwd_body<kTreeLstmLeaf, BF>(a, row); break;
     default: break;
   }
+}
+
+// dz . W^T of a level on narrow tiles
+template <typename T, int RT, int CT>
+__global__ __launch_bounds__(narrow::kThreads) void k_level_dx_n(Merged<DxArgs> m) {
+  __shared__ f32x4 red[NarrowDx<RT, CT>::kLds];
+  const int i = merged_part(m.begin, m.n, blockIdx.x);
+  const DxArgs a = m.a[i];
+  bwd_dx_narrow<T, RT, CT>(a, blockIdx.x - (unsigned)m.begin[i], red);
 }
 
 // dz . W^T of a level; variant = 2 * mt + (K split), mt <= MTMAX (the LDS is sized for MTMAX)
@@ -1422,11 +1496,42 @@ void launch_tok_table(const int* tok_rows, const int* tok_seg, const int* tok_st
                      tok_row, i0, count, per, 0, dh, ld, 0, H, tld, d_table);
 }
 
+// one group, or the groups of a level, on narrow tiles
+static void launch_dx_n(int dtype, const DxArgs* args, int n, const NarrowDxPlan& pl, hipStream_t st) {
+  Merged<DxArgs> m{};
+  int total = 0;
+  for (int k = 0; k < n; ++k) {
+    if (args[k].rows <= 0 || args[k].Nb <= 0) continue;
+    m.begin[m.n] = total;
+    m.a[m.n++] = args[k];
+    total += xcd_grid(cdiv(args[k].rows, 16 * pl.rt), args[k].Nb / (16 * pl.ct));
+  }
+  if (m.n == 0) return;
+  m.begin[m.n] = total;
+  const dim3 grid(total), block(narrow::kThreads);
+#define FOLD_DN(T_, RT_, CT_)                                                                       \
+  if (m.n == 1) hipLaunchKernelGGL((k_bwd_dx_n<T_, RT_, CT_>), grid, block, 0, st, m.a[0]);         \
+  else hipLaunchKernelGGL((k_level_dx_n<T_, RT_, CT_>), grid, block, 0, st, m);
+#define FOLD_DNC(T_, RT_) \
+  if (pl.ct == 1) { FOLD_DN(T_, RT_, 1) } else { FOLD_DN(T_, RT_, 2) }
+  if (dtype == FOLD_BF16) {
+    if (pl.rt == 1) { FOLD_DNC(uint16_t, 1) } else { FOLD_DNC(uint16_t, 2) }
+  } else {
+    if (pl.rt == 1) { FOLD_DNC(float, 1) } else { FOLD_DNC(float, 2) }
+  }
+#undef FOLD_DNC
+#undef FOLD_DN
+}
+
 void launch_bwd_dx(int dtype, const DxArgs& a0, hipStream_t st, const char* name) {
   if (a0.rows <= 0 || a0.Nb <= 0) return;
   DxArgs a = a0;
   ProfScope prof(name ? name : dtype == FOLD_BF16 ? "bwd_dx.bf16" : "bwd_dx.f32", st);
   const DxPlan pl = dx_plan(a.rows, a.Nb, a.Kb, dtype == FOLD_BF16 ? 2 : 4, a.can_split != 0);
+  if (a.narrow.rt) {
+    launch_dx_n(dtype, &a, 1, a.narrow, st);
+    return;
+  }
   if (pl.wide) {
     const int R = (int)cdiv(a.rows, wide::kRows), NT = (int)cdiv(a.Nb, 256);
     a.ksplit = pl.ksplit;
@@ -1603,6 +1708,11 @@ bool bwd_dx_is_narrow(int dtype, const DxArgs& a) {
 }
 
 void launch_level_dx(int dtype, const DxArgs* args, int n, hipStream_t st) {
+  if (n > 0 && args[0].narrow.rt) {  // the level's plan is the same in every group
+    ProfScope prof(dtype == FOLD_BF16 ? "bwd_dx.level.bf16" : "bwd_dx.level.f32", st);
+    launch_dx_n(dtype, args, n, args[0].narrow, st);
+    return;
+  }
   Merged<DxArgs> m{};
   m.n = 0;
   int total = 0, mtmax = 1;

@@ -237,7 +237,41 @@ void launch_level_cbwd(const int* kinds, const BwdCellArgs* args, int n, hipStre
 void launch_bwd_init(int N, int R, int ld, const float* dh_nodes, const float* dh_roots, const int* root_pos,
                      const int* pos_npar, float* dh, float* dc, hipStream_t st);
 
+// dz . W^T on 16-row tiles (narrow.h): rt row tiles and ct column tiles of 16 per workgroup; rt = 0: not narrow.  The
+// plan covers all groups of a level, which then run as one launch with one tile.
+struct NarrowDxPlan {
+  int rt = 0, ct = 0;
+};
+// The line: as in the forward, all workgroups in one round.  Single row tiles first; double ones reach further with
+// fp32, and with bf16 while K is short (us per Tree-LSTM level with 5 us event overhead, 128-row tiles / narrow: bf16
+// H = 300 1 row 11.6 / 7.2, 64 rows 13.4 / 8.4, 256 rows 13.6 / 11.6, 384 rows 13.8 / 18.4; H = 512 128 rows 15.6 / 13.3, 256
+// rows on double tiles 15.6 / 15.2; H = 1,024 32 rows 20.6 / 13.8, 64 rows 20.6 / 19.4, 128 rows 22.4 / 24.4; fp32 H = 256 1 row
+// 17.6 / 8.2, 512 rows 22.9 / 18.1; H = 512 1 row 27.6 / 11.3, 256 rows 31.6 / 26.9).  Two rounds lose (bf16 H = 512, 192 rows:
+// 15.6 / 21.9).
+struct DxGroup {
+  int rows, Nb, K;
+};
+inline NarrowDxPlan narrow_dx_plan(const DxGroup* g, int n, int esize) {
+  NarrowDxPlan p;
+  int most = 0, K = 0;
+  long long c1 = 0, c2 = 0;  // column tiles of 16 over all row tiles
+  for (int k = 0; k < n; ++k) {
+    most = std::max(most, g[k].rows);
+    K = std::max(K, g[k].K);
+    c1 += (long long)((g[k].rows + 15) / 16) * (g[k].Nb / 16);
+    c2 += (long long)((g[k].rows + 31) / 32) * (g[k].Nb / 16);
+  }
+  if (most <= 0 || most > (esize == 4 ? kNarrowRows : kNarrowRows / 2)) return p;
+  const bool single = c1 / 2 <= kNarrowRound;
+  const long long c = single ? c1 : c2;
+  if (!single && (c2 / 2 > kNarrowRound || (esize == 2 && K > 2048))) return p;
+  p.rt = single ? 1 : 2;
+  p.ct = c <= kNarrowRound ? 1 : 2;
+  return p;
+}
+
 struct DxArgs {
+  NarrowDxPlan narrow;
   int rows, row_begin, idx_off, arity;
   int H, HP, ld, gstride, Kb, Nb;
   const float* dz;
