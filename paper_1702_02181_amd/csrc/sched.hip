@@ -133,12 +133,23 @@ __global__ void k_node_graph(const int* gp, int* node_graph, const unsigned long
 // below it: the second child reads the first one's); otherwise a maximum and a count.
 constexpr int kGraphThreads = 128;
 
+// Parent edges of v, once all are linked; a single one is replaced by its parent's number.
+template <class L>
+__device__ __forceinline__ int close_node(const L& g, int v) {
+  int k = 0, p = 0;
+  unsigned nx;
+  for (unsigned j = g.get_head(v); j != L::kNone; j = nx) p = g.get_edge(j, nx), ++k;
+  if (k == 1) g.set_head(v, L::kSingle | (unsigned)p);
+  return k;
+}
+
 template <bool ARITY2>
 struct LdsLinks {
   static constexpr unsigned kNone = 0xffffu, kSingle = 0x80000000u;  // kNone has no kSingle bit
   static constexpr int kNodeBytes = ARITY2 ? 10 : 14, kEdgeBytes = 4;
   uint32_t *state, *depth, *head, *edge;
   uint16_t* list;
+  __device__ __forceinline__ LdsLinks() {}
   __device__ __forceinline__ LdsLinks(char* at, int n, int e) {
     state = reinterpret_cast<uint32_t*>(at);
     head = state + n;
@@ -169,6 +180,7 @@ struct LdsLinks {
     else depth[v] = (unsigned)d;
   }
   __device__ __forceinline__ int get_depth(int v) const { return (int)(ARITY2 ? state[v] : depth[v]); }
+  __device__ __forceinline__ int close(int v) const { return close_node(*this, v); }
   // a child one step below depth d reports to p; true when it was the last one, with p's depth
   __device__ __forceinline__ bool arrive(int p, int d, int& dp) const {
     if constexpr (ARITY2) {
@@ -251,6 +263,74 @@ struct GraphArgs {
   int num_inputs;
 };
 
+// The walk, from the leaves on the list: emit(v, depth) once for every node that it reaches; finished and deepest are
+// this thread's.  All links are in place (a barrier starts it).
+template <class L, class EMIT>
+__device__ __forceinline__ void walk_graph(const L& g, GraphShared& sh, const EMIT& emit, int& finished, int& deepest) {
+  const int t = threadIdx.x, T = blockDim.x;
+  finished = 0;
+  deepest = 0;
+  for (int lo = 0;;) {
+    __syncthreads();
+    const int hi = sh.tail;
+    __syncthreads();
+    if (lo == hi) break;
+    for (int i = lo + t; i < hi; i += T) {
+      int v = g.list[i], d = g.get_depth(v);
+      unsigned h = g.get_head(v);
+      while (true) {
+        emit(v, d);
+        ++finished;
+        int nv = -1, nd = 0;
+        unsigned nh = L::kNone;
+        if (h & L::kSingle) {  // the parent's own link is read along with the report: one LDS latency a step
+          const int p = (int)(h & ~L::kSingle);
+          nh = g.get_head(p);
+          if (g.arrive(p, d + 1, nd)) nv = p;
+        } else if (h != L::kNone) {
+          unsigned nx;
+          int p = g.get_edge(h, nx);
+          while (true) {  // the next edge is read along with the report
+            const bool more = nx != L::kNone;
+            unsigned nx2 = L::kNone;
+            const int p2 = more ? g.get_edge(nx, nx2) : 0;
+            int dp;
+            if (g.arrive(p, d + 1, dp)) {
+              int other = p, od = dp;
+              if (nv < 0 || p < nv) other = nv, od = nd, nv = p, nd = dp;
+              if (other >= 0) {
+                g.set_depth(other, od);
+                g.list[atomicAdd(&sh.tail, 1)] = other;
+              }
+            }
+            if (!more) break;
+            p = p2, nx = nx2;
+          }
+          if (nv >= 0) nh = g.get_head(nv);
+        }
+        if (nv < 0) break;
+        v = nv, d = nd, h = nh;
+      }
+      deepest = max(deepest, d);  // a chain's last node is its deepest
+    }
+    lo = hi;
+  }
+}
+
+// every thread's totals into sh
+__device__ __forceinline__ void graph_totals(GraphShared& sh, int finished, int deepest, int parents) {
+  for (int s = kWave / 2; s; s >>= 1) {
+    finished += __shfl_xor(finished, s);
+    deepest = max(deepest, __shfl_xor(deepest, s));
+    parents = max(parents, __shfl_xor(parents, s));
+  }
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+    atomicAdd(&sh.done, finished);
+    atomicMax(&sh.deepest, deepest);
+    atomicMax(&sh.parents, parents);
+  }
+}
+
 // Links the graph (nodes g0 .. g0 + n - 1, edges e0 .. e0 + e - 1) and, for a fold batch, checks every node first
 // (the lowest node with an error counts, and its first check).
 template <class L, bool CHECK>
@@ -298,71 +378,13 @@ __device__ __forceinline__ void run_graph(const L& g, const GraphArgs& a, const 
   if (sh.bad) return;
   int parents = 0;
   for (int v = t; v < n; v += T) {
-    int k = 0;
-    const unsigned h = g.get_head(v);
-    unsigned nx;
-    int p = 0;
-    for (unsigned j = h; j != L::kNone; j = nx) p = g.get_edge(j, nx), ++k;
-    if (k == 1) g.set_head(v, L::kSingle | (unsigned)p);
+    const int k = close_node(g, v);
     a.indeg[g0 + v] = k;
     parents = max(parents, k);
   }
-  int done = 0, deepest = 0;
-  for (int lo = 0;;) {
-    __syncthreads();
-    const int hi = sh.tail;
-    __syncthreads();
-    if (lo == hi) break;
-    for (int i = lo + t; i < hi; i += T) {
-      int v = g.list[i], d = g.get_depth(v);
-      unsigned h = g.get_head(v);
-      while (true) {
-        a.depth[g0 + v] = d;
-        ++done;
-        int nv = -1, nd = 0;
-        unsigned nh = L::kNone;
-        if (h & L::kSingle) {  // the parent's own link is read along with the report: one LDS latency a step
-          const int p = (int)(h & ~L::kSingle);
-          nh = g.get_head(p);
-          if (g.arrive(p, d + 1, nd)) nv = p;
-        } else if (h != L::kNone) {
-          unsigned nx;
-          int p = g.get_edge(h, nx);
-          while (true) {  // the next edge is read along with the report
-            const bool more = nx != L::kNone;
-            unsigned nx2 = L::kNone;
-            const int p2 = more ? g.get_edge(nx, nx2) : 0;
-            int dp;
-            if (g.arrive(p, d + 1, dp)) {
-              int other = p, od = dp;
-              if (nv < 0 || p < nv) other = nv, od = nd, nv = p, nd = dp;
-              if (other >= 0) {
-                g.set_depth(other, od);
-                g.list[atomicAdd(&sh.tail, 1)] = other;
-              }
-            }
-            if (!more) break;
-            p = p2, nx = nx2;
-          }
-          if (nv >= 0) nh = g.get_head(nv);
-        }
-        if (nv < 0) break;
-        v = nv, d = nd, h = nh;
-      }
-      deepest = max(deepest, d);  // a chain's last node is its deepest
-    }
-    lo = hi;
-  }
-  for (int s = kWave / 2; s; s >>= 1) {
-    done += __shfl_xor(done, s);
-    deepest = max(deepest, __shfl_xor(deepest, s));
-    parents = max(parents, __shfl_xor(parents, s));
-  }
-  if ((t & (kWave - 1)) == 0) {
-    atomicAdd(&sh.done, done);
-    atomicMax(&sh.deepest, deepest);
-    atomicMax(&sh.parents, parents);
-  }
+  int finished, deepest;
+  walk_graph(g, sh, [&](int v, int d) { a.depth[g0 + v] = d; }, finished, deepest);
+  graph_totals(sh, finished, deepest, parents);
   __syncthreads();
   if (t == 0) {
     if (sh.done < n) {
@@ -1037,6 +1059,435 @@ __global__ void k_finish(const unsigned long long* err, const int* meta, const i
   for (int o = i0; o < num_ops; o += step) go[kGroupArrays * gcap + o] = op_runs[o];
 }
 
+// ---------------------------------------------------------------- a small batch in one launch
+// A batch of up to 4,096 nodes is a chain of launches with almost no work in them (17, about 60 us), so one workgroup
+// does all of it in LDS: the same steps as above, with barriers for launches (152 nodes in one kernel of 27 us, the
+// schedule and the forward of eight levels 112 -> 90 us; 2,322 nodes in 45 us, with fourteen levels 222 -> 196).  It is bound by those barriers and the dependent LDS and memory accesses between them;
+// past 4,096 nodes (or 8,192 edges or graphs) the arrays no longer fit and one compute unit is too few.
+constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / kWave;
+constexpr int kSmallNodes = 4096, kSmallEdges = 8192;
+
+struct SmallArgs {
+  const int *gp, *cp, *ci, *node_op, *node_input;
+  int G, N, E, num_inputs;
+  int *depth, *node_pos, *pos_node, *input_idx, *root_pos, *child_pos, *child_one, *gid, *pos_npar, *op_rows, *op_cpos,
+      *op_inp, *tok_rows, *tok_seg, *tok_start, *tok_row, *level_ptr, *g_level, *g_op, *g_row_begin, *g_rows, *g_idx_off,
+      *g_cbase0, *g_cbase1;
+  int row_passes, tok_passes;  // digits of a leaf-table row; with one more where several ops read the table (0: none does)
+  int lcap, gcap;
+  int* out;
+};
+
+struct SmallLds {
+  uint32_t head[kSmallNodes], state[kSmallNodes];  // links and depths; then ops by row, and the sorted keys
+  uint32_t edge[kSmallEdges];                      // links; then the waves' digit counts
+  uint16_t list[kSmallNodes];                      // links; then the groups' withdrawn child bases
+  uint32_t keys[kSmallNodes];                      // each node's graph; then the sort's keys
+  uint16_t vals[kSmallNodes], pos[kSmallNodes], parents[kSmallNodes], child[2][kSmallNodes], start[kSmallNodes],
+      offset[kSmallNodes];
+  int base[kDigits];
+  int op_total[kMaxOps], op_at[kMaxOps], tok_at[kMaxOps], tok_op[kMaxOps], runs[kMaxOps];
+  int sums[3][kSmallWaves];
+  unsigned char bits[kMaxOps];
+  unsigned long long err, cycle;
+  GraphShared sh;
+};
+static_assert(sizeof(SmallLds) <= 160 * 1024, "the LDS of a compute unit");
+static_assert(kSmallWaves * kDigits * 2 <= kSmallEdges * 4, "the digit counts take the edges' place");
+
+// One stable pass over n (key, value) pairs in registers, item (wave, round, lane) in that order; through keys / vals.
+template <class DIGIT>
+__device__ __forceinline__ void small_pass(SmallLds& s, int n, int rounds, unsigned (&key)[kTileItems],
+                                           int (&val)[kTileItems], const DIGIT& digit) {
+  const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+  uint16_t* counts = reinterpret_cast<uint16_t*>(s.edge);
+  for (int i = t; i < kSmallWaves * kDigits / 2; i += kSmallThreads) s.edge[i] = 0;
+  int d[kTileItems], rank[kTileItems];
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int i = (w * rounds + r) * kWave + lane;
+    d[r] = r < rounds && i < n ? digit(key[r], val[r]) : -1;
+  }
+  __syncthreads();
+  wave_ranks(counts + w * kDigits, d, kDigitBits, rank);
+  __syncthreads();
+  int run = 0, all;
+  for (int k = 0; k < kSmallWaves; ++k) {
+    const int c = counts[k * kDigits + t];
+    counts[k * kDigits + t] = (uint16_t)run;
+    run += c;
+  }
+  s.base[t] = block_exscan<kSmallThreads>(run, &all);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r)
+    if (d[r] >= 0) {
+      const int at = s.base[d[r]] + counts[w * kDigits + d[r]] + rank[r];
+      s.keys[at] = key[r];
+      s.vals[at] = (uint16_t)val[r];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int i = (w * rounds + r) * kWave + lane;
+    if (r < rounds && i < n) key[r] = s.keys[i], val[r] = s.vals[i];
+  }
+}
+
+__global__ __launch_bounds__(kSmallThreads) void k_schedule_small(SmallArgs a, OpTable ops) {
+  static_assert(kDigits == kSmallThreads, "one digit a thread");
+  __shared__ SmallLds s;
+  const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave, N = a.N, K = ops.n;
+  const int rounds = (N + kSmallThreads - 1) / kSmallThreads;
+  auto item = [&](int r) { return (w * rounds + r) * kWave + lane; };
+  auto done = [&](unsigned long long e) {  // the error word alone
+    if (t == 0) {
+      a.out[0] = (int)(unsigned)(e & 0xffffffffull);
+      a.out[1] = (int)(unsigned)(e >> 32);
+    }
+  };
+  // pointers; keys[v] = the end of the graph that starts at node v (0: none does)
+  if (t == 0) {
+    s.err = s.cycle = kNoErr;
+    s.sh = {0, 0, 0, 0, 0};
+  }
+  for (int o = t; o < kMaxOps; o += kSmallThreads) s.op_total[o] = s.runs[o] = 0;
+  for (int o = t; o < K; o += kSmallThreads) s.bits[o] = ops.bits[o];
+  for (int v = t; v < N; v += kSmallThreads) {
+    s.head[v] = LdsLinks<true>::kNone;
+    s.keys[v] = 0;
+  }
+  __syncthreads();
+  bool bad = t == 0 && (a.gp[0] != 0 || a.gp[a.G] != N || a.cp[0] != 0 || a.cp[N] != a.E);
+  for (int g = t; g < a.G; g += kSmallThreads) {
+    const int lo = a.gp[g], hi = a.gp[g + 1];
+    if (lo < 0 || hi > N || lo > hi) bad = true;
+    else if (lo < hi) s.keys[lo] = (unsigned)hi;
+  }
+  for (int v = t; v < N; v += kSmallThreads) {
+    const int lo = a.cp[v], hi = a.cp[v + 1];
+    if (lo < 0 || hi > a.E || lo > hi) bad = true;
+  }
+  if (bad) s.sh.bad = 1;
+  __syncthreads();
+  if (s.sh.bad) {
+    done((unsigned long long)(-FOLD_E_INVALID));
+    return;
+  }
+  // the first node of every node's graph: the last graph start up to it
+  int first[kTileItems], carry = 0;
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int v = item(r);
+    int m = r < rounds && v < N && s.keys[v] ? v : 0;
+    for (int d = 1; d < kWave; d <<= 1) {
+      const int up = __shfl_up(m, d);
+      if (lane >= d) m = max(m, up);
+    }
+    first[r] = max(m, carry);
+    carry = max(carry, __shfl(m, kWave - 1));
+  }
+  if (lane == 0) s.sums[0][w] = carry;
+  __syncthreads();
+  for (int k = 0; k < w; ++k)
+#pragma unroll
+    for (int r = 0; r < kTileItems; ++r) first[r] = max(first[r], s.sums[0][k]);
+  // node checks and links
+  LdsLinks<true> g;
+  g.state = s.state, g.head = s.head, g.edge = s.edge, g.depth = s.edge, g.list = s.list;
+  int op_[kTileItems], c0[kTileItems], input[kTileItems];
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int v = item(r);
+    const bool in = r < rounds && v < N;
+    op_[r] = in ? a.node_op[v] : 0;
+    input[r] = in ? a.node_input[v] : -1;
+    c0[r] = in ? a.cp[v] : 0;
+    if (!in) continue;
+    const int lo = c0[r], hi = a.cp[v + 1], g0 = first[r], g1 = (int)s.keys[g0];
+    int fault = 0;
+    if (op_[r] < 0 || op_[r] >= K) {
+      fault = FOLD_E_OP;
+    } else if (hi - lo != (s.bits[op_[r]] & 3)) {
+      fault = FOLD_E_ARITY;
+    } else {
+      for (int j = lo; j < hi; ++j)
+        if (a.ci[j] != -1 && (a.ci[j] < g0 || a.ci[j] >= g1)) fault = FOLD_E_CHILD;
+      if (!fault && (s.bits[op_[r]] & 4 ? input[r] < 0 || input[r] >= a.num_inputs : input[r] != -1))
+        fault = FOLD_E_INPUT;
+    }
+    if (fault) {
+      report(&s.err, v + 1, fault);
+      continue;
+    }
+    int children = 0;
+    for (int j = lo; j < hi; ++j)
+      if (a.ci[j] >= 0) {
+        ++children;
+        g.set_edge(j, v, g.link(a.ci[j], j));
+      }
+    if (children) {
+      g.wait_for(v, children);
+    } else {
+      g.set_depth(v, 1);
+      g.list[atomicAdd(&s.sh.tail, 1)] = (uint16_t)v;
+    }
+  }
+  __syncthreads();
+  if (s.err != kNoErr) {
+    done(s.err);
+    return;
+  }
+  int most = 0;
+  for (int v = t; v < N; v += kSmallThreads) {
+    const int k = g.close(v);
+    s.parents[v] = (uint16_t)k;
+    most = max(most, k);
+  }
+  int finished, deepest;
+  walk_graph(g, s.sh, [&](int v, int d) { g.set_depth(v, d); }, finished, deepest);
+  graph_totals(s.sh, finished, deepest, most);
+  __syncthreads();
+  if (s.sh.done < N) {  // the lowest graph with a node that no walk finished (its state is no depth)
+#pragma unroll
+    for (int r = 0; r < kTileItems; ++r) {
+      const int v = item(r);
+      if (r < rounds && v < N && (s.state[v] == 0 || s.state[v] >> 24)) report(&s.cycle, first[r] + 1, FOLD_E_CYCLE);
+    }
+    __syncthreads();
+    done(s.cycle);
+    return;
+  }
+  const int D = s.sh.deepest;
+  // sort by depth and op
+  unsigned key[kTileItems];
+  int val[kTileItems];
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int v = item(r);
+    const bool in = r < rounds && v < N;
+    const int d = in ? (int)s.state[v] : 1;
+    key[r] = (unsigned)((d - 1) * K + op_[r]);
+    val[r] = v;
+    if (in) a.depth[v] = d;
+  }
+  __syncthreads();
+  for (int shift = 0; shift == 0 || ((long long)D * K - 1) >> shift; shift += kDigitBits)
+    small_pass(s, N, rounds, key, val, [&](unsigned k, int) { return (int)(k >> shift) & (kDigits - 1); });
+  // rows, group starts, edges, roots
+  unsigned char* row_op = reinterpret_cast<unsigned char*>(s.head);
+  unsigned* moved = reinterpret_cast<unsigned*>(s.list);  // [2][kSmallNodes / 32] bits by group
+  for (int i = t; i < kSmallNodes / 16; i += kSmallThreads) moved[i] = 0;
+  int s_at[kTileItems], e_at[kTileItems], r_at[kTileItems], ws = 0, we = 0, wr = 0;
+  bool start[kTileItems], root[kTileItems];
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int p = item(r);
+    const bool in = r < rounds && p < N;
+    const int level = (int)(key[r] / (unsigned)K);
+    op_[r] = in ? (int)(key[r] - (unsigned)level * K) : -1;
+    const unsigned prev = in && p > 0 ? s.keys[p - 1] : ~0u;
+    start[r] = in && prev != key[r];
+    root[r] = in && s.parents[p] == 0;
+    const int arity = in ? s.bits[op_[r]] & 3 : 0;
+    if (in) {
+      s.state[p] = key[r];
+      row_op[p] = (unsigned char)op_[r];
+      s.pos[val[r]] = (uint16_t)p;
+      a.pos_node[p] = val[r];
+      a.node_pos[val[r]] = p;
+      a.pos_npar[p] = s.parents[val[r]];
+      if (p == 0 || (int)(prev / (unsigned)K) != level) {
+        a.level_ptr[level] = p;
+        if (level <= a.lcap) a.out[kHdr + level] = p;
+      }
+      if (p == N - 1) {
+        a.level_ptr[level + 1] = N;
+        if (level + 1 <= a.lcap) a.out[kHdr + level + 1] = N;
+      }
+      const unsigned next = p + 1 < N ? s.keys[p + 1] : ~0u;  // rows of an op: its runs' ends minus their starts
+      if (start[r]) atomicAdd(&s.op_total[op_[r]], -p);
+      if (next != key[r]) atomicAdd(&s.op_total[op_[r]], p + 1);
+    }
+    const unsigned long long ms = __ballot(start[r]), m1 = __ballot(arity & 1), m2 = __ballot(arity & 2),
+                             mr = __ballot(root[r]), lt = lanes_below();
+    s_at[r] = ws + __popcll(ms & lt);
+    e_at[r] = we + __popcll(m1 & lt) + 2 * __popcll(m2 & lt);
+    r_at[r] = wr + __popcll(mr & lt);
+    ws += __popcll(ms);
+    we += __popcll(m1) + 2 * __popcll(m2);
+    wr += __popcll(mr);
+  }
+  if (lane == 0) s.sums[0][w] = ws, s.sums[1][w] = we, s.sums[2][w] = wr;
+  // ranks within each op (the digit counts' place, cleared first)
+  uint16_t* counts = reinterpret_cast<uint16_t*>(s.edge);
+  for (int i = t; i < kSmallWaves * kMaxOps / 2; i += kSmallThreads) s.edge[i] = 0;
+  __syncthreads();
+  int rank[kTileItems], op_bits = 0;
+  while ((1 << op_bits) < K) ++op_bits;
+  wave_ranks(counts + w * kMaxOps, op_, op_bits, rank);
+  {
+    const bool is_op = t < K, reads = is_op && (s.bits[t] & 4);
+    const int total = is_op ? s.op_total[t] : 0;
+    int all, entries, n;
+    const int at = block_exscan<kSmallThreads>(total, &all);
+    const int tok = block_exscan<kSmallThreads>(reads ? total : 0, &entries);
+    const int number = block_exscan<kSmallThreads>(reads ? 1 : 0, &n);
+    if (is_op) {
+      s.op_at[t] = at;
+      s.tok_at[t] = tok - at;
+      s.tok_op[t] = reads ? number : -1;
+      int run = 0;
+      for (int k = 0; k < kSmallWaves; ++k) {
+        const int c = counts[k * kMaxOps + t];
+        counts[k * kMaxOps + t] = (uint16_t)run;
+        run += c;
+      }
+    }
+    if (t == 0) s.base[0] = entries;
+  }
+  __syncthreads();
+  const int entries = s.base[0];
+  int starts = 0, edges = 0, roots = 0, num_groups = 0, num_roots = 0;
+  for (int k = 0; k < kSmallWaves; ++k) {
+    if (k < w) starts += s.sums[0][k], edges += s.sums[1][k], roots += s.sums[2][k];
+    num_groups += s.sums[0][k];
+    num_roots += s.sums[2][k];
+  }
+  // every index; child[k][p]: the child's row, 0x4000 where it has one parent edge, 0x8000 for no child
+  constexpr unsigned kOne = 0x4000, kNoChild = 0x8000;
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int p = item(r);
+    if (r >= rounds || p >= N) continue;
+    const int v = val[r], arity = s.bits[op_[r]] & 3, gg = starts + s_at[r] + (start[r] ? 1 : 0) - 1, off = edges + e_at[r];
+    const int at = a.cp[v], in_row = a.node_input[v], q = s.op_at[op_[r]] + counts[w * kMaxOps + op_[r]] + rank[r];
+    int cpos[2] = {-1, -1};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int c = k < arity ? a.ci[at + k] : -1;
+      const bool one = c >= 0 && s.parents[c] == 1;
+      cpos[k] = c >= 0 ? (int)s.pos[c] : -1;
+      s.child[k][p] = (uint16_t)(c >= 0 ? (unsigned)cpos[k] | (one ? kOne : 0u) : kNoChild);
+      if (k < arity) {
+        a.child_pos[off + k] = cpos[k];
+        a.child_one[off + k] = one;
+      }
+    }
+    if (start[r]) {
+      s.start[gg] = (uint16_t)p;
+      s.offset[gg] = (uint16_t)off;
+    }
+    c0[r] = gg;
+    a.gid[p] = gg;
+    a.input_idx[p] = in_row;
+    a.op_rows[q] = p;
+    a.op_cpos[2 * q] = cpos[0];
+    a.op_cpos[2 * q + 1] = cpos[1];
+    a.op_inp[q] = in_row;
+    if (s.tok_op[op_[r]] >= 0) {  // in (op, row) order
+      s.keys[q + s.tok_at[op_[r]]] = (unsigned)in_row;
+      s.vals[q + s.tok_at[op_[r]]] = (uint16_t)p;
+    }
+    if (root[r]) a.root_pos[roots + r_at[r]] = s.pos[p];
+  }
+  __syncthreads();
+  // child bases: withdrawn where a row's child does not follow the previous row's
+#pragma unroll
+  for (int r = 0; r < kTileItems; ++r) {
+    const int p = item(r);
+    if (r >= rounds || p >= N || start[r]) continue;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const unsigned x = s.child[k][p], before = s.child[k][p - 1];
+      if (k < (s.bits[op_[r]] & 3) && (!(x & kOne) || (x & 0x3fff) != (before & 0x3fff) + 1))
+        atomicOr(&moved[k * (kSmallNodes / 32) + (c0[r] >> 5)], 1u << (c0[r] & 31));
+    }
+  }
+  __syncthreads();
+  int* go = a.out + kHdr + a.lcap + 1;
+  for (int gg = t; gg < num_groups; gg += kSmallThreads) {
+    const int p = s.start[gg], rows = (gg + 1 < num_groups ? (int)s.start[gg + 1] : N) - p;
+    const int level = (int)(s.state[p] / (unsigned)K) + 1, op = row_op[p];
+    int cb[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const unsigned x = s.child[k][p];
+      const bool ok = (x & kOne) && !(moved[k * (kSmallNodes / 32) + (gg >> 5)] >> (gg & 31) & 1);
+      cb[k] = ok ? (int)(x & 0x3fff) : -1;
+    }
+    a.g_level[gg] = level;
+    a.g_op[gg] = op;
+    a.g_row_begin[gg] = p;
+    a.g_rows[gg] = rows;
+    a.g_idx_off[gg] = s.offset[gg];
+    a.g_cbase0[gg] = cb[0];
+    a.g_cbase1[gg] = cb[1];
+    if (gg < a.gcap) {
+      const int row[kGroupArrays] = {level, op, p, rows, (int)s.offset[gg], cb[0], cb[1]};
+#pragma unroll
+      for (int k = 0; k < kGroupArrays; ++k) go[k * a.gcap + gg] = row[k];
+    }
+  }
+  // the rows that read the leaf table by (op, leaf-table row), and their runs
+  if (a.tok_passes > 0) {
+    const int n = entries, per = (n + kSmallThreads - 1) / kSmallThreads;
+    auto entry = [&](int r) { return (w * per + r) * kWave + lane; };
+#pragma unroll
+    for (int r = 0; r < kTileItems; ++r) {
+      const int i = entry(r);
+      key[r] = r < per && i < n ? s.keys[i] : 0u;
+      val[r] = r < per && i < n ? (int)s.vals[i] : 0;
+    }
+    __syncthreads();
+    for (int ps = 0; ps < a.tok_passes; ++ps) {
+      if (ps < a.row_passes)
+        small_pass(s, n, per, key, val, [&](unsigned k, int) { return (int)(k >> (kDigitBits * ps)) & (kDigits - 1); });
+      else
+        small_pass(s, n, per, key, val, [&](unsigned, int p) { return s.tok_op[row_op[p]]; });
+    }
+    ws = 0;
+#pragma unroll
+    for (int r = 0; r < kTileItems; ++r) {
+      const int i = entry(r);
+      const bool in = r < per && i < n;
+      start[r] = in && (i == 0 || s.keys[i - 1] != key[r] || row_op[s.vals[i - 1]] != row_op[val[r]]);
+      const unsigned long long m = __ballot(start[r]);
+      s_at[r] = ws + __popcll(m & lanes_below());
+      ws += __popcll(m);
+    }
+    if (lane == 0) s.sums[0][w] = ws;
+    __syncthreads();
+    starts = 0;
+    for (int k = 0; k < w; ++k) starts += s.sums[0][k];
+#pragma unroll
+    for (int r = 0; r < kTileItems; ++r) {
+      const int i = entry(r);
+      if (r >= per || i >= n) continue;
+      const int u = starts + s_at[r] + (start[r] ? 1 : 0) - 1;
+      a.tok_rows[i] = val[r];
+      a.tok_seg[i] = u;
+      if (start[r]) {
+        a.tok_start[u] = i;
+        a.tok_row[u] = (int)key[r];
+        atomicAdd(&s.runs[s.tok_op[row_op[val[r]]]], 1);
+      }
+      if (i == n - 1) a.tok_start[u + 1] = n;
+    }
+  }
+  __syncthreads();
+  for (int o = t; o < K; o += kSmallThreads) go[kGroupArrays * a.gcap + o] = s.runs[o];
+  if (t == 0) {
+    done(kNoErr);
+    int* meta = a.out + 2;
+    meta[0] = D;
+    meta[1] = s.sh.parents;
+    meta[4] = num_groups;
+    meta[5] = num_roots;
+    meta[6] = entries;
+  }
+}
+
 inline dim3 grid_for(long long n) { return dim3((unsigned)std::max(1LL, (n + kBlock - 1) / kBlock)); }
 
 // Temporaries of one phase on one stream: the sizes are declared first (reserve), then one pooled block backs them all
@@ -1184,9 +1635,10 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   constexpr int kLcap = 4096, kGcap = 4096;  // levels and groups read back with the error word
   static_assert(kHdr + (kLcap + 1) + kGroupArrays * (size_t)kGcap + kMaxOps <= kStageInts, "the read-back buffer");
   int* op_runs = nullptr;  // [kMaxOps] runs of equal (op, leaf-table row) of the ops that read the leaf table
+  const bool small = N > 0 && N <= kSmallNodes && E <= kSmallEdges && G <= kSmallEdges;
   tmp.reserve(&em, 1);
   tmp.reserve(&op_runs, kMaxOps);
-  if (N > 0) {
+  if (N > 0 && !small) {
     tmp.reserve(&indeg, N);
     tmp.reserve(&scratch, (size_t)scratch_ints);
     tmp.reserve(&moved, 2 * (size_t)N);
@@ -1209,76 +1661,93 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
   }
   unsigned long long* err = &em->err;
   int* meta = em->meta;
-  hipLaunchKernelGGL(k_init_meta, dim3(1), dim3(kBlock), 0, st, em, 8, op_runs, kMaxOps);
-  hipLaunchKernelGGL(k_check_struct, grid_for(std::max(G + 1, N + 1)), dim3(kBlock), 0, st, b->graph_ptr, G,
-                     b->child_ptr, N, E, err);
-  if (N > 0) {
-    if (G > 0) {
-      const int lds = graph_lds_bytes(N, E, G, LdsLinks<true>::kNodeBytes, LdsLinks<true>::kEdgeBytes);
-      const GraphArgs ga{b->graph_ptr, b->child_ptr, b->child_idx, s.depth, indeg, scratch, err, &em->cycle, meta,
-                         b->node_op, b->node_input, b->num_inputs};
-      hipLaunchKernelGGL(k_graph_depth<true>, dim3(G), dim3(kGraphThreads), lds, st, ga, ops, lds);
-    }
-
-    // sort by (depth - 1) * num_ops + op: as many passes as N * num_ops keys could need are launched; those the actual
-    // depth does not need return at once
-    const unsigned long long max_key = std::min<unsigned long long>((unsigned long long)N * K,
-                                                                    (unsigned long long)kMaxKeys) - 1;
-    const int passes = sort_passes(max_key);
-    const SortSize all{N, nullptr};
-    for (int ps = 0; ps < passes; ++ps) {
-      const SortGate gate{err, meta, K, ps};
-      if (ps == 0)
-        sort_pass<NodeKeys, true>({s.depth, b->node_op, K}, all, 0, sort_counts, keys[0], vals[0], gate, err, &em->cycle,
-                                  st);
-      else
-        sort_pass<PairKeys<unsigned>>({keys[(ps - 1) & 1], vals[(ps - 1) & 1]}, all, kDigitBits * ps, sort_counts,
-                                      keys[ps & 1], vals[ps & 1], gate, err, &em->cycle, st);
-    }
-    EmitArgs ea{};
-    for (int i = 0; i < 2; ++i) {
-      ea.keys[i] = keys[i];
-      ea.vals[i] = vals[i];
-    }
-    ea.cp = b->child_ptr; ea.ci = b->child_idx; ea.node_input = b->node_input; ea.indeg = indeg;
-    ea.N = N; ea.num_ops = K; ea.tiles = B;
-    ea.starts = tile_sums; ea.edges = tile_sums + B; ea.roots = tile_sums + 2 * (size_t)B;
-    ea.op_count = op_count; ea.moved = moved; ea.link = link;
-    ea.pos_node = s.pos_node; ea.node_pos = s.node_pos; ea.gid = s.pos_group; ea.level_ptr = s.level_ptr;
-    ea.g_level = s.g_level; ea.g_op = s.g_op; ea.g_row_begin = s.g_row_begin; ea.g_idx_off = s.g_idx_off;
-    ea.g_cbase0 = s.g_cbase0; ea.g_cbase1 = s.g_cbase1;
-    ea.child_pos = s.child_pos; ea.child_one = s.child_one; ea.input_idx = s.input_idx; ea.pos_npar = s.pos_npar;
-    ea.root_pos = s.root_pos; ea.op_rows = s.op_rows; ea.op_cpos = s.op_cpos; ea.op_inp = s.op_inp;
-    ea.tok_key = tok_keys[0]; ea.tok_val = tok_vals[0];
-    ea.meta = meta; ea.err = err;
-    hipLaunchKernelGGL(k_emit_sums, dim3(B), dim3(kTileThreads), 0, st, ea, ops);
-    hipLaunchKernelGGL(k_emit, dim3(B), dim3(kTileThreads), 0, st, ea, ops);
-
-    // the rows that read the leaf table in (op, leaf-table row) order, and their runs: they come in (op, row) order,
-    // so passes over the leaf-table row's bits and, where several ops read it, one over the op sort them
-    if (any_input) {
-      const int row_passes = sort_passes((unsigned long long)std::max(b->num_inputs - 1, 0));
-      const int tok_passes = row_passes + (input_ops > 1 ? 1 : 0);
-      const SortSize entries{N, meta + 6};
-      for (int ps = 0; ps < tok_passes; ++ps) {
-        const SortGate gate{err, nullptr, 0, 0};
-        sort_pass<PairKeys<unsigned long long>>({tok_keys[ps & 1], tok_vals[ps & 1]}, entries,
-                                                ps < row_passes ? kDigitBits * ps : 32, sort_counts,
-                                                tok_keys[(ps + 1) & 1],
-                                                ps + 1 < tok_passes ? tok_vals[(ps + 1) & 1] : s.tok_rows, gate, err,
-                                                &em->cycle, st);
+  // digits of a leaf-table row, and one pass more over the op where several ops read the table
+  const int row_passes = any_input ? sort_passes((unsigned long long)std::max(b->num_inputs - 1, 0)) : 0;
+  const int tok_passes = row_passes + (input_ops > 1 ? 1 : 0);
+  if (small) {
+    SmallArgs a{};
+    a.gp = b->graph_ptr; a.cp = b->child_ptr; a.ci = b->child_idx; a.node_op = b->node_op; a.node_input = b->node_input;
+    a.G = G; a.N = N; a.E = E; a.num_inputs = b->num_inputs;
+    a.depth = s.depth; a.node_pos = s.node_pos; a.pos_node = s.pos_node; a.input_idx = s.input_idx;
+    a.root_pos = s.root_pos; a.child_pos = s.child_pos; a.child_one = s.child_one; a.gid = s.pos_group;
+    a.pos_npar = s.pos_npar; a.op_rows = s.op_rows; a.op_cpos = s.op_cpos; a.op_inp = s.op_inp;
+    a.tok_rows = s.tok_rows; a.tok_seg = s.tok_seg; a.tok_start = s.tok_start; a.tok_row = s.tok_row;
+    a.level_ptr = s.level_ptr; a.g_level = s.g_level; a.g_op = s.g_op; a.g_row_begin = s.g_row_begin;
+    a.g_rows = s.g_rows; a.g_idx_off = s.g_idx_off; a.g_cbase0 = s.g_cbase0; a.g_cbase1 = s.g_cbase1;
+    a.row_passes = row_passes; a.tok_passes = tok_passes;
+    a.lcap = kLcap; a.gcap = kGcap; a.out = tmp.stage;
+    hipLaunchKernelGGL(k_schedule_small, dim3(1), dim3(kSmallThreads), 0, st, a, ops);
+  } else {
+    hipLaunchKernelGGL(k_init_meta, dim3(1), dim3(kBlock), 0, st, em, 8, op_runs, kMaxOps);
+    hipLaunchKernelGGL(k_check_struct, grid_for(std::max(G + 1, N + 1)), dim3(kBlock), 0, st, b->graph_ptr, G,
+                       b->child_ptr, N, E, err);
+    if (N > 0) {
+      if (G > 0) {
+        const int lds = graph_lds_bytes(N, E, G, LdsLinks<true>::kNodeBytes, LdsLinks<true>::kEdgeBytes);
+        const GraphArgs ga{b->graph_ptr, b->child_ptr, b->child_idx, s.depth, indeg, scratch, err, &em->cycle, meta,
+                           b->node_op, b->node_input, b->num_inputs};
+        hipLaunchKernelGGL(k_graph_depth<true>, dim3(G), dim3(kGraphThreads), lds, st, ga, ops, lds);
       }
-      const unsigned long long* sorted = tok_keys[tok_passes & 1];
-      int* tok_starts = tile_sums + 3 * (size_t)B;
-      hipLaunchKernelGGL(k_tok_sums, dim3(B), dim3(kTileThreads), 0, st, sorted, meta + 6, tok_starts, err);
-      hipLaunchKernelGGL(k_tok_emit, dim3(B), dim3(kTileThreads), 0, st, sorted, meta + 6, tok_starts, s.tok_start,
-                         s.tok_row, s.tok_seg, op_runs, err);
+
+      // sort by (depth - 1) * num_ops + op: as many passes as N * num_ops keys could need are launched; those the actual
+      // depth does not need return at once
+      const unsigned long long max_key = std::min<unsigned long long>((unsigned long long)N * K,
+                                                                      (unsigned long long)kMaxKeys) - 1;
+      const int passes = sort_passes(max_key);
+      const SortSize all{N, nullptr};
+      for (int ps = 0; ps < passes; ++ps) {
+        const SortGate gate{err, meta, K, ps};
+        if (ps == 0)
+          sort_pass<NodeKeys, true>({s.depth, b->node_op, K}, all, 0, sort_counts, keys[0], vals[0], gate, err, &em->cycle,
+                                    st);
+        else
+          sort_pass<PairKeys<unsigned>>({keys[(ps - 1) & 1], vals[(ps - 1) & 1]}, all, kDigitBits * ps, sort_counts,
+                                        keys[ps & 1], vals[ps & 1], gate, err, &em->cycle, st);
+      }
+      EmitArgs ea{};
+      for (int i = 0; i < 2; ++i) {
+        ea.keys[i] = keys[i];
+        ea.vals[i] = vals[i];
+      }
+      ea.cp = b->child_ptr; ea.ci = b->child_idx; ea.node_input = b->node_input; ea.indeg = indeg;
+      ea.N = N; ea.num_ops = K; ea.tiles = B;
+      ea.starts = tile_sums; ea.edges = tile_sums + B; ea.roots = tile_sums + 2 * (size_t)B;
+      ea.op_count = op_count; ea.moved = moved; ea.link = link;
+      ea.pos_node = s.pos_node; ea.node_pos = s.node_pos; ea.gid = s.pos_group; ea.level_ptr = s.level_ptr;
+      ea.g_level = s.g_level; ea.g_op = s.g_op; ea.g_row_begin = s.g_row_begin; ea.g_idx_off = s.g_idx_off;
+      ea.g_cbase0 = s.g_cbase0; ea.g_cbase1 = s.g_cbase1;
+      ea.child_pos = s.child_pos; ea.child_one = s.child_one; ea.input_idx = s.input_idx; ea.pos_npar = s.pos_npar;
+      ea.root_pos = s.root_pos; ea.op_rows = s.op_rows; ea.op_cpos = s.op_cpos; ea.op_inp = s.op_inp;
+      ea.tok_key = tok_keys[0]; ea.tok_val = tok_vals[0];
+      ea.meta = meta; ea.err = err;
+      hipLaunchKernelGGL(k_emit_sums, dim3(B), dim3(kTileThreads), 0, st, ea, ops);
+      hipLaunchKernelGGL(k_emit, dim3(B), dim3(kTileThreads), 0, st, ea, ops);
+
+      // the rows that read the leaf table in (op, leaf-table row) order, and their runs: they come in (op, row) order,
+      // so passes over the leaf-table row's bits and, where several ops read it, one over the op sort them
+      if (any_input) {
+        const SortSize entries{N, meta + 6};
+        for (int ps = 0; ps < tok_passes; ++ps) {
+          const SortGate gate{err, nullptr, 0, 0};
+          sort_pass<PairKeys<unsigned long long>>({tok_keys[ps & 1], tok_vals[ps & 1]}, entries,
+                                                  ps < row_passes ? kDigitBits * ps : 32, sort_counts,
+                                                  tok_keys[(ps + 1) & 1],
+                                                  ps + 1 < tok_passes ? tok_vals[(ps + 1) & 1] : s.tok_rows, gate, err,
+                                                  &em->cycle, st);
+        }
+        const unsigned long long* sorted = tok_keys[tok_passes & 1];
+        int* tok_starts = tile_sums + 3 * (size_t)B;
+        hipLaunchKernelGGL(k_tok_sums, dim3(B), dim3(kTileThreads), 0, st, sorted, meta + 6, tok_starts, err);
+        hipLaunchKernelGGL(k_tok_emit, dim3(B), dim3(kTileThreads), 0, st, sorted, meta + 6, tok_starts, s.tok_start,
+                           s.tok_row, s.tok_seg, op_runs, err);
+      }
     }
   }
   GroupArrays ga{{s.g_level, s.g_op, s.g_row_begin, s.g_rows, s.g_idx_off, s.g_cbase0, s.g_cbase1}};
   // a workgroup per 1,024 possible groups, at most 16 (a batch has few groups; a thousand-level chain of them still
   // takes a few steps)
-  hipLaunchKernelGGL(k_finish, dim3(std::min(16, N / 1024 + 1)), dim3(kBlock), 0, st, err, meta, s.level_ptr, ga, N, moved,
+  if (!small)
+    hipLaunchKernelGGL(k_finish, dim3(std::min(16, N / 1024 + 1)), dim3(kBlock), 0, st, err, meta, s.level_ptr, ga, N, moved,
                      s.g_rows, s.g_cbase0, s.g_cbase1, kLcap, kGcap, op_runs, K, tmp.stage);
   if (hipGetLastError() != hipSuccess) {
     set_error("fold_schedule: kernel launch failed");

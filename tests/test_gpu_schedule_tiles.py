@@ -28,7 +28,8 @@ def _chains(rng, total, longest, num_ops):
 
 
 @pytest.mark.parametrize("total,longest,num_ops", [
-    (1, 1, 2), (63, 5, 2), (2047, 9, 3), (2048, 9, 2), (2049, 40, 5),
+    (1, 1, 2), (63, 5, 2), (4096, 4000, 3), (4096, 9, 256), (4097, 9, 5),  # one launch up to 4,096 nodes
+    (2047, 9, 3), (2048, 9, 2), (2049, 40, 5),
     (65535, 30, 2), (65537, 30, 4),     # 32 tiles and one node more: the column scan
     (3000, 700, 3),                     # two digits
     (5000, 5000, 256),                  # one chain of 5,000: keys past 2^20, three digits, no room in LDS
@@ -38,7 +39,53 @@ def test_tile_and_digit_edges(total, longest, num_ops):
     C.assert_schedule_equal(_gpu_sched(w), C.oracle_schedule(w))
 
 
-@pytest.mark.parametrize("total,rows", [(1, 1), (2049, 1), (4097, 3000), (70001, 5), (70001, 100003)])
+def test_dags_of_both_paths():
+    """Shared children, a child taken twice and zero states, just below and above the one-launch limit."""
+    from tests.test_oracle_schedule import random_dag
+    for seed, n in ((5, 130), (6, 420)):
+        w = random_dag(np.random.default_rng(seed), n_graphs=n, max_nodes=60)
+        C.assert_schedule_equal(_gpu_sched(w), C.oracle_schedule(w))
+
+
+@pytest.mark.parametrize("total", [200, 6000])
+@pytest.mark.parametrize("what", ["op", "arity", "child", "other graph", "input", "cycle", "pointers", "lowest"])
+def test_errors_of_both_paths(total, what):
+    """Every error code from the one-launch schedule and from the tiled one; the lowest node counts."""
+    from paper_1702_02181_amd import fold as F
+    w = _chains(np.random.default_rng(1), total, 12, 3)
+    gp, at = w.graph_ptr, int(np.nonzero(np.diff(w.graph_ptr) > 4)[0][3])  # a graph of five nodes or more
+    first = int(gp[at])
+    edge = lambda v: int(w.child_ptr[v])  # noqa: E731
+    code = {"op": F.FOLD_E_OP, "arity": F.FOLD_E_ARITY, "child": F.FOLD_E_CHILD, "other graph": F.FOLD_E_CHILD,
+            "input": F.FOLD_E_INPUT, "cycle": F.FOLD_E_CYCLE, "pointers": F.FOLD_E_INVALID, "lowest": F.FOLD_E_INPUT}[what]
+    if what == "op":
+        w.node_op[first + 2] = 3
+    elif what == "arity":
+        w.node_op[first + 2], w.node_input[first + 2] = 0, 0
+    elif what == "child":
+        w.child_idx[edge(first + 2)] = total
+    elif what == "other graph":
+        w.child_idx[edge(first + 2)] = first - 1
+    elif what == "input":
+        w.node_input[first] = 9
+    elif what == "cycle":
+        w.child_idx[edge(first + 1)] = first + 3
+    elif what == "pointers":
+        w.child_ptr[first + 2] = w.child_ptr[-1] + 1
+    else:  # a cycle and an operation out of range come after a bad input in node order
+        w.node_input[first] = -1
+        w.node_op[first + 3] = 7
+        w.child_idx[edge(first + 1)] = first + 2
+    with pytest.raises(F.FoldError) as e:
+        _gpu_sched(w)
+    assert e.value.code == code
+    if what == "cycle":
+        assert f"(node {first})" in str(e.value)
+    elif what == "lowest":
+        assert f"(node {first})" in str(e.value)
+
+
+@pytest.mark.parametrize("total,rows", [(1, 1), (2049, 1), (4096, 3000), (4097, 3000), (70001, 5), (70001, 100003)])
 def test_leaf_table_runs(total, rows):
     """Nodes that are embeddings of two operations, both reading random rows: each leaf-table row's gradient is the sum
     of its nodes' upstream gradients (fp32 sums of n terms: error below n 2^-24 times the sum of their magnitudes)."""
