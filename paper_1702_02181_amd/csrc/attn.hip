@@ -95,9 +95,19 @@ __device__ __forceinline__ void add4(float* dst, const float (&v)[4], bool singl
 }
 // A child's dc row, whose only nonzero entry is column 1 (ds): a child with one parent edge gets the whole row
 // stored (its row is never initialised), a shared child an atomic add of ds into its zeroed row.
-__device__ __forceinline__ void ds_to(float* row, int ld, int lane, float ds, bool single) {
+// (a row that nobody reads whole: `dc_cols` columns of it)
+__device__ __forceinline__ int dc_cols(const AttnArgs& a, int child) {
+  if (a.child_dc_dead) return 0;
+  if (!a.pos_group) return a.ld;
+  const int op = a.group_op[a.pos_group[child]];
+  return (a.attn_ops[op >> 5] >> (op & 31)) & 1u ? 4 : a.ld;
+}
+__device__ __forceinline__ void ds_to(const AttnArgs& a, int child, int lane, float ds, bool single) {
+  float* row = a.dc + (size_t)child * a.ld;
+  const int cols = dc_cols(a, child);
+  if (cols == 0) return;
   if (single) {
-    put_ms(row, ld, lane, 0.f, ds);
+    put_ms(row, cols, lane, 0.f, ds);
   } else if (lane == 0 && ds != 0.f) {
     unsafeAtomicAdd(row + 1, ds);
   }
@@ -188,7 +198,7 @@ __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_attn_bwd(AttnArgs a) {
         for (int e = 0; e < 4; ++e) g[e] = j + e < a.H ? g[e] + de * wv[e] : 0.f;
         add4(&a.dh[(size_t)c0 * a.ld + j], g, one, a.dh_fresh);
       }
-      ds_to(a.dc + (size_t)c0 * a.ld, a.ld, lane, 0.f, one);  // an item passes no cell-state gradient down
+      ds_to(a, c0, lane, 0.f, one);  // an item passes no cell-state gradient down
     }
   } else if constexpr (KIND == FOLD_ATTN_SUM) {
     // with m fixed, acc and s are linear in the children's: dh_k += x_k dh, ds_k += x_k ds
@@ -220,7 +230,7 @@ __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_attn_bwd(AttnArgs a) {
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k)
-      if (ck[k] >= 0) ds_to(a.dc + (size_t)ck[k] * a.ld, a.ld, lane, xk[k] * ds, one[k]);
+      if (ck[k] >= 0) ds_to(a, ck[k], lane, xk[k] * ds, one[k]);
   } else {  // FOLD_ATTN_OUT: h = acc / s -> dacc = dh / s, ds = -(dh . acc) / s^2
     const int c0 = a.child_pos[a.idx_off + row];
     if (c0 < 0) return;
@@ -231,7 +241,7 @@ __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_attn_bwd(AttnArgs a) {
         const float z[4] = {0.f, 0.f, 0.f, 0.f};
         if (a.dh_fresh)
           for (int j = 4 * lane; j < a.ld; j += 4 * kWave) st4(&a.dh[(size_t)c0 * a.ld + j], z);
-        put_ms(a.dc + (size_t)c0 * a.ld, a.ld, lane, 0.f, 0.f);
+        ds_to(a, c0, lane, 0.f, true);
       }
       return;
     }
@@ -248,7 +258,7 @@ __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_attn_bwd(AttnArgs a) {
       add4(&a.dh[(size_t)c0 * a.ld + j], g, one, a.dh_fresh);
     }
     const double tot = wave_total(part);
-    ds_to(a.dc + (size_t)c0 * a.ld, a.ld, lane, (float)(-tot / ((double)s * s)), one);
+    ds_to(a, c0, lane, (float)(-tot / ((double)s * s)), one);
   }
 }
 

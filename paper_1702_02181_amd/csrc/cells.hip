@@ -751,7 +751,7 @@ __device__ __forceinline__ void cell_bwd_body(const BwdCellArgs a, int row) {
       } else {  // TreeRNN, PROJ: h = tanh(z)
         const float h = g[0][e];
         dz[0][e] = dh[e] * (1.f - h * h);
-        if constexpr (KIND == FOLD_PROJ) dck[0][e] = a.dc[p * a.ld + j + e];  // c = c_child
+        if constexpr (KIND == FOLD_PROJ) dck[0][e] = a.child_dc_dead ? 0.f : a.dc[p * a.ld + j + e];  // c = c_child
       }
       if (!live[e]) {  // pad columns: zero dz and zero gradients for the children
 #pragma unroll
@@ -773,9 +773,9 @@ __device__ __forceinline__ void cell_bwd_body(const BwdCellArgs a, int row) {
       if (ck[k] < 0) continue;
       float* dcr = a.dc + (size_t)ck[k] * a.ld + j;
       if (sk[k]) {
-        *reinterpret_cast<float2*>(dcr) = make_float2(dck[k][0], dck[k][1]);
+        if (!a.child_dc_dead) *reinterpret_cast<float2*>(dcr) = make_float2(dck[k][0], dck[k][1]);
         if (a.zero_child_dh) *reinterpret_cast<float2*>(a.dh + (size_t)ck[k] * a.ld + j) = make_float2(0.f, 0.f);
-      } else if (KIND != FOLD_TREERNN) {
+      } else if (KIND != FOLD_TREERNN && !a.child_dc_dead) {
 #pragma unroll
         for (int e = 0; e < 2; ++e)
           if (live[e]) unsafeAtomicAdd(dcr + e, dck[k][e]);

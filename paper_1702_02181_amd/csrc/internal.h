@@ -229,6 +229,7 @@ struct BwdCellArgs {
   // this group's dz . W^T adds K slices into its children's dh atomically: zero the dh rows of the children
   // with one parent edge first (their rows are not initialised)
   int zero_child_dh = 0;
+  int child_dc_dead = 0;  // nobody reads the children's dc (see backward_impl): it is not written
 };
 void launch_cell_bwd(int kind, const BwdCellArgs& a, hipStream_t st);
 void launch_level_cbwd(const int* kinds, const BwdCellArgs* args, int n, hipStream_t st);
@@ -318,6 +319,11 @@ struct AttnArgs {
   float* gates;         // backward: the scorer saves de at gates[p * gstride] (NULL: not saved)
   int gstride;
   int dh_fresh;         // backward: the dh rows of children with one parent edge start undefined (stored whole)
+  // backward without a dc output: nobody reads the children's dc (it is not written), or (pos_group given) a child
+  // that is an attention node reads column 1 alone (its first four columns are written)
+  int child_dc_dead = 0;
+  const int *pos_group = nullptr, *group_op = nullptr;
+  uint32_t attn_ops[8] = {0};  // by op: an attention kind
 };
 // rows of the scorer's weight gradient reduced by one workgroup (chunk order is fixed)
 constexpr int kAttnWgradChunk = 128;
