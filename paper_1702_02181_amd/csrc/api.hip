@@ -554,6 +554,14 @@ int32_t backward_impl(const Sched& s, const Packed& p, const void* table, int64_
 
   // Rows of nodes with one parent edge are not initialised: that parent's backward stores them whole (dh
   // rows only when no per-node upstream gradient has to be added to).
+  // Per-node upstream gradients are added where the cell backward reads dh, and dh then holds the parents' part alone
+  // (a copy of every row into dh, read again by each dz . W^T before it adds: 65,790 rows at H = 300, the training step
+  // 1,421 -> 1,392 us); they start the rows where an output or another reader of dh (attention, an embedding's
+  // leaf-table gradient) wants the sum.
+  bool sum_in_dh = dh_out != nullptr;
+  for (const fold_op& op : s.ops) sum_in_dh = sum_in_dh || is_attn(op.kind) || op.kind == FOLD_EMBED;
+  const float* dh_add = sum_in_dh ? nullptr : dh_nodes;
+  if (dh_add) dh_nodes = nullptr;
   const int dh_fresh = dh_nodes == nullptr;
   const int esize = p.dtype == FOLD_BF16 ? 2 : 4;
   launch_bwd_init(s.N, s.R, p.ld, dh_nodes, dh_roots, s.root_pos, s.pos_npar, dh, dc, st);
@@ -630,6 +638,7 @@ int32_t backward_impl(const Sched& s, const Packed& p, const void* table, int64_
       const bool dc_unread = op.arity == 1 ? dc_dead[below] : dc_dead_to[below];
       const bool dh_unread = no_embed_dh && below == 1;
       b.child_dc_dead = dc_unread;
+      b.dh_add = dh_add;
       if (is_attn(op.kind)) {  // adds into the children itself: no dz . W^T
         AttnArgs at = attn_args(s, p, g, const_cast<void*>(h_pool), const_cast<float*>(c_pool));
         at.dh = dh;

@@ -728,6 +728,11 @@ __device__ __forceinline__ void cell_bwd_body(const BwdCellArgs a, int row) {
     }
     float dh[2], dz[G][2], dck[2][2] = {{0.f, 0.f}, {0.f, 0.f}};  // dc passed to child slot k
     ld2(a.dh + p * a.ld + j, dh);
+    if (a.dh_add) {
+      float up[2];
+      ld2(a.dh_add + p * a.ld + j, up);
+      dh[0] += up[0], dh[1] += up[1];
+    }
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       if constexpr (KIND == FOLD_TREELSTM || KIND == kTreeLstmLeaf || KIND == FOLD_LSTM) {

@@ -230,6 +230,7 @@ struct BwdCellArgs {
   // with one parent edge first (their rows are not initialised)
   int zero_child_dh = 0;
   int child_dc_dead = 0;  // nobody reads the children's dc (see backward_impl): it is not written
+  const float* dh_add = nullptr;  // per-node upstream gradients that dh does not hold yet, or NULL
 };
 void launch_cell_bwd(int kind, const BwdCellArgs& a, hipStream_t st);
 void launch_level_cbwd(const int* kinds, const BwdCellArgs* args, int n, hipStream_t st);
