@@ -214,7 +214,8 @@ WsLayout workspace_layout(const Sched& s, const Packed& p) {
       continue;
     }
     const PackedSet& ps = p.sets[op.param_set];
-    const FwdPlan pl = fwd_plan(s.h_rows[g], p.HP, op.has_input ? ps.INP : 0, op.arity,
+    const int gates = is_tree_lstm_leaf(op) ? gates_of(kTreeLstmLeaf) : ps.G;
+    const FwdPlan pl = fwd_plan(s.h_rows[g], p.HP, op.has_input ? ps.INP : 0, op.arity, gates,
                                 p.dtype == FOLD_BF16 ? 2 : 4, true);
     const size_t need = pl.ksplit > 1 ? (size_t)pl.ksplit * s.h_rows[g] * ps.G * p.HP : 0;
     w.zneed[g] = need;

@@ -1232,8 +1232,8 @@ inline int narrow_grid(int rows, int HP, const NarrowPlan& n) { return xcd_grid(
 
 template <typename T, int KIND>
 void cell_fwd_kind(const FwdArgs& a0, hipStream_t st) {
-  const FwdPlan pl = fwd_plan(a0.rows, a0.HP, a0.has_input ? a0.INP : 0, a0.arity, sizeof(T), a0.zpart != nullptr,
-                              true);
+  const FwdPlan pl = fwd_plan(a0.rows, a0.HP, a0.has_input ? a0.INP : 0, a0.arity, Gates<KIND>::G, sizeof(T),
+                              a0.zpart != nullptr, true);
   FwdArgs a = a0;
   if (pl.wide) {
     const int R = (int)cdiv(a.rows, wide::kRows), NU = a.HP / 64;
@@ -1641,13 +1641,15 @@ void launch_level_fwd(int dtype, const int* kinds, const FwdArgs* args, int n, h
   for (int k = 0; k < n; ++k) {
     const FwdArgs& a = args[k];
     if (a.rows <= 0) continue;
-    const FwdPlan pl = fwd_plan(a.rows, a.HP, a.has_input ? a.INP : 0, a.arity, esize, a.zpart != nullptr);
+    const FwdPlan pl = fwd_plan(a.rows, a.HP, a.has_input ? a.INP : 0, a.arity, gates_of(kinds[k]), esize,
+                                a.zpart != nullptr);
     planned += (long long)cdiv(a.rows, 128) * (a.HP / 32) * pl.ksplit;
   }
   for (int k = 0; k < n; ++k) {
     FwdArgs a = args[k];
     if (a.rows <= 0) continue;
-    const FwdPlan pl = fwd_plan(a.rows, a.HP, a.has_input ? a.INP : 0, a.arity, esize, a.zpart != nullptr);
+    const FwdPlan pl = fwd_plan(a.rows, a.HP, a.has_input ? a.INP : 0, a.arity, gates_of(kinds[k]), esize,
+                                a.zpart != nullptr);
     const int G = gates_of(kinds[k]);
     a.ksplit = pl.ksplit;
     if (planned > kLevelFwdWorkgroups && a.ksplit > 1)

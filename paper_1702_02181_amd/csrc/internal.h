@@ -134,7 +134,8 @@ inline NarrowPlan narrow_fwd_plan(int rows, int HP, int K, int esize) {
 }
 
 // alone: the group launches by itself (not in a level launch, whose groups' splits are cut together)
-inline FwdPlan fwd_plan(int rows, int HP, int inp_used, int arity, int esize, bool can_split, bool alone = false) {
+inline FwdPlan fwd_plan(int rows, int HP, int inp_used, int arity, int gates, int esize, bool can_split,
+                        bool alone = false) {
   const int BK = esize == 4 ? 32 : 64;
   const int nst = inp_used / BK + arity * (HP / BK);
   const long long ub = HP / 32;
@@ -144,6 +145,27 @@ inline FwdPlan fwd_plan(int rows, int HP, int inp_used, int arity, int esize, bo
   p.wide = ((long long)(rows + 255) / 256) * (ub / 2) >= 256;
   if (p.wide) return p;
   const long long base = ((long long)(rows + 127) / 128) * ub;
+  // fp32 cells of several gates: the matrix cores are the bound, so a level takes as long as its fullest compute unit
+  // has tiles to do (288 tiles as long as 512).  K is cut where a shorter last round saves more than the partial sums
+  // cost (written and read once at about 4.5 TB/s, 5 us for the second launch; a tile takes 0.436 us per gate and 128
+  // bytes of K).  TreeLSTM, H = 1,024, us a level before -> now: 257 rows 125 -> 99, 557 rows 183 -> 137, 1,062 rows
+  // 331 -> 246, 2,112 rows 500 -> 461 (256 trees of 64 leaves: 4.92 -> 4.63 ms); no level of H = 64 .. 2,048 and 150 ..
+  // 19,200 rows got slower.  Whole row tiles are counted, so that levels of up to 128 rows split alike.  Under 96 tiles
+  // the rule below is better (H = 256, 900 leaves: 20 us against 25), and for one gate, whose tiles share a compute
+  // unit (H = 512, 900 rows: 22 against 30).
+  if (can_split && esize == 4 && gates > 1 && nst >= 4 && base >= 96) {
+    const double tile = 0.436 * gates * nst, part = (double)((rows + 127) / 128 * 128) * gates * HP * 8 / 4.5e6;
+    double best = 0;
+    for (int ks = 1; ks <= std::min(8, nst / 2); ++ks) {
+      const double cost = (double)((base * ks + 255) / 256) * ((nst + ks - 1) / ks) / nst * tile +
+                          (ks > 1 ? part * ks + 5.0 : 0.0);
+      if (ks == 1 || cost < 0.95 * best) {
+        best = cost;
+        p.ksplit = ks;
+      }
+    }
+    return p;
+  }
   if (can_split && base < 192 && nst >= 4) {
     // aim at a workgroup per compute unit; a bf16 group alone with a short K (under 16 stages of 128 bytes) at
     // half of that: its slices are short, and the partial sums cost more than the extra workgroups gain
