@@ -2,10 +2,9 @@
 // scheduling algorithm), gfx950.
 //
 //   validate   CSR structure, op ids, arity, child range / same graph, inputs
-//   depth      one workgroup per graph runs Kahn's algorithm bottom-up over the
-//              graph's reverse edges in LDS: a node whose children are all done
-//              gets depth 1 + max(child depths) (the zero state -1 and leaf-table
-//              rows are depth-0 constants).  Unprocessed nodes mean a cycle.
+//   depth      one workgroup per graph walks it bottom-up along the reverse edges in LDS: the thread that closes a
+//              node's last child goes on with that node, at depth 1 + max(child depths) (the zero state -1 and
+//              leaf-table rows are depth-0 constants).  Nodes never closed mean a cycle.
 //   sort       stable LSD radix sort (10-bit digits) of the node ids by the key (depth - 1) * num_ops + op: ties stay in
 //              node-id order.  A pass is a count and a scatter over tiles of 2,048 items (a column scan between them
 //              only where there are many tiles)
@@ -121,8 +120,8 @@ __global__ void k_node_graph(const int* gp, int* node_graph, const unsigned long
 // parent and goes on with it, so a chain runs in one lane from step to step with no barrier and no queue.  What
 // bounds it is the chain of dependent LDS accesses per step (the parent link, then one returning atomic); a
 // level-synchronous frontier paid two barriers, a queue and generic-address atomics per level instead (4,096 graphs,
-// 2.0 M nodes, 511-node chains among them: 700 us, now 182; 1,024 sentiment trees: 101 us, now 26; 512 LSTM chains of up to 100 steps
-// under reduce trees: 75 us, now 64).
+// 2.0 M nodes, 511-node chains among them: 700 us, now 182; 1,024 sentiment trees: 101 us, now 26; 512 LSTM chains of
+// up to 100 steps under reduce trees: 75 us, now 64).
 // Parents of a node are a linked list of its edges; a node with one parent keeps that parent's number itself.  A lane
 // that finishes several parents at once goes on with the lowest (the nearest one up a chain, where nodes are numbered
 // children first) and puts the others on a list, which the next round takes.
@@ -1062,8 +1061,9 @@ __global__ void k_finish(const unsigned long long* err, const int* meta, const i
 // ---------------------------------------------------------------- a small batch in one launch
 // A batch of up to 4,096 nodes is a chain of launches with almost no work in them (17, about 60 us), so one workgroup
 // does all of it in LDS: the same steps as above, with barriers for launches (152 nodes in one kernel of 27 us, the
-// schedule and the forward of eight levels 112 -> 90 us; 2,322 nodes in 45 us, with fourteen levels 222 -> 196).  It is bound by those barriers and the dependent LDS and memory accesses between them;
-// past 4,096 nodes (or 8,192 edges or graphs) the arrays no longer fit and one compute unit is too few.
+// schedule and the forward of eight levels 112 -> 90 us; 2,322 nodes in 45 us, with fourteen levels 222 -> 196).  It is
+// bound by those barriers and the dependent LDS and memory accesses between them; past 4,096 nodes (or 8,192 edges or
+// graphs) the arrays no longer fit and one compute unit is too few.
 constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / kWave;
 constexpr int kSmallNodes = 4096, kSmallEdges = 8192;
 
