@@ -134,3 +134,31 @@ def test_schedules_from_several_threads():
     for t in threads:
         t.join()
     assert not failed, failed
+
+
+def test_schedule_freed_while_another_thread_captures():
+    """A schedule freed by one thread while another records a stream: the recording ends well and replays, and a schedule
+    made afterwards is whole."""
+    import threading
+    import torch
+    from paper_1702_02181_amd import fold as F
+    w = _chains(np.random.default_rng(3), 700, 12, 3)
+    i32 = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.int32)).cuda()
+    sched = F.Schedule(i32(w.graph_ptr), i32(w.node_op), i32(w.child_ptr), i32(w.child_idx), i32(w.node_input),
+                       [(o.kind, o.arity, o.has_input, o.param_set) for o in w.ops], w.leaf_table.shape[0])
+    x, y = torch.arange(64, dtype=torch.float32, device="cuda"), torch.zeros(64, device="cuda")
+    torch.cuda.synchronize()
+
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, capture_error_mode="thread_local"):
+        torch.mul(x, 2, out=y)
+        t = threading.Thread(target=sched.__del__)
+        t.start()
+        t.join()
+    assert sched.handle is None
+    for k in range(3):
+        y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, 2 * x), k
+        C.assert_schedule_equal(_gpu_sched(w), C.oracle_schedule(w))
