@@ -115,17 +115,29 @@ struct NarrowPlan {
 // replaces that of two; past it the operands are read again for every 16 or 32 rows and the 128-row tiles win (us per
 // Tree-LSTM level, 128-row tiles / narrow, event overhead of 5 us in both: bf16 H = 300 1 row 11.9 / 8.3, 64 rows 13.8 /
 // 9.9; H = 512 256 rows 22.0 / 14.4, 512 rows 22.3 / 24.7; H = 768 128 rows 19.7 / 17.7, 192 rows 20.6 / 30.5; fp32 H = 256
-// 64 rows 16.6 / 11.7, 512 rows 23.4 / 21.0; H = 1,024 1 row 34.0 / 16.1, 64 rows 36.2 / 34.5).  fp32 multiplies a quarter of
-// the bf16 K a cycle, so past 64 rows only a short K stays bound by latency (H = 512: 128 rows 25.1 / 26.9).  bf16 takes
-// single row tiles up to 48 rows (H = 300, 48 rows: 9.1 against 9.7 us; 64 rows: 13.5 against 9.9), fp32 wherever they
+// 64 rows 16.6 / 11.7, 512 rows 23.4 / 21.0; H = 1,024 1 row 34.0 / 16.1, 64 rows 36.2 / 34.5).
+//
+// Up to 128 rows the width alone decides, neither the rows nor the operation's K: a graph's level sums K in one order
+// whatever the batch puts beside it, so its states have the same bits alone and in any batch whose levels stay at 128
+// rows.  (The order does not depend on rt or units.)  Widths up to 1,024 are narrow: four row tiles of 32 fit the round.
+// fp32 with a long K pays for that above 64 rows (H = 300: 96 rows 20.6 / 14.8; H = 512: 96 rows 25.2 / 26.3; H = 768: 65
+// rows 29.9 / 27.5, 128 rows 32.2 / 39.4; H = 1,024: 65 rows 37.7 / 47.1, 128 rows 40.4 / 47.9) and gains more below.
+// Wider ones are not: their 128 rows take two rounds and more (bf16 H = 2,048: 1 row 29.1 / 19.6, 128 rows 34.5 / 61.9; fp32
+// 1 row 99 / 33, 128 rows 104 / 152; bf16 H = 4,096: 128 rows 119 / 221).
+//
+// Past 128 rows fp32 stays narrow with a short K: it multiplies a quarter of the bf16 K a cycle.  bf16 takes single row
+// tiles up to 48 rows (H = 300, 48 rows: 9.1 against 9.7 us; 64 rows: 13.5 against 9.9), fp32 wherever they
 // still fit the round (H = 256, 64 rows: 11.7 against 13.7).  Fewer units a workgroup while all still fit it: more
 // compute units share the weights (fp32 H = 1,024, 1 row: 8 units 20.9, 4 units 16.1).
 constexpr int kNarrowRows = 512, kNarrowRound = 256;
+constexpr int kOneOrderRows = 128, kOneOrderWidth = 1024;
+static_assert(kOneOrderRows / 32 * (kOneOrderWidth / 16) <= kNarrowRound, "every level of kOneOrderRows fits the round");
 inline NarrowPlan narrow_fwd_plan(int rows, int HP, int K, int esize) {
   NarrowPlan p;
-  if (rows <= 0 || rows > kNarrowRows || (esize == 4 && K > 512 && rows > 64)) return p;
+  if (rows <= 0 || rows > kNarrowRows) return p;
+  if (rows <= kOneOrderRows ? HP > kOneOrderWidth : esize == 4 && K > 512) return p;
   const int t1 = (rows + 15) / 16, t2 = (rows + 31) / 32;
-  const bool single = esize == 4 ? t1 * (HP / 16) <= kNarrowRound : rows <= 48;
+  const bool single = (esize == 4 || rows <= 48) && t1 * (HP / 16) <= kNarrowRound;
   const int tiles = single ? t1 : t2;
   if (tiles * (HP / 16) > kNarrowRound) return p;
   p.rt = single ? 1 : 2;
