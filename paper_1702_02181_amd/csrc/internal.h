@@ -129,7 +129,7 @@ struct NarrowPlan {
 // tiles up to 48 rows (H = 300, 48 rows: 9.1 against 9.7 us; 64 rows: 13.5 against 9.9), fp32 wherever they
 // still fit the round (H = 256, 64 rows: 11.7 against 13.7).  Fewer units a workgroup while all still fit it: more
 // compute units share the weights (fp32 H = 1,024, 1 row: 8 units 20.9, 4 units 16.1).
-constexpr int kNarrowRows = 512, kNarrowRound = 256;
+constexpr int kNarrowRows = 512, kNarrowRound = 256, kNarrowLongK = 512;
 constexpr int kOneOrderRows = 128, kOneOrderWidth = 1024;
 static_assert(kOneOrderRows / 32 * (kOneOrderWidth / 16) <= kNarrowRound, "every level of kOneOrderRows fits the round");
 // Workgroups of a grid of R row tiles x C column tiles, counted as the XCDs take them: each owns C / 8 columns, rounded up
@@ -140,7 +140,7 @@ inline long long narrow_round(long long R, int C) { return R * ((C + 7) / 8 * 8)
 inline NarrowPlan narrow_fwd_plan(int rows, int HP, int K, int esize) {
   NarrowPlan p;
   if (rows <= 0 || rows > kNarrowRows) return p;
-  if (rows <= kOneOrderRows ? HP > kOneOrderWidth : esize == 4 && K > 512) return p;
+  if (rows <= kOneOrderRows ? HP > kOneOrderWidth : esize == 4 && K > kNarrowLongK) return p;
   const int t1 = (rows + 15) / 16, t2 = (rows + 31) / 32;
   const bool single = (esize == 4 || rows <= 48) && narrow_round(t1, HP / 16) <= kNarrowRound;
   const int tiles = single ? t1 : t2;
