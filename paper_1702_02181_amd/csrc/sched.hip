@@ -130,7 +130,16 @@ __global__ void k_node_graph(const int* gp, int* node_graph, const unsigned long
 // memory; what atomics write is read through atomics there, past the first-level cache).  ARITY2: at most two
 // children, and one atomic both counts a child in and hands over its depth (count in the top byte, the depths summed
 // below it: the second child reads the first one's); otherwise a maximum and a count.
-constexpr int kGraphThreads = 128;
+//
+// Threads of a workgroup, by the nodes of an average graph.  A walk is one lane's chain, but linking and checking go node
+// by node: a graph of 100,000 nodes takes 3,434 us with 128 threads, 1,921 with 256, 694 with 1,024 (8 of 10,000: 408, 275,
+// 156).  Graphs of a few hundred nodes fit the LDS and take the same with any (4,096 of 511: 327, 320, 335), and many tiny
+// ones are bound by starting waves (100,000 of one node: 214, 254, 810).  A large graph among small ones gets 256 (20,000
+// nodes among 1,000 graphs of 20: within 3 % of 1,024, the chains take the time).
+inline int graph_threads(long long N, int G) {
+  const long long mean = N / std::max(G, 1);
+  return mean >= 1024 ? 1024 : (mean >= 16 ? 256 : 128);
+}
 
 // Parent edges of v, once all are linked; a single one is replaced by its parent's number.
 template <class L>
@@ -399,8 +408,8 @@ __device__ __forceinline__ void run_graph(const L& g, const GraphArgs& a, const 
 
 // The pointer arrays have been checked.  CHECK (fold batches, at most two children): the nodes are checked here;
 // without it their children have been checked too.  lds_bytes: dynamic LDS for the links.
-template <bool CHECK>
-__global__ __launch_bounds__(kGraphThreads) void k_graph_depth(GraphArgs a, OpTable ops, int lds_bytes) {
+template <bool CHECK, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_graph_depth(GraphArgs a, OpTable ops, int lds_bytes) {
   if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 8 == 0) return;  // a pointer array
   if (!CHECK && *a.err != kNoErr) return;
   extern __shared__ __attribute__((aligned(16))) char links[];
@@ -419,11 +428,20 @@ __global__ __launch_bounds__(kGraphThreads) void k_graph_depth(GraphArgs a, OpTa
                          n, e0, e);
 }
 
+template <bool CHECK>
+void launch_graph_depth(const GraphArgs& a, const OpTable& ops, long long N, int G, int lds_bytes, hipStream_t st) {
+  switch (graph_threads(N, G)) {
+    case 128: hipLaunchKernelGGL((k_graph_depth<CHECK, 128>), dim3(G), dim3(128), lds_bytes, st, a, ops, lds_bytes); break;
+    case 256: hipLaunchKernelGGL((k_graph_depth<CHECK, 256>), dim3(G), dim3(256), lds_bytes, st, a, ops, lds_bytes); break;
+    default: hipLaunchKernelGGL((k_graph_depth<CHECK, 1024>), dim3(G), dim3(1024), lds_bytes, st, a, ops, lds_bytes); break;
+  }
+}
+
 // LDS for the links of a graph: twice what an average graph takes, at least what a tree of 1,000 nodes takes (eleven
 // such workgroups fit a compute unit) and at most 60 KB; larger graphs use scratch memory
 inline int graph_lds_bytes(long long N, long long E, int G, int node_bytes, int edge_bytes) {
   const long long mean = (N * node_bytes + E * edge_bytes) / std::max(G, 1);
-  return (int)std::min<long long>(61440, std::max<long long>(1000 * (node_bytes + edge_bytes), 2 * mean + 255) / 256 * 256);
+  return (int)std::min<long long>(61440, (std::max<long long>(1000 * (node_bytes + edge_bytes), 2 * mean) + 255) / 256 * 256);
 }
 
 // ---------------------------------------------------------------- device-wide exclusive scan
@@ -1686,7 +1704,7 @@ int32_t schedule_impl(const fold_batch* b, hipStream_t st, fold_sched** out) {
         const int lds = graph_lds_bytes(N, E, G, LdsLinks<true>::kNodeBytes, LdsLinks<true>::kEdgeBytes);
         const GraphArgs ga{b->graph_ptr, b->child_ptr, b->child_idx, s.depth, indeg, scratch, err, &em->cycle, meta,
                            b->node_op, b->node_input, b->num_inputs};
-        hipLaunchKernelGGL(k_graph_depth<true>, dim3(G), dim3(kGraphThreads), lds, st, ga, ops, lds);
+        launch_graph_depth<true>(ga, ops, N, G, lds, st);
       }
 
       // sort by (depth - 1) * num_ops + op: as many passes as N * num_ops keys could need are launched; those the actual
@@ -2197,7 +2215,7 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
       const int lds = graph_lds_bytes(N, E, G, LdsLinks<false>::kNodeBytes, LdsLinks<false>::kEdgeBytes);
       const GraphArgs ga{b->graph_ptr, b->in_ptr, b->in_node, kdepth, indeg, scratch, err, err, meta, nullptr, nullptr,
                          0};
-      hipLaunchKernelGGL(k_graph_depth<false>, dim3(G), dim3(kGraphThreads), lds, st, ga, OpTable{}, lds);
+      launch_graph_depth<false>(ga, OpTable{}, N, G, lds, st);
     }
     hipLaunchKernelGGL(k_typed_nodes, grid_for(N), dim3(kBlock), 0, st, kdepth, b->node_op, N, ops, depth, nout_v,
                        last, meta, err);
