@@ -29,6 +29,7 @@ struct Pools {
   std::map<int, DevicePool> device;
   std::map<void*, size_t> handed_out;
   std::vector<int*> stages;
+  Pools() { stages.reserve(kIdleStages); }
 };
 
 // never destroyed: no HIP call is made after the runtime's own shutdown
@@ -44,72 +45,96 @@ size_t size_class(size_t bytes) {
 }
 
 // takes the oldest idle blocks past `keep` bytes out of the pool
-std::vector<void*> trim(DevicePool& d, size_t keep) {
-  std::vector<void*> out;
-  while (d.idle_bytes > keep) {
-    out.push_back(d.idle.front().ptr);
-    d.idle_bytes -= d.idle.front().bytes;
-    d.idle.erase(d.idle.begin());
-  }
+std::vector<Idle> trim(DevicePool& d, size_t keep) {
+  size_t n = 0, left = d.idle_bytes;
+  while (left > keep) left -= d.idle[n++].bytes;
+  std::vector<Idle> out(d.idle.begin(), d.idle.begin() + n);
+  d.idle.erase(d.idle.begin(), d.idle.begin() + n);
+  d.idle_bytes = left;
   return out;
 }
 
-void release(const std::vector<void*>& blocks) {
-  for (void* p : blocks) (void)hipFree(p);
+size_t release(const std::vector<Idle>& blocks) {
+  size_t bytes = 0;
+  for (const Idle& b : blocks) {
+    bytes += b.bytes;
+    (void)hipFree(b.ptr);
+  }
+  return bytes;
+}
+
+// a block of a class that is idle, or NULL
+void* take(int device, size_t size, bool lasting) {
+  Pools& P = pools();
+  std::lock_guard<std::mutex> lk(P.mu);
+  DevicePool& d = P.device[device];
+  for (size_t i = d.idle.size(); i-- > 0;) {  // the last one given back first
+    if (d.idle[i].bytes != size) continue;
+    void* p = d.idle[i].ptr;
+    P.handed_out[p] = size;
+    d.idle_bytes -= size;
+    d.idle.erase(d.idle.begin() + i);
+    d.alive += lasting;
+    return p;
+  }
+  return nullptr;
+}
+
+void* device_alloc(size_t size) {
+  void* p = nullptr;
+  if (hipMalloc(&p, size) == hipSuccess) return p;
+  (void)hipGetLastError();
+  return nullptr;
 }
 
 }  // namespace
 
-void* pool_alloc(int device, size_t bytes, bool lasting) {
-  Pools& P = pools();
+void* pool_alloc(int device, size_t bytes, bool lasting) noexcept {
   const size_t size = size_class(bytes);
-  std::vector<void*> drop;
-  {
-    std::lock_guard<std::mutex> lk(P.mu);
-    DevicePool& d = P.device[device];
-    for (size_t i = d.idle.size(); i-- > 0;) {  // the last one given back first
-      if (d.idle[i].bytes != size) continue;
-      void* p = d.idle[i].ptr;
-      P.handed_out[p] = size;
-      d.idle_bytes -= size;
-      d.idle.erase(d.idle.begin() + i);
-      d.alive += lasting;
-      return p;
-    }
-  }
   void* p = nullptr;
-  if (hipMalloc(&p, size) != hipSuccess) {
-    (void)hipGetLastError();
-    {
-      std::lock_guard<std::mutex> lk(P.mu);
-      drop = trim(P.device[device], 0);
+  try {
+    Pools& P = pools();
+    if ((p = take(device, size, lasting))) return p;
+    p = device_alloc(size);
+    if (!p) {
+      std::vector<Idle> drop;
+      {
+        std::lock_guard<std::mutex> lk(P.mu);
+        drop = trim(P.device[device], 0);
+      }
+      release(drop);
+      p = device_alloc(size);
     }
-    release(drop);
-    if (hipMalloc(&p, size) != hipSuccess) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
+    if (!p) return nullptr;
+    std::lock_guard<std::mutex> lk(P.mu);
+    P.handed_out[p] = size;
+    P.device[device].alive += lasting;
+    return p;
+  } catch (...) {  // no host memory for the pool's own lists
+    if (p) (void)hipFree(p);
+    return nullptr;
   }
-  std::lock_guard<std::mutex> lk(P.mu);
-  P.handed_out[p] = size;
-  P.device[device].alive += lasting;
-  return p;
 }
 
-void pool_free(int device, void* ptr, bool lasting) {
+void pool_free(int device, void* ptr, bool lasting) noexcept {
   if (!ptr) return;
   Pools& P = pools();
-  std::vector<void*> drop;
-  {
+  std::vector<Idle> drop;
+  bool kept = false;
+  try {
     std::lock_guard<std::mutex> lk(P.mu);
     DevicePool& d = P.device[device];
     auto it = P.handed_out.find(ptr);
     if (it == P.handed_out.end()) return;
-    d.idle.push_back({ptr, it->second});
-    d.idle_bytes += it->second;
+    const size_t size = it->second;
     P.handed_out.erase(it);
     d.alive -= lasting;
+    d.idle.push_back({ptr, size});
+    d.idle_bytes += size;
+    kept = true;
     drop = trim(d, d.alive > 0 ? kIdleBytes : kIdleBytesUnused);
+  } catch (...) {
+    if (!kept) (void)hipFree(ptr);
   }
   release(drop);
 }
@@ -123,7 +148,7 @@ static bool wait_for_device() {
   return hipMalloc(&p, 256) == hipSuccess && hipFree(p) == hipSuccess;
 }
 
-void pool_free_after_wait(int device, void* ptr) {
+void pool_free_after_wait(int device, void* ptr) noexcept {
   if (!ptr) return;
   int current = device;
   (void)hipGetDevice(&current);
@@ -137,14 +162,15 @@ void pool_free_after_wait(int device, void* ptr) {
       Pools& P = pools();
       std::lock_guard<std::mutex> lk(P.mu);
       P.handed_out.erase(ptr);
-      P.device[device].alive -= 1;
+      auto d = P.device.find(device);
+      if (d != P.device.end()) d->second.alive -= 1;
     }
     (void)hipFree(ptr);
   }
   if (current != device) (void)hipSetDevice(current);
 }
 
-int* stage_alloc() {
+int* stage_alloc() noexcept {
   Pools& P = pools();
   {
     std::lock_guard<std::mutex> lk(P.mu);
@@ -162,12 +188,12 @@ int* stage_alloc() {
   return static_cast<int*>(p);
 }
 
-void stage_free(int* p) {
+void stage_free(int* p) noexcept {
   if (!p) return;
   Pools& P = pools();
   {
     std::lock_guard<std::mutex> lk(P.mu);
-    if ((int)P.stages.size() < kIdleStages) {
+    if (P.stages.size() < P.stages.capacity() && P.stages.size() < (size_t)kIdleStages) {
       P.stages.push_back(p);
       return;
     }
