@@ -175,7 +175,18 @@ typedef struct {
  * fold_sched_free; on error *out is NULL. */
 int32_t fold_schedule(const fold_batch* batch, hipStream_t stream, fold_sched** out);
 int32_t fold_sched_get_info(const fold_sched* sched, fold_sched_info* out);
+/* Waits until the device has finished everything queued on it (as hipFree
+ * does), on every stream.  The schedule's device memory then stays with the
+ * library for the next schedule: at most 1 GiB per device while any schedule
+ * lives there (temporaries included), 256 MiB otherwise.  The library gives
+ * it up by itself only when an allocation of its own fails; fold_trim gives
+ * it to other allocators of the process. */
 int32_t fold_sched_free(fold_sched* sched);
+/* Gives back to the system all memory that the library keeps idle between
+ * schedules, on every device, and its idle pinned buffers; schedules that
+ * live are not touched.  Waits for the devices concerned.  *bytes (may be
+ * NULL): the device memory given back. */
+int32_t fold_trim(size_t* bytes);
 
 /* ---- the paper's own form of the schedule ---------------------------------
  * Section 2 schedules a typed DAG: source nodes are constants of a tensor
@@ -261,6 +272,7 @@ typedef struct {
  * `stream` twice: once to size the pass-through arrays, once at the end. */
 int32_t fold_schedule_typed(const fold_typed_batch* batch, hipStream_t stream, fold_typed_sched** out);
 int32_t fold_typed_sched_get_info(const fold_typed_sched* sched, fold_typed_sched_info* out);
+/* Waits and keeps memory as fold_sched_free. */
 int32_t fold_typed_sched_free(fold_typed_sched* sched);
 
 

@@ -15,6 +15,7 @@
 
 #include "common.h"
 #include "internal.h"
+#include "pool.h"
 
 namespace fold {
 
@@ -1066,6 +1067,12 @@ int32_t fold_sched_free(fold_sched* h) {
   sched_destroy_impl(h);
   return FOLD_OK;
   FOLD_GUARD_END
+}
+
+int32_t fold_trim(size_t* bytes) {
+  const size_t n = pool_trim();
+  if (bytes) *bytes = n;
+  return FOLD_OK;
 }
 
 int32_t fold_schedule_typed(const fold_typed_batch* b, hipStream_t st, fold_typed_sched** out) {

@@ -4,7 +4,7 @@
 // up to milliseconds for the 0.2 GB of a 2 M-node one), and a copy into pageable memory goes through a staging buffer.
 // Blocks are handed out whole by size class (four to a power of two, so at most a quarter is unused), under one lock,
 // to any thread; a block comes back only when the GPU has finished with it.  At most kIdleBytes per device stay idle,
-// kIdleBytesUnused once no schedule is alive there, and none when an allocation of the pool's own fails
+// kIdleBytesUnused once no schedule is alive there, and none after pool_trim or when an allocation of the pool's own fails
 // for want of memory.  Nothing here throws: what cannot be kept for want of host memory is given back at once.
 #pragma once
 
@@ -21,6 +21,8 @@ void* pool_alloc(int device, size_t bytes, bool lasting) noexcept;
 void pool_free(int device, void* ptr, bool lasting) noexcept;
 // Waits for the device (as hipFree would), then gives a lasting block back.
 void pool_free_after_wait(int device, void* ptr) noexcept;
+// Gives every idle block and read-back buffer of all devices back to the system; returns the device bytes.
+size_t pool_trim() noexcept;
 
 // A pinned host buffer of kStageInts ints that kernels write, or NULL; at most kIdleStages stay idle.
 constexpr size_t kStageInts = 33536;

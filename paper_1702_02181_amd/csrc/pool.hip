@@ -139,6 +139,25 @@ void pool_free(int device, void* ptr, bool lasting) noexcept {
   release(drop);
 }
 
+size_t pool_trim() noexcept {
+  std::vector<std::vector<Idle>> drop;
+  int* stages[kIdleStages];
+  int n = 0;
+  try {
+    Pools& P = pools();
+    std::lock_guard<std::mutex> lk(P.mu);
+    drop.reserve(P.device.size());
+    for (auto& d : P.device) drop.push_back(trim(d.second, 0));
+    for (int* p : P.stages) stages[n++] = p;
+    P.stages.clear();
+  } catch (...) {  // no host memory for the lists: what was not taken stays idle
+  }
+  size_t bytes = 0;
+  for (const auto& blocks : drop) bytes += release(blocks);
+  while (n > 0) (void)hipHostFree(stages[--n]);
+  return bytes;
+}
+
 // Waits for everything on the current device by freeing a small allocation.  hipDeviceSynchronize would do, but where
 // another thread records a stream (a graph of its own, a framework's) it fails and breaks that recording; hipFree, which
 // gave the schedules' arrays back before there was a pool, does not.  It costs 13 to 21 us more a schedule (84 ->

@@ -6,7 +6,7 @@ PyTorch provides device memory (``tensor.data_ptr()``) and streams
 binding raises -- there is no fallback.
 
 The functions keep the ABI's names:
-    fold_schedule, fold_sched_get_info, fold_sched_free,
+    fold_schedule, fold_sched_get_info, fold_sched_free, fold_trim,
     fold_pack_params, fold_packed_free, fold_workspace_size,
     fold_forward, fold_backward, fold_row_ld, fold_last_error,
     fold_graph_create, fold_graph_launch, fold_graph_num_nodes, fold_graph_free
@@ -139,7 +139,7 @@ EXPORTS = ["fold_schedule", "fold_sched_get_info", "fold_sched_free", "fold_pack
            "fold_graph_num_nodes", "fold_graph_free", "fold_pack_update", "fold_loss_softmax_ce",
            "fold_loss_workspace_size", "fold_adam_step", "fold_forward_dropout", "fold_backward_dropout",
            "fold_dropout_mask", "fold_forward_noalloc", "fold_schedule_typed", "fold_typed_sched_get_info",
-           "fold_typed_sched_free", "fold_level_launches"]
+           "fold_typed_sched_free", "fold_level_launches", "fold_trim"]
 
 _lib = None
 
@@ -165,6 +165,8 @@ def lib():
     L.fold_sched_get_info.argtypes = [c_void_p, POINTER(fold_sched_info)]
     L.fold_sched_free.restype = c_int32
     L.fold_sched_free.argtypes = [c_void_p]
+    L.fold_trim.restype = c_int32
+    L.fold_trim.argtypes = [POINTER(c_size_t)]
     L.fold_pack_params.restype = c_int32
     L.fold_pack_params.argtypes = [POINTER(fold_params), c_void_p, POINTER(c_void_p)]
     L.fold_packed_free.restype = c_int32
@@ -315,6 +317,14 @@ def fold_sched_get_info(handle) -> fold_sched_info:
 
 def fold_sched_free(handle):
     _check(lib().fold_sched_free(handle))
+
+
+def fold_trim() -> int:
+    """Give back the device memory that the library keeps between schedules; the bytes given back.  (PyTorch's allocator
+    cannot reclaim it by itself.)"""
+    n = c_size_t()
+    _check(lib().fold_trim(byref(n)))
+    return int(n.value)
 
 
 def fold_pack_params(params: fold_params, stream=None) -> c_void_p:

@@ -130,17 +130,30 @@ int main(int, char** argv) {
       });
     for (auto& x : t) x.join();
     CHECK(device_bytes <= kIdleBytesUnused && pinned.size() <= kIdleStages);
-  }
+  }TRIM
   std::puts("ok");
   return 0;
 }
 '''
+TRIM = r''' else if (what == "trim") {  // every device's idle blocks and the buffers go back, those handed out stay
+    void* a = pool_alloc(0, 8 * MB, true);
+    void* b = pool_alloc(1, 16 * MB, false);
+    void* c = pool_alloc(0, 32 * MB, false);
+    int* s = stage_alloc();
+    stage_free(s);
+    pool_free(1, b, false);
+    pool_free(0, c, false);
+    CHECK(pool_trim() == 48 * MB && live.size() == 1 && live.count(a) && pinned.empty());
+    CHECK(pool_trim() == 0);
+    pool_free_after_wait(0, a);
+    CHECK(pool_trim() == 8 * MB && live.empty());
+  }'''
 
 
 @pytest.fixture(scope="module")
 def program(tmp_path_factory):
     d = tmp_path_factory.mktemp("pool")
-    (d / "stub.cpp").write_text(STUB)
+    (d / "stub.cpp").write_text(STUB.replace("TRIM", TRIM))
     src = os.path.join(B.CSRC, "pool.hip")
     cxx = shutil.which("g++")
     if cxx is None or not os.path.exists("/opt/rocm/include/hip/hip_runtime_api.h"):
@@ -151,7 +164,7 @@ def program(tmp_path_factory):
     return str(d / "pool")
 
 
-@pytest.mark.parametrize("what", ["reuse", "bounds", "out of memory", "host memory", "threads"])
+@pytest.mark.parametrize("what", ["reuse", "bounds", "out of memory", "host memory", "threads", "trim"])
 def test_pool(program, what):
     r = subprocess.run([program, what], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr[-500:])
