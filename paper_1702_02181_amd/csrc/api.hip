@@ -193,46 +193,54 @@ WsLayout workspace_layout(const Sched& s, const Packed& p) {
   auto al = [](size_t x) { return (x + 255) / 256 * 256; };
   w.gates_off = 0;
   w.gates_bytes = al(N * w.gstride * sizeof(float));
-  // the forward's launches and the partial sums each K-split group needs (a level launch's groups side by side)
-  size_t zp = 0, run = 0;
-  int nb = 0, in_batch = 0, prev_level = -1;
+  // the forward's launches and the partial sums each K-split group needs (a level launch's groups side by side; none where
+  // the launch, and with it every group of it alone, runs on narrow tiles)
+  size_t zp = 0;
+  int nb = 0, prev_level = -1;
+  const int esize = p.dtype == FOLD_BF16 ? 2 : 4;
   w.batch.assign(s.num_groups, -1);
   w.zoff.assign(s.num_groups, 0);
   w.zneed.assign(s.num_groups, 0);
+  std::vector<FwdGroup> batch;
+  int first = 0;  // group of batch[0]: a batch's groups are consecutive
+  auto close = [&]() {
+    const int n = (int)batch.size();
+    if (n == 0) return;
+    const bool narrow = n == 1 ? narrow_fwd_plan(batch[0].rows, p.HP, batch[0].K, esize).rt > 0
+                               : level_narrow_plan(batch.data(), n, p.HP, esize).rt > 0;
+    size_t run = 0;
+    for (int g = first; g < first + n; ++g) {
+      if (narrow) w.zneed[g] = 0;
+      w.zoff[g] = run;
+      run += w.zneed[g];
+    }
+    zp = std::max(zp, run);
+    batch.clear();
+    ++nb;
+  };
   for (int g = 0; g < s.num_groups; ++g) {
     const fold_op& op = s.ops[s.h_op[g]];
-    const bool new_level = s.h_level[g] != prev_level;
+    if (s.h_level[g] != prev_level || (int)batch.size() == kMaxMerge) close();
     prev_level = s.h_level[g];
-    if (new_level || in_batch == kMaxMerge) {
-      if (in_batch > 0) ++nb;
-      in_batch = 0;
-      run = 0;
-    }
     if (op.kind == FOLD_EMBED || is_attn(op.kind) || op.param_set >= (int)p.sets.size()) {
-      if (in_batch > 0) ++nb;
-      in_batch = 0;
-      run = 0;
+      close();
       continue;
     }
     const PackedSet& ps = p.sets[op.param_set];
     const int gates = is_tree_lstm_leaf(op) ? gates_of(kTreeLstmLeaf) : ps.G;
-    const FwdPlan pl = fwd_plan(s.h_rows[g], p.HP, op.has_input ? ps.INP : 0, op.arity, gates,
-                                p.dtype == FOLD_BF16 ? 2 : 4, true);
-    const size_t need = pl.ksplit > 1 ? (size_t)pl.ksplit * s.h_rows[g] * ps.G * p.HP : 0;
-    w.zneed[g] = need;
+    const int inp = op.has_input ? ps.INP : 0;
+    const FwdPlan pl = fwd_plan(s.h_rows[g], p.HP, inp, op.arity, gates, esize, true);
+    w.zneed[g] = pl.ksplit > 1 ? (size_t)pl.ksplit * s.h_rows[g] * ps.G * p.HP : 0;
     if (pl.wide) {
-      if (in_batch > 0) ++nb;
-      in_batch = 0;
-      run = 0;
-      zp = std::max(zp, need);
+      close();
+      zp = std::max(zp, w.zneed[g]);
       continue;
     }
+    if (batch.empty()) first = g;
     w.batch[g] = nb;
-    w.zoff[g] = run;
-    run += need;
-    ++in_batch;
-    zp = std::max(zp, run);
+    batch.push_back({s.h_rows[g], inp + op.arity * p.HP, gates});
   }
+  close();
   w.zpart_off = w.gates_bytes;
   w.zpart_bytes = al(zp * sizeof(float));
   w.dh_off = w.zpart_off + w.zpart_bytes;

@@ -1570,51 +1570,7 @@ void launch_bwd_dx(int dtype, const DxArgs& a0, hipStream_t st, const char* name
 
 constexpr long long kLevelFwdWorkgroups = 256;  // the K-split forward of a level launch aims at this grid
 
-// The tile with which a level's groups run narrow as one launch, if they do: every group would alone, and the workgroups of
-// 16 units of the cells with several gates fit one round (those of one gate are over in a fraction of it).  bf16, three
-// groups a level, us with 5 us event overhead, 128-row tiles and epilogues / narrow, by those workgroups: H = 512 224
-// 18.6 / 14.2, 256 19.9 / 15.8, 288 20.2 / 21.6; H = 768 240 20.6 / 17.8, 288 21.0 / 25.0; H = 1,024 256 27.2 / 20.5, 320
-// 27.4 / 29.7; fp32 H = 256 272 26.0 / 30.5.  bf16 under a width of 512 still gains in a second round (H = 300 264 19.1 /
-// 17.4, 384 20.5 / 19.4), up to 400 workgroups of all groups.  Single row tiles up to 48 rows, but only where they fit
-// that round (H = 768, 97 rows in three groups: 336 of them 22.4, 240 double ones 17.7); with fp32 too: past 48 rows double
-// tiles leave the workgroups fewer units each (H = 64, 525 rows: 12.2 against 14.8).
-// A level of at most 128 rows always runs narrow (up to the width that narrow_fwd_plan takes), so that a group's arithmetic
-// is the same with and without the others.  In a higher one an fp32 group of more than 64 rows with a long K takes the
-// level off the narrow tiles (H = 400, 193 rows in three groups: 26.5 / 28.9).
-constexpr int kLevelNarrow = 400, kLevelNarrowWidth = 512;
-static NarrowPlan level_narrow_plan(const int* kinds, const FwdArgs* args, int n, int esize) {
-  NarrowPlan p;
-  int rows = 0, most = 0, HP = 0, gates = 0;
-  for (int k = 0; k < n; ++k) {
-    if (args[k].rows <= 0) continue;
-    rows += args[k].rows;
-    gates = std::max(gates, gates_of(kinds[k]));
-  }
-  long long long_ones[2] = {0, 0}, tiles[2] = {0, 0};  // by rt - 1
-  for (int k = 0; k < n; ++k) {
-    const FwdArgs& a = args[k];
-    if (a.rows <= 0) continue;
-    const int K = fwd_k(a);
-    if (!narrow_fwd_plan(a.rows, a.HP, K, esize).rt) return p;
-    if (rows > kOneOrderRows && esize == 4 && K > kNarrowLongK && a.rows > 64) return p;
-    HP = a.HP;
-    most = std::max(most, a.rows);
-    for (int i = 0; i < 2; ++i) {
-      const long long t = cdiv(a.rows, 16 * (i + 1));
-      tiles[i] += t;
-      if (gates == 1 || gates_of(kinds[k]) > 1) long_ones[i] += narrow_round(t, HP / 16);
-    }
-  }
-  if (rows == 0) return p;
-  const int i = most <= 48 && long_ones[0] <= kNarrowRound ? 0 : 1;
-  if (rows > kOneOrderRows && long_ones[i] > kNarrowRound &&
-      !(esize == 2 && HP < kLevelNarrowWidth && tiles[1] * (HP / 16) <= kLevelNarrow))
-    return p;
-  p.rt = i + 1;
-  p.units = tiles[i] * (HP / 4) <= kNarrowRound ? 4 : (tiles[i] * (HP / 8) <= kNarrowRound ? 8 : 16);
-  return p;
-}
-
+// the groups of a level on narrow tiles
 static void launch_level_fwd_n(int dtype, const int* kinds, const FwdArgs* args, int n, const NarrowPlan& plan,
                                hipStream_t st) {
   Merged<FwdArgs> m{};
@@ -1642,7 +1598,9 @@ static void launch_level_fwd_n(int dtype, const int* kinds, const FwdArgs* args,
 
 void launch_level_fwd(int dtype, const int* kinds, const FwdArgs* args, int n, hipStream_t st) {
   ProfScope prof(dtype == FOLD_BF16 ? "cell_fwd.level.bf16" : "cell_fwd.level.f32", st);
-  if (const NarrowPlan plan = level_narrow_plan(kinds, args, n, dtype == FOLD_BF16 ? 2 : 4); plan.rt) {
+  FwdGroup groups[kMaxMerge];
+  for (int k = 0; k < n; ++k) groups[k] = {args[k].rows, fwd_k(args[k]), gates_of(kinds[k])};
+  if (const NarrowPlan plan = level_narrow_plan(groups, n, n > 0 ? args[0].HP : 0, dtype == FOLD_BF16 ? 2 : 4); plan.rt) {
     launch_level_fwd_n(dtype, kinds, args, n, plan, st);
     return;
   }

@@ -29,7 +29,7 @@ struct WsLayout {
   // The forward's launches: batch[g] = the level launch group g belongs to (consecutive narrow groups of one
   // level, at most kMaxMerge to a launch), or -1 for a group launched alone (an embedding, a wide group).
   // Groups of one level launch run at once, so each has its own part of the K-split partial sums: zoff[g]
-  // (floats from the region's start) and zneed[g] (floats, 0 when it does not split).
+  // (floats from the region's start) and zneed[g] (floats, 0 when it does not split or the launch runs on narrow tiles).
   std::vector<int> batch;
   std::vector<size_t> zoff, zneed;
 };
@@ -147,6 +147,51 @@ inline NarrowPlan narrow_fwd_plan(int rows, int HP, int K, int esize) {
   if (narrow_round(tiles, HP / 16) > kNarrowRound) return p;
   p.rt = single ? 1 : 2;
   p.units = narrow_round(tiles, HP / 4) <= kNarrowRound ? 4 : (narrow_round(tiles, HP / 8) <= kNarrowRound ? 8 : 16);
+  return p;
+}
+
+// The tile with which a level's groups run narrow as one launch, if they do: every group would alone, and the workgroups of
+// 16 units of the cells with several gates fit one round (those of one gate are over in a fraction of it).  bf16, three
+// groups a level, us with 5 us event overhead, 128-row tiles and epilogues / narrow, by those workgroups: H = 512 224
+// 18.6 / 14.2, 256 19.9 / 15.8, 288 20.2 / 21.6; H = 768 240 20.6 / 17.8, 288 21.0 / 25.0; H = 1,024 256 27.2 / 20.5, 320
+// 27.4 / 29.7; fp32 H = 256 272 26.0 / 30.5.  bf16 under a width of 512 still gains in a second round (H = 300 264 19.1 /
+// 17.4, 384 20.5 / 19.4), up to 400 workgroups of all groups.  Single row tiles up to 48 rows, but only where they fit
+// that round (H = 768, 97 rows in three groups: 336 of them 22.4, 240 double ones 17.7); with fp32 too: past 48 rows double
+// tiles leave the workgroups fewer units each (H = 64, 525 rows: 12.2 against 14.8).
+// A level of at most 128 rows always runs narrow (up to the width that narrow_fwd_plan takes), so that a group's arithmetic
+// is the same with and without the others.  In a higher one an fp32 group of more than 64 rows with a long K takes the
+// level off the narrow tiles (H = 400, 193 rows in three groups: 26.5 / 28.9).
+constexpr int kLevelNarrow = 400, kLevelNarrowWidth = 512;
+struct FwdGroup {
+  int rows, K, gates;
+};
+inline NarrowPlan level_narrow_plan(const FwdGroup* g, int n, int HP, int esize) {
+  NarrowPlan p;
+  int rows = 0, most = 0, gates = 0;
+  for (int k = 0; k < n; ++k) {
+    if (g[k].rows <= 0) continue;
+    rows += g[k].rows;
+    most = std::max(most, g[k].rows);
+    gates = std::max(gates, g[k].gates);
+  }
+  long long long_ones[2] = {0, 0}, tiles[2] = {0, 0};  // by rt - 1
+  for (int k = 0; k < n; ++k) {
+    if (g[k].rows <= 0) continue;
+    if (!narrow_fwd_plan(g[k].rows, HP, g[k].K, esize).rt) return p;
+    if (rows > kOneOrderRows && esize == 4 && g[k].K > kNarrowLongK && g[k].rows > 64) return p;
+    for (int i = 0; i < 2; ++i) {
+      const long long t = (g[k].rows + 16 * i + 15) / (16 * (i + 1));
+      tiles[i] += t;
+      if (gates == 1 || g[k].gates > 1) long_ones[i] += narrow_round(t, HP / 16);
+    }
+  }
+  if (rows == 0) return p;
+  const int i = most <= 48 && long_ones[0] <= kNarrowRound ? 0 : 1;
+  if (rows > kOneOrderRows && long_ones[i] > kNarrowRound &&
+      !(esize == 2 && HP < kLevelNarrowWidth && tiles[1] * (HP / 16) <= kLevelNarrow))
+    return p;
+  p.rt = i + 1;
+  p.units = tiles[i] * (HP / 4) <= kNarrowRound ? 4 : (tiles[i] * (HP / 8) <= kNarrowRound ? 8 : 16);
   return p;
 }
 
