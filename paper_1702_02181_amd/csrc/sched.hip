@@ -411,7 +411,12 @@ __device__ __forceinline__ void run_graph(const L& g, const GraphArgs& a, const 
 template <bool CHECK, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_graph_depth(GraphArgs a, OpTable ops, int lds_bytes) {
   if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 8 == 0) return;  // a pointer array
-  if (!CHECK && *a.err != kNoErr) return;
+  // Another graph's cycle does not end this one (the lowest cyclic graph counts), and must not: it can come in while this
+  // workgroup starts, and then only the waves that read the word later would leave.  Errors of the checks are all in.
+  if constexpr (!CHECK) {
+    const unsigned long long e = __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (e != kNoErr && (e & 0xff) != (unsigned)-FOLD_E_CYCLE) return;
+  }
   extern __shared__ __attribute__((aligned(16))) char links[];
   __shared__ GraphShared sh;
   const int g = blockIdx.x;
@@ -1870,7 +1875,8 @@ __device__ __forceinline__ int t_nout(const TypedOpTable& o, int op) { return op
 
 __global__ void k_typed_check(const int* node_op, const int* in_ptr, const int* in_node, const int* in_slot,
                               const int* node_graph, int N, TypedOpTable ops, unsigned long long* err) {
-  if (*err != kNoErr) return;
+  // a pointer array; another node's error does not end this node's check (the lowest counts)
+  if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 8 == 0) return;
   const int v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= N) return;
   const int op = node_op[v], a = in_ptr[v], b = in_ptr[v + 1];

@@ -110,3 +110,30 @@ def test_errors():
     # two graphs with an edge across them
     assert code((node_op, in_ptr, in_node, in_slot), graph_ptr=np.array([0, 4, 8], np.int32)) == F.FOLD_E_CHILD
     assert code((node_op, in_ptr, in_node, in_slot), o=[([0], [1]), ([1, 1], [1])], T=0) == F.FOLD_E_INVALID
+
+
+@pytest.mark.parametrize("every", [1, 7])
+@pytest.mark.parametrize("fault", ["cycle", "op"])
+def test_lowest_faulty_graph_counts(fault, every):
+    """Many graphs with a fault beside others without: the error names the lowest one (a cycle: its graph's first node),
+    whatever the GPU comes to first."""
+    from paper_1702_02181_amd import fold as F
+    ops, graphs, first = [([0, 0], [0])], 3000, 11
+    node_op, ins, gp = [], [], [0]
+    for g in range(graphs):
+        b = len(node_op)
+        n = 40 if g == first else 3 + g % 5
+        bad = g >= first and (g - first) % every == 0
+        node_op += [-1] + [0] * n
+        ins += [[]] + [[b + v - 1, b + (v + 1 if bad and fault == "cycle" and v == 1 else 0)] for v in range(1, n + 1)]
+        if bad and fault == "op":
+            node_op[-1], ins[-1] = (5, ins[-1]) if g == first else (0, ins[-1][:1])
+        gp.append(len(node_op))
+    in_ptr = np.cumsum([0] + [len(x) for x in ins])
+    in_node = np.array([u for x in ins for u in x])
+    code, node = (F.FOLD_E_CYCLE, gp[first]) if fault == "cycle" else (F.FOLD_E_OP, gp[first + 1] - 1)
+    for _ in range(5):
+        with pytest.raises(F.FoldError) as e:
+            _gpu(gp, (node_op, in_ptr, in_node, np.zeros_like(in_node)), ops, 1)
+        assert e.value.code == code
+        assert f"(node {node})" in str(e.value)
