@@ -170,8 +170,9 @@ typedef struct {
  * the per-group gather indices.  The edge label of the paper (index i into
  * the concatenated outputs of depth d) is the pool row minus
  * level_ptr[d - 1]; pass-throughs are unnecessary because the pool keeps
- * every level.  Synchronises `stream` twice (error flag and depth, then the
- * group table).  On success *out is a new handle to free with
+ * every level.  Synchronises `stream` once (error word, level and group
+ * tables), and once more for a schedule of more than 4,096 levels or groups.
+ * On success *out is a new handle to free with
  * fold_sched_free; on error *out is NULL. */
 int32_t fold_schedule(const fold_batch* batch, hipStream_t stream, fold_sched** out);
 int32_t fold_sched_get_info(const fold_sched* sched, fold_sched_info* out);
@@ -573,9 +574,11 @@ int32_t fold_graph_free(fold_graph* graph);
  * levels with several operations.  fold_level_launches(0) turns this off for
  * every later call in the process (each group then launches alone, as a static
  * graph of one batched operation per node would run); fold_level_launches(1)
- * turns it back on.  Returns the previous setting (1 or 0).  Results are the
- * same either way up to the order of the atomic additions of shared
- * children. */
+ * turns it back on.  Returns the previous setting (1 or 0).  Levels of at most
+ * 128 rows compute the same forward states bit for bit either way; on higher
+ * ones a group's tiles and K slices depend on the groups beside it, so its
+ * states are the same up to the order of their fp32 sums, and gradients up to
+ * that and the order of the atomic additions of shared children. */
 int32_t fold_level_launches(int32_t on);
 
 /* ---- per-kernel timing (profiling aid) ----------------------------------

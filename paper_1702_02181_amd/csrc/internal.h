@@ -94,7 +94,7 @@ __device__ __forceinline__ int fwd_child(const FwdArgs& a, int row, int k) {
 }
 void launch_cell_fwd(int dtype, int kind, const FwdArgs& a, hipStream_t st);
 // The narrow groups of one level (at most kMaxMerge, every one narrow by fwd_plan) as one launch, plus one for
-// their K-split epilogues; kinds as for launch_cell_fwd.
+// their K-split epilogues (none where the level runs on narrow tiles); kinds as for launch_cell_fwd.
 void launch_level_fwd(int dtype, const int* kinds, const FwdArgs* args, int n, hipStream_t st);
 
 // Tiling of one forward group.  Wide groups (at least one workgroup per compute unit) use the wide

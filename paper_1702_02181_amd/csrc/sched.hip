@@ -15,7 +15,8 @@
 // the stream without a host round trip until one read-back at the end: arrays
 // are sized by N (levels and groups never outnumber nodes), the radix passes
 // the actual depth needs are decided on the device, and every kernel after
-// validation returns at once when the error word is set.
+// validation that uses a value as an index returns at once when the error word
+// is set (the scans do not look at it: they add up arrays of fixed length).
 
 #include <hip/hip_runtime.h>
 
@@ -2231,7 +2232,7 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
     scan_exclusive(counts, offsets, N, 2, meta + 2, scan_tmp1, st);
   }
   if (hipGetLastError() != hipSuccess) return device_error("kernel launch failed");
-  // first synchronisation: the error word, the depth, and the sizes of phase 2
+  // first synchronisation: the error word, the depth, and the sizes of phase 2 (no values where the error word is set)
   ErrMeta hm{};
   if (hipMemcpyAsync(&hm, em, sizeof(hm), hipMemcpyDeviceToHost, st) != hipSuccess ||
       hipStreamSynchronize(st) != hipSuccess)

@@ -81,3 +81,18 @@ def test_levels_of_two_operations(dtype, hidden, counts):
         F.fold_level_launches(prev)
     for k in ("h", "c", "roots"):
         assert np.array_equal(whole[k], single[k]), k
+
+
+@pytest.mark.parametrize("dtype,hidden,counts", [("f32", 512, (70, 100)), ("bf16", 512, (256, 256))])
+def test_merged_and_single_above_128_rows(dtype, hidden, counts):
+    """Above 128 rows a group can run on other tiles beside another one than alone (the 70 rows; 512 workgroups together):
+    the order of the sums may then differ, the states match the oracle either way."""
+    w = _chains("lstm+treelstm", counts, hidden, dtype)
+    o = C.run_oracle(w, backward=False)
+    prev = F.fold_level_launches(True)
+    try:
+        for on in (True, False):
+            F.fold_level_launches(on)
+            C.compare_all(w, C.run_device(w, backward=False), o, check_backward=False)
+    finally:
+        F.fold_level_launches(prev)

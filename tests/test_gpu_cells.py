@@ -74,8 +74,9 @@ def test_config5_shape_dag_bf16():
 def test_batching_invariance_on_gpu():
     """Each graph's forward states inside the batch equal, bit for bit, those of the graph scheduled alone and
     those of the batch with its graphs in reverse order; and the batch matches the oracle.  Every level here
-    has at most 128 rows, so alone and in the batch each level runs the same kernel with the same K split,
-    and a row's arithmetic does not depend on the rows around it: batching is a pure rewrite (Section 2)."""
+    has at most 128 rows, so alone and in the batch each level sums K in the same order, and a row's arithmetic
+    does not depend on the rows around it: batching is a pure rewrite (Section 2).  (test_gpu_batch_invariance.py
+    has the widths and row counts at which the tiles change.)"""
     w = gen.config4(num_graphs=6, max_chain=20, hidden=64, in_dim=32)
     g = C.run_device(w, backward=False)
     assert max(np.diff(g["sched"]["level_ptr"])) <= 128
@@ -106,9 +107,9 @@ def test_table1_workloads_forward(mode):
 def test_level_launches_match_one_launch_per_group(case):
     """Levels of several operations run their narrow groups as level launches (one launch for the level's
     contractions, one for its K-split epilogues, one for its cell backwards, one for its dz . W^T).  The
-    forward states equal those of one launch per group (fold_level_launches(0)) bit for bit -- every group
-    runs the same kernel body with the same K split -- and the gradients up to the order of atomic additions;
-    both match the oracle."""
+    forward states equal those of one launch per group (fold_level_launches(0)) bit for bit -- at these sizes
+    every group sums K in the same order either way (always so up to 128 rows a level) -- and the gradients up
+    to the order of atomic additions; both match the oracle."""
     from oracle import compare
     from paper_1702_02181_amd import fold as F
     from tests.test_gpu_random import _random_batch
