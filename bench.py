@@ -45,8 +45,8 @@ PEAKS = {  # MI355X datasheet, dense
 # Sources whose code decides a kernel class's kernels: a traffic record is valid only while they are
 # unchanged.
 CLASS_SOURCES = {
-    "cell_fwd": ("cells.hip", "dma.h", "mfma.h", "wide.h", "common.h", "internal.h"),
-    "bwd_dx": ("cells.hip", "dma.h", "mfma.h", "wide.h", "common.h", "internal.h"),
+    "cell_fwd": ("cells.hip", "dma.h", "mfma.h", "narrow.h", "wide.h", "common.h", "internal.h"),
+    "bwd_dx": ("cells.hip", "dma.h", "mfma.h", "narrow.h", "wide.h", "common.h", "internal.h"),
     "wgrad": ("wgrad.hip", "dma.h", "mfma.h", "wide.h", "common.h", "internal.h"),
 }
 COPY_KERNEL = "k_probe_copy"
@@ -70,12 +70,12 @@ def rocprof_role(kernel_class: str, name: str):
     cls, dt = parts[0], CTYPE[parts[-1]]
     if cls == "cell_fwd":
         kinds = "|".join(str(k) for k in KERNEL_KINDS.get(parts[1], (KIND_IDS[parts[1]],)))
-        if re.search(rf"k_cell_fwd(_w)?<{dt}, ({kinds})[,>]", name):
+        if re.search(rf"k_cell_fwd(_w|_n)?<{dt}, ({kinds})[,>]", name):
             return "main"
         if re.search(rf"k_cell_epi<{dt}, ({kinds})>", name):
             return "extra"
     elif cls == "bwd_dx":
-        if re.search(rf"k_bwd_dx(2|_w)<{dt}[,>]", name):
+        if re.search(rf"k_bwd_dx(2|_w|_n)<{dt}[,>]", name):
             return "main"
     elif cls == "wgrad":
         if re.search(r"k_wgrad_(f32|bf16)(_w)?\b|k_wgrad<", name):

@@ -188,3 +188,20 @@ def test_rocprof_roles_follow_the_library_kind_ids():
     assert bench.rocprof_role("cell_fwd.treelstm.f32", f"{ns}k_cell_epi<float, {leaf}>(fold::FwdArgs, int)") == "extra"
     assert bench.rocprof_role("cell_fwd.treelstm.f32", f"{ns}k_cell_fwd_w<float, 3>(fold::FwdArgs)") is None
     assert bench.rocprof_role("cell_fwd.treelstm.f32", f"{ns}k_cell_fwd_w<unsigned short, 2>(fold::FwdArgs)") is None
+
+
+def test_rocprof_roles_of_every_contraction_kernel():
+    """Every forward and dz . W^T kernel of one group in the library's source counts as a launch of its class: bytes per
+    launch would come out too high without the narrow levels' ones."""
+    import os
+    import re
+    src = open(os.path.join(os.path.dirname(bench.__file__), "paper_1702_02181_amd", "csrc", "cells.hip")).read()
+    fwd = set(re.findall(r"\bvoid (k_cell_fwd\w*)\(FwdArgs", src))
+    dx = set(re.findall(r"\bvoid (k_bwd_dx\w*)\(DxArgs", src))
+    assert {"k_cell_fwd", "k_cell_fwd_w", "k_cell_fwd_n"} <= fwd and {"k_bwd_dx2", "k_bwd_dx_w", "k_bwd_dx_n"} <= dx
+    for k in fwd:
+        assert bench.rocprof_role("cell_fwd.lstm.bf16", f"void {k}<unsigned short, 3, 1, 4>(fold::FwdArgs)") == "main", k
+    for k in dx:
+        assert bench.rocprof_role("bwd_dx.f32", f"void {k}<float, 1, 2>(fold::DxArgs)") == "main", k
+    for f in re.findall(r'#include "(\w+\.h)"', src):
+        assert f in bench.CLASS_SOURCES["cell_fwd"] and f in bench.CLASS_SOURCES["bwd_dx"], f
