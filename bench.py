@@ -195,8 +195,30 @@ def table_runs(w) -> dict:
             for o, op in enumerate(w.ops) if op.has_input}
 
 
-def flops_by_kernel(w, sched_host, table_grad: bool) -> dict:
-    """Algorithmic FLOPs of one forward + backward, by kernel class (2 FLOPs per multiply-add)."""
+def read_gradients(w, host, table_grad: bool):
+    """What of the state gradients a step without gradient outputs has to compute: the groups whose children's dh
+    somebody reads (not where the whole level below is embeddings of a fixed table), and a function (level, arity)
+    that tells whether any child of such a group has a dc that is read (by a cell with a cell state or attention, or
+    by a projection that passes it on)."""
+    from paper_1702_02181_amd import gen
+    levels = host.get("group_level")
+    if levels is None:
+        return set(range(len(host["group_op"]))), lambda level, arity: True
+    kinds = collections.defaultdict(set)
+    for lv, o in zip(levels, host["group_op"]):
+        kinds[int(lv)].add(w.ops[int(o)].kind)
+    dc = {0: False}
+    for lv in sorted(kinds):
+        dc[lv] = any(k not in (gen.KIND_EMBED, gen.KIND_TREERNN) and (k != gen.KIND_PROJ or dc[lv - 1])
+                     for k in kinds[lv])
+    fixed = kinds[1] == {gen.KIND_EMBED} and not table_grad
+    dh = {g for g, lv in enumerate(levels) if not (fixed and int(lv) == 2)}
+    return dh, lambda level, arity: dc[level - 1] if arity < 2 else any(dc[lv] for lv in range(level))
+
+
+def flops_by_kernel(w, sched_host, table_grad: bool, alone=None) -> dict:
+    """Algorithmic FLOPs of one forward + backward, by kernel class (2 FLOPs per multiply-add).  alone: the (pass,
+    group) pairs that ran as launches of their class (the others of a level share a launch of another class)."""
     from paper_1702_02181_amd import gen
     H = w.hidden
     dt = "bf16" if w.dtype == "bf16" else "f32"
@@ -205,9 +227,15 @@ def flops_by_kernel(w, sched_host, table_grad: bool) -> dict:
     def add(k, v):
         out[k] = out.get(k, 0.0) + float(v)
 
-    rows_of_op = {}
-    for op_id, rows in zip(sched_host["group_op"], sched_host["group_rows"]):
-        rows_of_op[int(op_id)] = rows_of_op.get(int(op_id), 0) + int(rows)
+    rows_of_op, fwd_rows, dx_rows = {}, {}, {}
+    dh_read, _ = read_gradients(w, sched_host, table_grad)
+    for g, (op_id, rows) in enumerate(zip(sched_host["group_op"], sched_host["group_rows"])):
+        op_id, rows = int(op_id), int(rows)
+        rows_of_op[op_id] = rows_of_op.get(op_id, 0) + rows
+        if alone is None or ("fwd", g) in alone:
+            fwd_rows[op_id] = fwd_rows.get(op_id, 0) + rows
+        if g in dh_read and (alone is None or ("bwd", g) in alone):
+            dx_rows[op_id] = dx_rows.get(op_id, 0) + rows
     runs = table_runs(w) if (w.backward and table_grad) else {}
     for op_id, rows in rows_of_op.items():
         op = w.ops[op_id]
@@ -217,10 +245,11 @@ def flops_by_kernel(w, sched_host, table_grad: bool) -> dict:
         ps = w.params[op.param_set]
         k_in = (ps.in_dim if op.has_input else 0) + op.arity * H
         name = gen.KIND_NAMES[op.kind]
-        add(f"cell_fwd.{name}.{dt}", 2.0 * rows * k_in * G * H)
+        if op_id in fwd_rows:
+            add(f"cell_fwd.{name}.{dt}", 2.0 * fwd_rows[op_id] * k_in * G * H)
         if w.backward:
-            if op.arity > 0:
-                add(f"bwd_dx.{dt}", 2.0 * rows * G * H * op.arity * H)
+            if op.arity > 0 and op_id in dx_rows:
+                add(f"bwd_dx.{dt}", 2.0 * dx_rows[op_id] * G * H * op.arity * H)
             if op_id in runs:
                 add(f"tgrad.{dt}", 2.0 * runs[op_id] * G * H * ps.in_dim)
             add(f"wgrad.{dt}", 2.0 * rows * k_in * G * H)
@@ -278,13 +307,15 @@ def pass_work(w, host, table_grad: bool) -> dict:
     op), its leaf-table gradient (dz summed per leaf-table row, then one contraction row per distinct row).
     Per node, with S = state bytes (h, plus fp32 c for cells that carry one) and S_g = its fp32
     gradient: forward reads the input row and the children's states and writes S; backward reads S_g
-    and the children's states and writes the children's S_g (plus the leaf-table gradient row).
+    and the children's states and writes the children's S_g (plus the leaf-table gradient row), each as far as
+    anybody reads it (read_gradients).
     Saved activations are implementation overhead, not counted."""
     from paper_1702_02181_amd import gen
     H = w.hidden
     bh = 2 if w.dtype == "bf16" else 4
     out = {}
     op_rows = {}
+    dh_read, child_dc_read = read_gradients(w, host, table_grad)
     for g, (op_id, rows) in enumerate(zip(host["group_op"], host["group_rows"])):
         op, rows = w.ops[int(op_id)], int(rows)
         op_rows[int(op_id)] = op_rows.get(int(op_id), 0) + rows
@@ -301,14 +332,16 @@ def pass_work(w, host, table_grad: bool) -> dict:
         din = w.params[op.param_set].in_dim if op.has_input else 0
         has_c = op.kind in (gen.KIND_TREELSTM, gen.KIND_LSTM, gen.KIND_PROJ)
         s_node = H * (bh + (4 if has_c else 0))
-        sg_node = 4 * H * (2 if has_c else 1)
+        dc = child_dc_read(int(host["group_level"][g]) if "group_level" in host else 0, op.arity)
+        sg_node = 4 * H * (2 if has_c and (dc or op.kind != gen.KIND_PROJ) else 1)
+        sg_child = 4 * H * ((g in dh_read) + (has_c and dc))
         k_in = din + op.arity * H
         out[("fwd", g)] = (2.0 * rows * k_in * G * H,
                            float(rows * (din * bh + op.arity * s_node + s_node) + k_in * G * H * bh + G * H * 4))
         if w.backward:
-            k_dx = op.arity * H
+            k_dx = op.arity * H if g in dh_read else 0
             out[("bwd", g)] = (2.0 * rows * G * H * k_dx,
-                               float(rows * (sg_node + op.arity * (s_node + sg_node)) + k_dx * G * H * bh))
+                               float(rows * (sg_node + op.arity * (s_node + sg_child)) + k_dx * G * H * bh))
     if w.backward and table_grad:
         runs = table_runs(w)
         for o, count in op_rows.items():
@@ -759,7 +792,9 @@ def measure(w, steps: int, warmup: int, table_grad: bool, schedule_reps: int = 5
     for name, _g, _o, ms in launch_times:
         n, tot, mx = stats.get(name, (0, 0.0, 0.0))
         stats[name] = (n + 1, tot + ms, max(mx, ms))
-    flops = flops_by_kernel(w, host, table_grad)
+    alone = {p for name, g, o, _ in launch_times if o >= -1 and class_of(name) in ("cell_fwd", "bwd_dx")
+             for p in pass_of(name, g, o)}
+    flops = flops_by_kernel(w, host, table_grad, alone)
     kernels = {}
     for name, (launches, total_ms, max_ms) in stats.items():
         per_step_ms = total_ms / steps
@@ -803,7 +838,7 @@ def measure(w, steps: int, warmup: int, table_grad: bool, schedule_reps: int = 5
             gbs = by / (kernels[name]["ms_per_step"] * 1e-3) / 1e9
             kernels[name].update(alg_bytes_per_step=round(by), gbs=round(gbs, 1),
                                  hbm_frac=round(gbs / PEAKS["hbm_gbs"], 4))
-    total_flops = sum(flops.values())
+    total_flops = sum(flops_by_kernel(w, host, table_grad).values())
     step_peak = PEAKS["bf16_mfma_tflops"] if w.dtype == "bf16" else PEAKS["f32_mfma_tflops"]
     classes = level_classes(pass_work(w, host, table_grad), launch_times, steps, step_peak, PEAKS["hbm_gbs"])
     out = {

@@ -205,3 +205,36 @@ def test_rocprof_roles_of_every_contraction_kernel():
         assert bench.rocprof_role("bwd_dx.f32", f"void {k}<float, 1, 2>(fold::DxArgs)") == "main", k
     for f in re.findall(r'#include "(\w+\.h)"', src):
         assert f in bench.CLASS_SOURCES["cell_fwd"] and f in bench.CLASS_SOURCES["bwd_dx"], f
+
+
+def test_unread_gradients_are_no_work():
+    """A projection over embeddings of a fixed table contracts nothing backward, and its dc (nobody below has a cell
+    state) is neither read nor passed on; with a trained table, or a cell with a state below, both are."""
+    H = 32
+    w = types.SimpleNamespace(
+        hidden=H, dtype="bf16", backward=True, node_op=[0, 0, 1, 1, 2], node_input=[3, 4, -1, -1, -1],
+        ops=[gen.OpSpec(gen.KIND_EMBED, 0, 1, 0), gen.OpSpec(gen.KIND_PROJ, 1, 0, 1), gen.OpSpec(gen.KIND_TREERNN, 2, 0, 2)],
+        params=[types.SimpleNamespace(in_dim=H)] * 3)
+    host = dict(group_op=[0, 1, 2], group_rows=[2, 2, 1], group_level=[1, 2, 3])
+    S = H * (2 + 4)
+    work = bench.pass_work(w, host, table_grad=False)
+    assert work[("bwd", 1)] == (0.0, 2 * (4 * H + S))
+    assert work[("bwd", 2)] == (2.0 * 1 * H * 2 * H, 1 * (4 * H + 2 * (2 * H + 4 * H)) + 2 * H * H * 2)
+    assert bench.flops_by_kernel(w, host, False)["bwd_dx.bf16"] == 2.0 * 1 * H * 2 * H
+    work = bench.pass_work(w, host, table_grad=True)
+    assert work[("bwd", 1)] == (2.0 * 2 * H * H, 2 * (4 * H + S + 4 * H) + H * H * 2)
+    w.ops[0] = gen.OpSpec(gen.KIND_LSTM, 1, 1, 0)  # first steps of chains in the embeddings' place
+    work = bench.pass_work(w, host, table_grad=False)
+    assert work[("bwd", 1)] == (2.0 * 2 * H * H, 2 * (8 * H + S + 8 * H) + H * H * 2)
+
+
+def test_class_flops_of_launches_of_their_own():
+    """Groups that share a level launch are not counted as work of the one-group launches' class."""
+    H = 64
+    w = _treelstm_workload(H, "f32")
+    host = dict(group_op=[0, 1, 0, 1], group_rows=[4, 2, 3, 1])
+    f = bench.flops_by_kernel(w, host, False, alone={("fwd", 0), ("fwd", 1), ("bwd", 1)})
+    assert f["cell_fwd.treelstm.f32"] == 2.0 * 4 * H * 3 * H + 2.0 * 2 * 2 * H * 5 * H
+    assert f["bwd_dx.f32"] == 2.0 * 2 * 5 * H * 2 * H
+    assert f["wgrad.f32"] == bench.flops_by_kernel(w, host, False)["wgrad.f32"]
+    assert "bwd_dx.f32" not in bench.flops_by_kernel(w, host, False, alone=set())
