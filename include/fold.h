@@ -575,10 +575,11 @@ int32_t fold_graph_free(fold_graph* graph);
  * every later call in the process (each group then launches alone, as a static
  * graph of one batched operation per node would run); fold_level_launches(1)
  * turns it back on.  Returns the previous setting (1 or 0).  Levels of at most
- * 128 rows compute the same forward states bit for bit either way; on higher
- * ones a group's tiles and K slices depend on the groups beside it, so its
- * states are the same up to the order of their fp32 sums, and gradients up to
- * that and the order of the atomic additions of shared children. */
+ * 128 rows compute the same forward states bit for bit either way for hidden
+ * sizes up to 1,024; beyond, a group's tiles and K slices depend on the groups
+ * beside it, so its states are the same up to the order of their fp32 sums,
+ * and gradients up to that and the order of the atomic additions of shared
+ * children. */
 int32_t fold_level_launches(int32_t on);
 
 /* ---- per-kernel timing (profiling aid) ----------------------------------

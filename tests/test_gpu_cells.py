@@ -108,7 +108,7 @@ def test_level_launches_match_one_launch_per_group(case):
     """Levels of several operations run their narrow groups as level launches (one launch for the level's
     contractions, one for its K-split epilogues, one for its cell backwards, one for its dz . W^T).  The
     forward states equal those of one launch per group (fold_level_launches(0)) bit for bit -- at these sizes
-    every group sums K in the same order either way (always so up to 128 rows a level) -- and the gradients up
+    every group sums K in the same order either way (always so up to 128 rows and H = 1,024) -- and the gradients up
     to the order of atomic additions; both match the oracle."""
     from oracle import compare
     from paper_1702_02181_amd import fold as F

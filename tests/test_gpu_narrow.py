@@ -45,3 +45,15 @@ def test_narrow_levels(dtype, hidden, rows, mixed):
     w = _levels(rows, hidden, dtype, mixed)
     errs = C.compare_all(w, C.run_device(w), C.run_oracle(w))
     print(dtype, hidden, rows, mixed, errs)
+
+
+@pytest.mark.parametrize("dtype,hidden,rows,mixed", [
+    ("f32", 1024, 33, False), ("f32", 768, 128, False), ("f32", 700, 65, True),
+    ("bf16", 1024, 64, False), ("bf16", 768, 128, False), ("bf16", 1024, 40, True), ("bf16", 1100, 20, False),
+])
+def test_narrow_levels_of_wide_states(dtype, hidden, rows, mixed):
+    """The same for states wider than 512: single and double row tiles of 4 to 16 units, and a width past the forward's
+    limit whose dz . W^T alone is narrow."""
+    w = _levels(rows, hidden, dtype, mixed)
+    errs = C.compare_all(w, C.run_device(w), C.run_oracle(w))
+    print(dtype, hidden, rows, mixed, errs)
