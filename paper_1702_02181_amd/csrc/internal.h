@@ -207,27 +207,6 @@ inline FwdPlan fwd_plan(int rows, int HP, int inp_used, int arity, int gates, in
   p.wide = ((long long)(rows + 255) / 256) * (ub / 2) >= 256;
   if (p.wide) return p;
   const long long base = ((long long)(rows + 127) / 128) * ub;
-  // fp32 cells of several gates: the matrix cores are the bound, so a level takes as long as its fullest compute unit
-  // has tiles to do (288 tiles as long as 512).  K is cut where a shorter last round saves more than the partial sums
-  // cost (written and read once at about 4.5 TB/s, 5 us for the second launch; a tile takes 0.436 us per gate and 128
-  // bytes of K).  TreeLSTM, H = 1,024, us a level before -> now: 257 rows 125 -> 99, 557 rows 183 -> 137, 1,062 rows
-  // 331 -> 246, 2,112 rows 500 -> 461 (256 trees of 64 leaves: 4.92 -> 4.63 ms); no level of H = 64 .. 2,048 and 150 ..
-  // 19,200 rows got slower.  Whole row tiles are counted, so that levels of up to 128 rows split alike.  Under 96 tiles
-  // the rule below is better (H = 256, 900 leaves: 20 us against 25), and for one gate, whose tiles share a compute
-  // unit (H = 512, 900 rows: 22 against 30).
-  if (can_split && esize == 4 && gates > 1 && nst >= 4 && base >= 96) {
-    const double tile = 0.436 * gates * nst, part = (double)((rows + 127) / 128 * 128) * gates * HP * 8 / 4.5e6;
-    double best = 0;
-    for (int ks = 1; ks <= std::min(8, nst / 2); ++ks) {
-      const double cost = (double)((base * ks + 255) / 256) * ((nst + ks - 1) / ks) / nst * tile +
-                          (ks > 1 ? part * ks + 5.0 : 0.0);
-      if (ks == 1 || cost < 0.95 * best) {
-        best = cost;
-        p.ksplit = ks;
-      }
-    }
-    return p;
-  }
   if (can_split && base < 192 && nst >= 4) {
     // aim at a workgroup per compute unit; a bf16 group alone with a short K (under 16 stages of 128 bytes) at
     // half of that: its slices are short, and the partial sums cost more than the extra workgroups gain
@@ -235,6 +214,32 @@ inline FwdPlan fwd_plan(int rows, int HP, int inp_used, int arity, int gates, in
     const long long aim = alone && esize == 2 && nst < 16 ? 128 : 256;
     const long long want = (aim + base - 1) / base;
     p.ksplit = (int)std::min<long long>(want, nst / 2);
+  }
+  // fp32 cells of several gates: the matrix cores are the bound, so a level takes as long as its fullest compute unit
+  // has tiles to do.  Another split than the one above is taken where that saves clearly more than the partial sums cost:
+  // a tile takes 0.436 us per gate and 128 bytes of K, the partial sums are written and read once at about 5 TB/s, the
+  // second launch costs 2 us, and 6 % is what the estimate is off by.  Tiles are counted as the XCDs take them: each owns
+  // an eighth of the row tiles or of the columns, rounded up (cell_fwd_kind), so 10 columns load the fullest like 16.  us
+  // a level of TreeLSTM, event overhead of 5 us a launch included, with the split above / this one: H = 256 1,627 rows 54 /
+  // 44, H = 448 859 rows 75 / 60, H = 768 603 rows 108 / 89, H = 1,024 1,115 rows 347 / 271 (256 trees of 64 leaves at H =
+  // 1,024: 4.92 / 4.63 ms).  Counted without the rounding, H = 320 1,243 rows took 74 in place of 62, H = 640 731 rows 127
+  // in place of 100.  Over 304 levels (H = 64 .. 1,024, 96 tiles and more) the split is within 1 % of the best one on
+  // average (13 % without this rule), and slower than without it on three (H = 192, 2,139 .. 2,523 rows: 48 / 45).
+  // Whole row tiles are counted, so that levels of up to 128 rows split alike.  Under 96 tiles the estimate was not
+  // measured; for one gate, whose tiles share a compute unit, it is wrong (H = 512, 900 rows: 22 against 30).
+  if (can_split && esize == 4 && gates > 1 && nst >= 4 && base >= 96) {
+    const long long R = (rows + 127) / 128;
+    const long long own = rows >= gates * HP ? (R + 7) / 8 * ub : (ub + 7) / 8 * R;  // tiles of the fullest XCD
+    const double tile = 0.436 * gates * nst, part = (double)(R * 128) * gates * HP * 8 / 5e6;
+    auto cost = [&](int ks) {
+      return (double)((own * ks + 31) / 32) * ((nst + ks - 1) / ks) / nst * tile + (ks > 1 ? part * ks + 2.0 : 0.0);
+    };
+    double best = 0.94 * cost(p.ksplit);
+    for (int ks = 1; ks <= std::min(8, nst / 2); ++ks)
+      if (const double c = cost(ks); c < best) {
+        best = c;
+        p.ksplit = ks;
+      }
   }
   return p;
 }

@@ -16,3 +16,11 @@ def test_level_split(hidden, rows, mixed):
     w = _levels(rows, hidden, "f32", mixed)
     errs = C.compare_all(w, C.run_device(w), C.run_oracle(w))
     print(hidden, rows, mixed, errs)
+
+
+@pytest.mark.parametrize("hidden,rows", [(320, 1243), (370, 1115), (640, 731)])
+def test_level_split_of_widths_between_xcd_shares(hidden, rows):
+    """Widths whose columns do not divide by the eight XCDs: the slices are counted by the fullest one."""
+    w = _levels(rows, hidden, "f32", False)
+    errs = C.compare_all(w, C.run_device(w), C.run_oracle(w))
+    print(hidden, rows, errs)
