@@ -268,9 +268,11 @@ typedef struct {
  * op table, graph_ptr / in_ptr, an edge from a missing node or output or of
  * the wrong type, a constant with inputs or an operation node with the wrong
  * input count; FOLD_E_CHILD for an edge across graphs; FOLD_E_OP for an
- * operation or constant type out of range; FOLD_E_CYCLE), then schedules it
+ * operation or constant type out of range; FOLD_E_CYCLE; FOLD_E_INVALID for
+ * a batch whose nodes, edges and pass-throughs reach 2^31), then schedules it
  * on the GPU.  The library allocates and owns the result.  Synchronises
- * `stream` twice: once to size the pass-through arrays, once at the end. */
+ * `stream` twice: once to size the pass-through arrays, once at the end (a
+ * third time where values times levels reach 2^31). */
 int32_t fold_schedule_typed(const fold_typed_batch* batch, hipStream_t stream, fold_typed_sched** out);
 int32_t fold_typed_sched_get_info(const fold_typed_sched* sched, fold_typed_sched_info* out);
 /* Waits and keeps memory as fold_sched_free. */

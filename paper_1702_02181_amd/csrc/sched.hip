@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cstring>
 
 #include "common.h"
@@ -1944,6 +1945,14 @@ __global__ void k_typed_npass(const int* depth, const int* nout_v, const int* la
   npass[v] = n;
 }
 
+// all of them in 64 bits (total starts at -1, the error word "none")
+__global__ void k_typed_pass_total(const int* npass, int N, unsigned long long* total) {
+  unsigned long long s = 0;
+  for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < N; v += gridDim.x * blockDim.x) s += (unsigned)npass[v];
+  for (int d = kWave / 2; d; d >>= 1) s += __shfl_xor(s, d);
+  if ((threadIdx.x & (kWave - 1)) == 0 && s) atomicAdd(total, s);
+}
+
 // the instances, and the first one of every value
 __global__ void k_typed_pass_emit(const int* depth, const int* nout_v, const int* val_ptr, const int* last,
                                   const int* node_pass, int N, int* pass_ptr, int* pass_node, int* pass_slot,
@@ -2246,6 +2255,20 @@ int32_t schedule_typed_impl(const fold_typed_batch* b, hipStream_t st, fold_type
   const int D = N > 0 ? hm.meta[0] - 1 : 0;
   const int V = N > 0 ? hm.meta[2] : 0;
   const int P = N > 0 ? hm.meta[3] : 0;
+  // 32-bit counts hold the rows of any batch whose values could not pass through every depth; of the others (deep graphs)
+  // the pass-throughs are counted again
+  if ((long long)V * D + N + E > INT_MAX) {
+    unsigned long long total = 0;
+    hipLaunchKernelGGL(k_typed_pass_total, dim3(std::min(256, N / kBlock + 1)), dim3(kBlock), 0, st, npass, N, &em->cycle);
+    if (hipGetLastError() != hipSuccess ||
+        hipMemcpyAsync(&total, &em->cycle, sizeof(total), hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess)
+      return device_error("device error while counting pass-throughs");
+    if ((total += 1) + N + E > INT_MAX) {
+      set_error("fold_schedule_typed: " + std::to_string(total) + " pass-throughs (rows and edges with them have to stay below 2^31)");
+      return fail(FOLD_E_INVALID);
+    }
+  }
   if ((long long)(D + 1) * (K + T) > kMaxKeys) {
     set_error("fold_schedule_typed: depth * (operations + types) exceeds 2^30 (the sort keys)");
     return fail(FOLD_E_INVALID);

@@ -137,3 +137,27 @@ def test_lowest_faulty_graph_counts(fault, every):
             _gpu(gp, (node_op, in_ptr, in_node, np.zeros_like(in_node)), ops, 1)
         assert e.value.code == code
         assert f"(node {node})" in str(e.value)
+
+
+@pytest.mark.parametrize("readers", [0, 1])
+def test_pass_throughs_past_32_bits(readers):
+    """A chain of 2 m operations, deep enough that they are counted in 64 bits: without other readers there are none; where
+    its upper half reads the lower half too there are m (m - 1), 2.5e9, which is refused before an array is sized by a
+    count that wrapped."""
+    from paper_1702_02181_amd import fold as F
+    m, ops = 50000, [([0], [0]), ([0, 0], [0])]
+    v = np.arange(1, 2 * m + 1)
+    up = (v > m) & bool(readers)
+    node_op = np.concatenate([[-1], np.where(up, 1, 0)])
+    in_ptr = np.concatenate([[0, 0], np.cumsum(np.where(up, 2, 1))])
+    in_node = np.stack([v - 1, np.where(up, v - m, -1)], 1).ravel()
+    in_node = in_node[in_node >= 0]
+    g = (node_op, in_ptr, in_node, np.zeros_like(in_node))
+    if readers:
+        with pytest.raises(F.FoldError, match=f"{m * (m - 1)} pass-throughs") as e:
+            _gpu([0, len(node_op)], g, ops, 1)
+        assert e.value.code == F.FOLD_E_INVALID
+    else:
+        got = _gpu([0, len(node_op)], g, ops, 1)
+        assert got["num_levels"] == 2 * m and len(got["pass_node"]) == 0
+        assert np.array_equal(got["item_node"], v) and not got["gather"].any()
