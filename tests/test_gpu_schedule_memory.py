@@ -28,7 +28,7 @@ def _free_bytes():
 def test_trim_gives_idle_memory_back():
     import torch
     w = gen.config2(num_graphs=1200, leaves=128, hidden=2)  # 306,000 nodes: blocks of some 40 and 50 MB
-    F.fold_trim()  # earlier schedules' blocks: the driver does not show those of less than its own 2 MB chunks as free
+    F.fold_trim()  # earlier schedules' blocks: those of less than 2 MB share allocations of the GPU driver and do not show as free
     keep = _make(w)
     other = _make(w)
     want = C.oracle_schedule(w)
